@@ -1,7 +1,7 @@
 // Offline kernels: re-tiling of the base weight, compression of one expert's delta
 // (Eq. 1 per output channel, fp16 salient columns -- Section 4.1), its inverse for tests,
-// and the salient-channel selection of Eq. 2.  None of these is on the serving path;
-// they are written for clarity and exact (fp64) arithmetic, not for speed.
+// and the salient-channel selection of Eq. 2.  None of these is on the serving path; all of them are bound by the
+// bytes of the delta matrix, with results that are exact (codes) or summed in fp64 (scores).
 #include "mes_internal.h"
 
 #include <hip/hip_fp16.h>
@@ -78,48 +78,116 @@ __global__ void k_unpack_base(const uint4* __restrict__ t, int d_in, int d_out, 
 
 // ---- delta compression -----------------------------------------------------------------------------
 
-__global__ void k_check_salient(const int32_t* __restrict__ sidx, int k, int d_in, int* flag) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= k) return;
-  int v = sidx[i];
-  bool bad = v < 0 || v >= d_in || (i > 0 && sidx[i - 1] >= v);
-  if (bad) atomicOr(flag, 1);
+// ---- a code without the fp64 division --------------------------------------------------------------
+// quant_code() decides floor(w / s) (or the nearest integer, ties to even) on the fp64 quotient, which is the exact
+// decision: w and s have 24 significant bits, so a quotient of magnitude >= 1 that is no integer (or half integer) is
+// further than 2^-49 from one, which fp64 resolves.  The same decision in fp32: m is estimated from the rounded
+// quotient (reciprocal and product err by less than 2^-22 relative) pushed upwards by 2^-21, so that it is the right
+// integer or one more, and corrected with one fused multiply-add whose sign is that of the exact w - m s (nothing
+// underflows while s is far from the ends of fp32's range).  Returns the clamped m, -2^(b-1) <= m < 2^(b-1), as a
+// float; infinities clamp and NaN gives the lowest code, as quant_code() has it.
+__device__ __forceinline__ bool fast_step(float s) { return s >= 0x1p-100f && s <= 0x1p100f; }
+
+template <int BITS, bool EQ1>
+__device__ __forceinline__ float clamped_cell(float w, float s, float inv_s) {
+  constexpr float kHalf = (float)(1 << (BITS - 1));
+  const float v = w * inv_s;
+  float m = __builtin_fmaf(__builtin_fabsf(v), 0x1p-21f, v);
+  if constexpr (EQ1) {
+    m = __builtin_floorf(m + 0.5f);
+    const float r = __builtin_fmaf(0.5f - m, s, w);          // w - (m - 1/2) s
+    const float hm = 0.5f * m;
+    const bool odd = __builtin_floorf(hm) != hm;
+    m -= (r < 0.0f || (r == 0.0f && odd)) ? 1.0f : 0.0f;
+  } else {
+    m = __builtin_floorf(m);
+    const float r = __builtin_fmaf(-m, s, w);                // w - m s
+    m -= r < 0.0f ? 1.0f : 0.0f;
+  }
+  return __builtin_fminf(__builtin_fmaxf(m, -kHalf), kHalf - 1.0f);
 }
 
-// One block per output channel.  MAXABS: exact max over the non-salient columns, then one fp64
-// division.  MEANABS: ascending sequential fp64 sum (thread 0), so the order is defined.
-__global__ void k_row_step(const float* __restrict__ delta, int d_in, const int32_t* __restrict__ sidx, int k,
-                           int bits, int grid, int policy, const float* __restrict__ step_in,
-                           float* __restrict__ step_out) {
-  const int row = blockIdx.x;
-  const float* r = delta + (size_t)row * d_in;
-  if (policy == MES_STEP_GIVEN) {
-    if (threadIdx.x == 0) { float s = step_in[row]; step_out[row] = s > 0.0f ? s : 0.0f; }
-    return;
-  }
-  if (policy == MES_STEP_MEANABS) {
-    if (threadIdx.x == 0) {
-      double tot = 0.0; int cnt = 0;
-      for (int c = 0; c < d_in; ++c)
-        if (!is_salient(sidx, k, c, nullptr)) { tot += (double)fabsf(r[c]); ++cnt; }
-      step_out[row] = cnt ? (float)(2.0 * (tot / (double)cnt)) : 0.0f;
-    }
-    return;
-  }
-  __shared__ float red[256];
+// Four consecutive floats.  The caller's matrix need not be 16-byte aligned (its rows are multiples of 32 bytes).
+__device__ __forceinline__ float4 load4(const float* p, bool aligned) {
+  if (aligned) return *reinterpret_cast<const float4*>(p);
+  return make_float4(p[0], p[1], p[2], p[3]);
+}
+
+__device__ __forceinline__ float max4(float m, float4 v) {
+  return fmaxf(fmaxf(fmaxf(m, fabsf(v.x)), fmaxf(fabsf(v.y), fabsf(v.z))), fabsf(v.w));
+}
+
+__device__ __forceinline__ float wave_max(float m) {
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) m = fmaxf(m, __shfl_xor(m, off));
+  return m;
+}
+
+__device__ __forceinline__ float maxabs_step(float m, int bits, bool eq1) {
+  const double div = eq1 ? (double)(1 << (bits - 1)) - 1.0 : (double)(1 << (bits - 1)) - 0.5;
+  return (float)((double)m / div);
+}
+
+// Salient selection: Eq. 1's initialisation max|X| / D over the whole row, one block per output channel.
+__global__ __launch_bounds__(256) void k_row_maxabs(const float* __restrict__ delta, int d_in, int bits, int grid,
+                                                    bool aligned, float* __restrict__ step_out) {
+  const float* r = delta + (size_t)blockIdx.x * d_in;
   float m = 0.0f;
-  for (int c = threadIdx.x; c < d_in; c += blockDim.x)
-    if (!is_salient(sidx, k, c, nullptr)) m = fmaxf(m, fabsf(r[c]));
-  red[threadIdx.x] = m;
+  for (int c = 4 * threadIdx.x; c < d_in; c += 1024) m = max4(m, load4(r + c, aligned));
+  __shared__ float red[4];
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
+  if (threadIdx.x == 0) step_out[blockIdx.x] = maxabs_step(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), bits, grid == MES_GRID_EQ1);
+}
+
+// b = 1: step = 2 mean|w| over the non-salient columns.  The fp64 sum runs over a row's columns in ascending order
+// (the stored step is the rounding of exactly that sum), so the columns of a row cannot be shared out; the rows can:
+// wavefront 0 of a block sums 64 rows, one per lane, out of LDS, while all four wavefronts bring in the next 64
+// columns.  A salient column counts as + 0, which leaves the sum as it is.
+__global__ __launch_bounds__(256) void k_row_meanabs(const float* __restrict__ delta, int d_in, int d_out,
+                                                     const int32_t* __restrict__ sidx, int k, bool aligned,
+                                                     float* __restrict__ step_out) {
+  __shared__ float tile[2][64][65];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int row_l = tid >> 2, c_l = 16 * (tid & 3);
+  const int row = 64 * blockIdx.x + row_l;
+  const float* r = delta + (size_t)(row < d_out ? row : d_out - 1) * d_in;
+  float4 v[4];
+  auto load = [&](int c0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int c = c0 + c_l + 4 * i;
+      v[i] = c < d_in ? load4(r + c, aligned) : make_float4(0, 0, 0, 0);   // d_in % 8 == 0
+    }
+  };
+  load(0);
+  int pos = 0;                                             // salient indices before this thread's columns
+  double tot = 0.0;
+  for (int c0 = 0, buf = 0; c0 < d_in; c0 += 64, buf ^= 1) {
+    float a[16];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { a[4 * i] = v[i].x; a[4 * i + 1] = v[i].y; a[4 * i + 2] = v[i].z; a[4 * i + 3] = v[i].w; }
+    while (pos < k && sidx[pos] < c0 + c_l) ++pos;
+    uint32_t sal = 0;
+    for (int q = pos; q < k; ++q) {
+      const int e = sidx[q] - (c0 + c_l);
+      if (e < 0 || e >= 16) break;
+      sal |= 1u << e;
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) tile[buf][row_l][c_l + e] = (sal >> e) & 1u ? 0.0f : fabsf(a[e]);
+    load(c0 + 64);
     __syncthreads();
+    // one barrier per tile: the buffer written next was last read before this barrier
+    if (tid < 64) {
+      const int n = d_in - c0 < 64 ? d_in - c0 : 64;
+#pragma unroll 8
+      for (int e = 0; e < n; ++e) tot += (double)tile[buf][lane][e];
+    }
   }
-  if (threadIdx.x == 0) {
-    double div = grid == MES_GRID_SYM ? (double)(1 << (bits - 1)) - 0.5 : (double)(1 << (bits - 1)) - 1.0;
-    step_out[row] = (float)((double)red[0] / div);
-  }
+  const int out = 64 * blockIdx.x + lane, cnt = d_in - k;
+  if (tid < 64 && out < d_out) step_out[out] = cnt > 0 ? (float)(2.0 * (tot / (double)cnt)) : 0.0f;
 }
 
 // Where the code of (row, col) is stored (see mes.h, "codes").  Blocks of 16 rows x 128 columns, chunk-major;
@@ -155,53 +223,161 @@ __device__ __forceinline__ CodeLoc code_location(int bits, int n_jt, int row, in
   return L;
 }
 
-// One thread per (row, 8 consecutive columns): quantise and OR the codes into their words (the buffer was
-// zeroed before; words are shared by threads, hence atomicOr).
-__global__ void k_pack_codes(const float* __restrict__ delta, int d_in, int d_out, const int32_t* __restrict__ sidx,
-                             int k, int bits, int grid, const float* __restrict__ step, int n_jt,
-                             uint32_t* __restrict__ out) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int groups = d_in / 8;
-  if (idx >= (size_t)d_out * groups) return;
-  const int row = (int)(idx / groups), col0 = (int)(idx % groups) * 8;
-  const float s = step[row];
-  const float* r = delta + (size_t)row * d_in;
-  uint32_t lo_bits = 0, hi_bits = 0;
-  const CodeLoc L0 = code_location(bits, n_jt, row, col0);   // the 8 columns share both words
-  for (int pp = 0; pp < 8; ++pp) {
-    const int col = col0 + pp;
-    if (is_salient(sidx, k, col, nullptr)) continue;
-    const uint32_t u = quant_code(r[col], s, bits, grid);
-    const CodeLoc L = code_location(bits, n_jt, row, col);
-    lo_bits |= (bits >= 3 ? (u & 3u) : u) << L.lo_shift;
-    if (bits >= 3) hi_bits |= (u >> 2) << L.hi_shift;
-  }
-  if (lo_bits) atomicOr(out + L0.lo_word, lo_bits);
-  if (bits >= 3 && hi_bits) atomicOr(out + L0.hi_word, hi_bits);
-}
+struct PackParams {
+  const float* delta;
+  const int32_t* sidx;
+  const float* step_in;     // GIVEN: the caller's steps (may be step_out); MEANABS: step_out, already written
+  float* step_out;
+  uint32_t* codes;
+  uint16_t* sal;
+  int* flag;                // set to 1 by block 0 if the salient list is not strictly ascending inside [0, d_in), else to 0
+  int d_in, d_out, k, n_jt, n_chunks, n_sb, policy;
+  bool aligned;             // delta is 16-byte aligned
+};
 
-// `flag` was written by k_check_salient earlier on the same stream: with indices that failed the check
-// nothing is gathered (an index is never used as an address unless the whole list is valid).
-__global__ void k_pack_salient(const float* __restrict__ delta, int d_in, int d_out, const int32_t* __restrict__ sidx,
-                               int k, int n_sb, size_t n_elems, const int* __restrict__ flag,
-                               uint16_t* __restrict__ out) {
-  size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n_elems) return;
-  if (*flag) { out[idx] = 0; return; }
-  int e = (int)(idx & 7);
-  int lane = (int)((idx >> 3) & 63);
-  size_t blk = idx >> 9;
-  int sb = (int)(blk % n_sb);
-  int jt = (int)(blk / n_sb);
-  int row = 16 * jt + (lane & 15);
-  int rc = 32 * sb + 8 * (lane >> 4) + e;
-  uint16_t v = 0;
-  if (row < d_out && rc < k) {
-    const int col = min(max(sidx[rc], 0), d_in - 1);
-    __half h = __float2half_rn(delta[(size_t)row * d_in + col]);
-    v = __half_as_ushort(h);
+// The value of the lane `CTRL` names (a permutation inside every 8 lanes) or'ed to this lane's.
+template <int CTRL>
+__device__ __forceinline__ uint32_t or_lanes(uint32_t v) {
+  return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror8 = 0x141;   // quad_perm [1,0,3,2], [2,3,0,1]; row_half_mirror
+
+// Compression of one output channel per block, in one pass over the delta: the row is read once into registers
+// (4 NV values per thread), its largest non-salient magnitude gives the step, the codes are formed from the registers,
+// the fp16 salient values are picked out of the row.  Rows and columns of padding are written as zeros, so nothing
+// has to be cleared before.
+// Bound by the bytes of the delta matrix: 4096 x 14336 at 2 bits in 62 us (4.0 TB/s; six launches that read the row
+// twice, searched the salient list for every element and divided in fp64: 719 us).
+// A thread owns 4 consecutive columns per pass (16-byte loads, coalesced); the 8 threads of a 32-column group or
+// their bits together through lane permutations and the first of them stores the group's words (see mes.h, "codes").
+// The 16 rows of a row tile share every 128-byte line of code words, so their blocks are given ids 8 apart: those go
+// to one XCD at about the same time, and its L2 holds whole lines when it writes them back.
+// NV = 0: rows longer than 64 values per thread; the row is read a second time instead.
+template <int BITS, bool EQ1, int NT, int NV>
+__global__ __launch_bounds__(NT) void k_pack_rows(const PackParams p) {
+  constexpr int kNW = NT / 64;
+  __shared__ uint32_t mask[NV > 0 ? NT * NV / 8 : 1];      // one bit per column: salient
+  __shared__ float red[kNW];
+  const int tid = threadIdx.x, b = blockIdx.x;
+  const int jt = (b >> 7) * 8 + (b & 7), r = (b >> 3) & 15, row = 16 * jt + r;
+  if (jt >= p.n_jt) return;                                // row tiles are dealt in eights
+  const bool real = row < p.d_out;
+  const float* drow = p.delta + (size_t)(real ? row : 0) * p.d_in;
+  float4 v[NV > 0 ? NV : 1];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = 4 * (i * NT + tid);
+    v[i] = real && c < p.d_in ? load4(drow + c, p.aligned) : make_float4(0, 0, 0, 0);
   }
-  out[idx] = v;
+  bool bad = false;
+  if (p.k > 0) {
+    if constexpr (NV > 0) {
+      for (int w = tid; w < NT * NV / 8; w += NT) mask[w] = 0;
+      __syncthreads();
+    }
+    int mine = 0;
+    for (int i = tid; i < p.k; i += NT) {
+      const int c = p.sidx[i];
+      const bool in = c >= 0 && c < p.d_in;
+      mine |= !in || (i > 0 && p.sidx[i - 1] >= c);
+      if constexpr (NV > 0) { if (in) atomicOr(&mask[c >> 5], 1u << (c & 31)); }
+    }
+    bad = __syncthreads_or(mine) != 0;
+  }
+  if (b == 0 && tid == 0) *p.flag = bad ? 1 : 0;
+  // the salient bits of the 4 columns from c on
+  auto salient4 = [&](int c) -> uint32_t {
+    if (p.k == 0) return 0;
+    if constexpr (NV > 0) return (mask[c >> 5] >> (c & 31)) & 15u;
+    uint32_t m = 0;
+    for (int e = 0; e < 4; ++e) m |= is_salient(p.sidx, p.k, c + e, nullptr) ? 1u << e : 0u;
+    return m;
+  };
+  auto values = [&](int i, int c) -> float4 {
+    if constexpr (NV > 0) return v[i];
+    return real && c < p.d_in ? load4(drow + c, p.aligned) : make_float4(0, 0, 0, 0);
+  };
+  const int n_pass = NV > 0 ? NV : (p.d_in + 4 * NT - 1) / (4 * NT);
+
+  float s = 0.0f;
+  if (p.policy == MES_STEP_MAXABS) {
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < n_pass; ++i) {
+      const int c = 4 * (i * NT + tid);
+      float4 a = values(i, c);
+      const uint32_t sal = c < p.d_in ? salient4(c) : 0;
+      if (sal) {
+        if (sal & 1) a.x = 0.0f;
+        if (sal & 2) a.y = 0.0f;
+        if (sal & 4) a.z = 0.0f;
+        if (sal & 8) a.w = 0.0f;
+      }
+      m = max4(m, a);
+    }
+    m = wave_max(m);
+    if (kNW > 1) {
+      if ((tid & 63) == 0) red[tid >> 6] = m;
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kNW; ++w) m = fmaxf(m, red[w]);
+    }
+    s = maxabs_step(m, BITS, EQ1);
+  } else if (real) {
+    s = p.step_in[row];
+    if (p.policy == MES_STEP_GIVEN) s = s > 0.0f ? s : 0.0f;
+  }
+  __syncthreads();                                         // step_in may be step_out: every thread has read it
+  if (real && tid == 0 && p.policy != MES_STEP_MEANABS) p.step_out[row] = s;
+
+  const bool fast = fast_step(s);
+  const float inv_s = fast ? 1.0f / s : 0.0f;
+  constexpr float kHalf = (float)(1 << (BITS - 1));
+  const int li = tid & 7;                                  // this thread's columns inside its group of 32: 4 li ..
+  const int q = li >> 1, p0 = 4 * (li & 1);
+#pragma unroll
+  for (int i = 0; i < n_pass; ++i) {
+    const int c = 4 * (i * NT + tid);
+    const float4 a = values(i, c);
+    const float w[4] = {a.x, a.y, a.z, a.w};
+    const uint32_t skip = real && c < p.d_in ? salient4(c) : 15u;
+    uint32_t lo = 0, hi = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      uint32_t u;
+      if (fast) u = (uint32_t)(int)(clamped_cell<BITS, EQ1>(w[e], s, inv_s) + kHalf);
+      else u = quant_code(w[e], s, BITS, EQ1 ? MES_GRID_EQ1 : MES_GRID_SYM);
+      u = (skip >> e) & 1u ? 0u : u;
+      if constexpr (BITS == 1) lo |= u << (4 * e);
+      else lo |= (u & 3u) << (4 * e);
+      if constexpr (BITS >= 3) hi |= (u >> 2) << (4 * e);
+    }
+    lo <<= 4 * p0 + (BITS == 1 ? q : 2 * (q & 1));
+    if constexpr (BITS >= 3) hi <<= 4 * p0 + (BITS == 3 ? q : 2 * (q & 1));
+    lo = or_lanes<kDppXor2>(or_lanes<kDppXor1>(lo));       // the 16 columns of four lanes
+    if constexpr (BITS >= 3) hi = or_lanes<kDppXor2>(or_lanes<kDppXor1>(hi));
+    uint32_t lo2 = 0, hi2 = 0;                             // two-word planes: the other 16 columns' word
+    if constexpr (BITS == 1) lo = or_lanes<kDppMirror8>(lo);
+    else lo2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, kDppMirror8, 0xf, 0xf, true);
+    if constexpr (BITS == 3) hi = or_lanes<kDppMirror8>(hi);
+    if constexpr (BITS == 4) hi2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, kDppMirror8, 0xf, 0xf, true);
+    const int chunk = c >> 7, lane = 16 * ((c >> 5) & 3) + r;
+    if (li == 0 && chunk < p.n_chunks) {
+      uint32_t* blk = p.codes + ((size_t)chunk * p.n_jt + jt) * (64 * BITS);
+      if constexpr (BITS == 1) blk[lane] = lo;
+      else *reinterpret_cast<uint2*>(blk + 2 * lane) = make_uint2(lo, lo2);
+      if constexpr (BITS == 3) blk[128 + lane] = hi;
+      if constexpr (BITS == 4) *reinterpret_cast<uint2*>(blk + 128 + 2 * lane) = make_uint2(hi, hi2);
+    }
+  }
+
+  // fp16 salient values of this row: rank rc sits in block rc / 32, lane 16 ((rc / 8) % 4) + r, element rc % 8.  With
+  // a list that failed the check nothing is gathered (an index is an address only if the whole list is valid).
+  for (int rc = tid; rc < 32 * p.n_sb; rc += NT) {
+    uint16_t h = 0;
+    if (real && !bad && rc < p.k) h = __half_as_ushort(__float2half_rn(drow[p.sidx[rc]]));
+    p.sal[(((size_t)jt * p.n_sb + (rc >> 5)) * 64 + 16 * ((rc >> 3) & 3) + r) * 8 + (rc & 7)] = h;
+  }
 }
 
 __device__ __forceinline__ uint32_t load_code(const uint32_t* codes, int bits, int n_jt, int row, int col) {
@@ -234,48 +410,129 @@ __global__ void k_unpack_delta(const uint32_t* __restrict__ codes, const float* 
 
 // ---- salient selection (Eq. 2) ------------------------------------------------------------------------
 // score_i = (sum_t x_ti^2) * (sum_j (D_ji - Dhat_ji)^2): the same number as the double sum of Eq. 2,
-// since x_ti factors out of each squared term.  One thread per input channel, ascending fp64 sums.
-__global__ void k_scores(const float* __restrict__ delta, const float* __restrict__ xc, int n, int d_in, int d_out,
-                         int bits, int grid, const float* __restrict__ step, double* __restrict__ score) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d_in) return;
-  const double z = zero_point(bits, grid);
-  double err = 0.0;
-  for (int j = 0; j < d_out; ++j) {
-    float w = delta[(size_t)j * d_in + i];
-    float s = step[j];
-    double wh = ((double)quant_code(w, s, bits, grid) - z) * (double)s;
-    double d = (double)w - wh;
-    err += d * d;
+// since x_ti factors out of each squared term.
+// A block owns 16 input channels (64-byte pieces of every row) and all the rows: 256 row lanes of 4 threads, 4
+// channels per thread, fp64 sums per thread, added up over the row lanes in a fixed order that is the same for every
+// channel (equal columns get equal scores).  (u - z) s is exact in fp64 (half integers of few bits times 24 bits), so
+// the fused multiply-add below is the rounded difference D - Dhat itself.
+// Bound by the bytes of the delta, in 64-byte pieces: 4096 x 4096 in 16 us (4.2 TB/s; one thread per channel
+// walking all the rows with an fp64 division each: 1448 us).  Neighbouring blocks share 128-byte lines: their ids go to one XCD.
+template <int BITS, bool EQ1>
+__global__ __launch_bounds__(1024) void k_scores(const float* __restrict__ delta, const float* __restrict__ xc, int n,
+                                                 int d_in, int d_out, const float* __restrict__ step, bool aligned,
+                                                 bool x_aligned, double* __restrict__ score, double* __restrict__ score_out) {
+  const int strips = (d_in + 15) / 16, per_xcd = (strips + 7) / 8;
+  const int strip = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_xcd || strip >= strips) return;
+  const int tid = threadIdx.x, rl = tid >> 2, c = 16 * strip + 4 * (tid & 3);
+  const bool in = c < d_in;                                // d_in % 8 == 0
+  double err[4] = {0, 0, 0, 0}, xs[4] = {0, 0, 0, 0};
+  if (in) {
+    const float* col = delta + c;
+#pragma unroll 4
+    for (int j = rl; j < d_out; j += 256) {
+      const float4 a = load4(col + (size_t)j * d_in, aligned);
+      const float w[4] = {a.x, a.y, a.z, a.w};
+      const float s = step[j];
+      const double sd = (double)s;
+      if (fast_step(s)) {
+        const float inv_s = __builtin_amdgcn_rcpf(s);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float level = clamped_cell<BITS, EQ1>(w[e], s, inv_s) + (EQ1 ? 0.0f : 0.5f);
+          const double d = __builtin_fma(-(double)level, sd, (double)w[e]);
+          err[e] = __builtin_fma(d, d, err[e]);
+        }
+      } else {
+        const double z = zero_point(BITS, EQ1 ? MES_GRID_EQ1 : MES_GRID_SYM);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double d = (double)w[e] - ((double)quant_code(w[e], s, BITS, EQ1 ? MES_GRID_EQ1 : MES_GRID_SYM) - z) * sd;
+          err[e] = __builtin_fma(d, d, err[e]);
+        }
+      }
+    }
+    const float* xcol = xc + c;
+#pragma unroll 4
+    for (int t = rl; t < n; t += 256) {
+      const float4 a = load4(xcol + (size_t)t * d_in, x_aligned);
+      const float w[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) xs[e] = __builtin_fma((double)w[e], (double)w[e], xs[e]);
+    }
   }
-  double xs = 0.0;
-  for (int t = 0; t < n; ++t) { double v = (double)xc[(size_t)t * d_in + i]; xs += v * v; }
-  score[i] = xs * err;
+  __shared__ double sum[2][16][16];                        // [err, xs][wavefront][channel]
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+#pragma unroll
+    for (int off = 4; off < 64; off <<= 1) {
+      err[e] += __shfl_xor(err[e], off);
+      xs[e] += __shfl_xor(xs[e], off);
+    }
+    if ((tid & 63) < 4) {
+      sum[0][tid >> 6][4 * (tid & 3) + e] = err[e];
+      sum[1][tid >> 6][4 * (tid & 3) + e] = xs[e];
+    }
+  }
+  __syncthreads();
+  if (tid < 16 && 16 * strip + tid < d_in) {
+    double te = 0.0, tx = 0.0;
+    for (int w = 0; w < 16; ++w) { te += sum[0][w][tid]; tx += sum[1][w][tid]; }
+    score[16 * strip + tid] = tx * te;
+    if (score_out) score_out[16 * strip + tid] = tx * te;
+  }
 }
 
-__global__ void k_rank(const double* __restrict__ score, int d_in, int k, int* __restrict__ chosen) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d_in) return;
-  double s = score[i];
+// chosen[i] = fewer than k channels come before channel i (a larger score, or the same one at a lower index).  A block
+// ranks 64 channels, one per lane; its 16 wavefronts share out the channels compared with, which are the same for
+// all lanes and come through scalar loads.  (4096 channels: 14 us; one thread per
+// channel comparing with all of them: 281 us.)
+__global__ __launch_bounds__(1024) void k_rank(const double* __restrict__ score, int d_in, int k, int* __restrict__ chosen) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i0 = 64 * blockIdx.x, i = i0 + lane;
+  const double s = score[i < d_in ? i : d_in - 1];
+  const int per = (d_in + 15) / 16;
+  const int lo = wave * per < d_in ? wave * per : d_in, hi = lo + per < d_in ? lo + per : d_in;
+  const int a = lo > i0 ? lo : (i0 < hi ? i0 : hi);        // [lo, a): before the block's channels, [b, hi): after them
+  const int b = a > i0 + 64 ? a : (i0 + 64 < hi ? i0 + 64 : hi);
   int rank = 0;
-  for (int o = 0; o < d_in; ++o) {
-    double so = score[o];
+#pragma unroll 8
+  for (int o = lo; o < a; ++o) rank += score[o] >= s;
+  for (int o = a; o < b; ++o) {
+    const double so = score[o];
     rank += (so > s) || (so == s && o < i);
   }
-  chosen[i] = rank < k;
+#pragma unroll 8
+  for (int o = b; o < hi; ++o) rank += score[o] > s;
+  __shared__ int part[16][64];
+  part[wave][lane] = rank;
+  __syncthreads();
+  if (wave == 0 && i < d_in) {
+    for (int w = 1; w < 16; ++w) rank += part[w][lane];
+    chosen[i] = rank < k;
+  }
 }
 
-__global__ void k_compact(const int* __restrict__ chosen, int d_in, int k, int32_t* __restrict__ idx_out) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d_in || !chosen[i]) return;
-  int pos = 0;
-  for (int o = 0; o < i; ++o) pos += chosen[o];
-  if (pos < k) idx_out[pos] = i;   // more than k can only be chosen when scores are NaN
-}
-
-__global__ void k_fill_zero(uint32_t* p, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+// The chosen channels in ascending order: one block, 1024 channels at a time, positions by counting lane masks
+// (4096 channels: 4 us; every thread counting the chosen ones before it: 198 us).
+__global__ __launch_bounds__(1024) void k_compact(const int* __restrict__ chosen, int d_in, int k, int32_t* __restrict__ idx_out) {
+  __shared__ int count[2][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int before = 0;
+  for (int base = 0, buf = 0; base < d_in; base += 1024, buf ^= 1) {
+    const int i = base + tid;
+    const bool c = i < d_in && chosen[i] != 0;
+    const unsigned long long m = __ballot(c);
+    if (lane == 0) count[buf][wave] = __popcll(m);
+    __syncthreads();
+    int pos = before + __popcll(m & ((1ull << lane) - 1ull));
+    for (int w = 0; w < 16; ++w) {
+      const int cw = count[buf][w];
+      pos += w < wave ? cw : 0;
+      before += cw;
+    }
+    if (c && pos < k) idx_out[pos] = i;   // more than k can only be chosen when scores are NaN
+  }
 }
 
 inline unsigned blocks_for(size_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
@@ -309,37 +566,57 @@ hipError_t launch_copy_probe(void* dst, const void* src, size_t bytes, hipStream
   return hipGetLastError();
 }
 
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
-  size_t n = bytes / 4;
-  if (n == 0) return hipSuccess;
-  k_fill_zero<<<blocks_for(n, 256), 256, 0, s>>>(reinterpret_cast<uint32_t*>(p), n);
-  return hipGetLastError();
+namespace {
+
+// Threads per block and values per thread of k_pack_rows by row length: 64 threads up to 1024 columns, 256 beyond,
+// and registers for the whole row up to 16384 columns.
+template <int BITS, bool EQ1>
+void launch_pack_rows(const PackParams& p, hipStream_t s) {
+  const unsigned grid = (unsigned)((p.n_jt + 7) / 8 * 8 * 16);
+  const int cols = kColPad * p.n_chunks;                   // padding columns get code 0
+  if (cols <= 1024) k_pack_rows<BITS, EQ1, 64, 4><<<grid, 64, 0, s>>>(p);
+  else if (cols <= 4096) k_pack_rows<BITS, EQ1, 256, 4><<<grid, 256, 0, s>>>(p);
+  else if (cols <= 8192) k_pack_rows<BITS, EQ1, 256, 8><<<grid, 256, 0, s>>>(p);
+  else if (cols <= 16384) k_pack_rows<BITS, EQ1, 256, 16><<<grid, 256, 0, s>>>(p);
+  else k_pack_rows<BITS, EQ1, 256, 0><<<grid, 256, 0, s>>>(p);
 }
+
+inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
+}  // namespace
 
 hipError_t launch_pack_delta(const float* delta, int d_in, int d_out, const int32_t* sidx, int k, int bits,
                              int grid, int policy, const float* step_in, uint32_t* codes, float* step_out,
                              uint16_t* sal, int* flag, hipStream_t s) {
   hipError_t e;
-  k_fill_zero<<<1, 64, 0, s>>>(reinterpret_cast<uint32_t*>(flag), 1);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (k > 0) {
-    k_check_salient<<<blocks_for(k, 256), 256, 0, s>>>(sidx, k, d_in, flag);
+  PackParams p;
+  p.delta = delta;
+  p.sidx = sidx;
+  p.step_in = policy == MES_STEP_MEANABS ? step_out : step_in;
+  p.step_out = step_out;
+  p.codes = codes;
+  p.sal = sal;
+  p.flag = flag;
+  p.d_in = d_in;
+  p.d_out = d_out;
+  p.k = k;
+  p.n_jt = ceil_to(d_out, kRowPad) / 16;
+  p.n_chunks = ceil_to(d_in, kColPad) / kColPad;
+  p.n_sb = ceil_to(k, kSalPad) / 32;
+  p.policy = policy;
+  p.aligned = aligned16(delta);
+  if (policy == MES_STEP_MEANABS) {
+    k_row_meanabs<<<blocks_for(d_out, 64), 256, 0, s>>>(delta, d_in, d_out, sidx, k, p.aligned, step_out);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  k_row_step<<<d_out, 256, 0, s>>>(delta, d_in, sidx, k, bits, grid, policy, step_in, step_out);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  int po = ceil_to(d_out, kRowPad), pi = ceil_to(d_in, kColPad);
-  const int n_jt = po / 16;
-  if ((e = launch_fill_zero(codes, (size_t)po * pi * bits / 8, s)) != hipSuccess) return e;
-  k_pack_codes<<<blocks_for((size_t)d_out * (d_in / 8), 256), 256, 0, s>>>(delta, d_in, d_out, sidx, k, bits, grid, step_out, n_jt, codes);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (k > 0) {
-    int n_sb = ceil_to(k, kSalPad) / 32;
-    size_t n_el = (size_t)(po / 16) * n_sb * 512;
-    k_pack_salient<<<blocks_for(n_el, 256), 256, 0, s>>>(delta, d_in, d_out, sidx, k, n_sb, n_el, flag, sal);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+  const bool eq1 = grid == MES_GRID_EQ1;
+  switch (bits) {
+    case 1: launch_pack_rows<1, false>(p, s); break;
+    case 2: eq1 ? launch_pack_rows<2, true>(p, s) : launch_pack_rows<2, false>(p, s); break;
+    case 3: eq1 ? launch_pack_rows<3, true>(p, s) : launch_pack_rows<3, false>(p, s); break;
+    default: eq1 ? launch_pack_rows<4, true>(p, s) : launch_pack_rows<4, false>(p, s); break;
   }
-  return hipSuccess;
+  return hipGetLastError();
 }
 
 hipError_t launch_unpack_delta(const mes_delta& d, float* delta_hat, uint8_t* codes_out, hipStream_t s) {
@@ -362,19 +639,24 @@ hipError_t launch_select(const float* delta, const float* xc, int n, int d_in, i
   float* step = reinterpret_cast<float*>(p);
   p += (size_t)ceil_to(d_out, 64) * sizeof(float);
   int* chosen = reinterpret_cast<int*>(p);
+  const bool aligned = aligned16(delta), x_aligned = aligned16(xc), eq1 = grid == MES_GRID_EQ1;
   hipError_t e;
-  k_row_step<<<d_out, 256, 0, s>>>(delta, d_in, nullptr, 0, bits, grid, policy, nullptr, step);
+  if (policy == MES_STEP_MEANABS) k_row_meanabs<<<blocks_for(d_out, 64), 256, 0, s>>>(delta, d_in, d_out, nullptr, 0, aligned, step);
+  else k_row_maxabs<<<d_out, 256, 0, s>>>(delta, d_in, bits, grid, aligned, step);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_scores<<<blocks_for(d_in, 64), 64, 0, s>>>(delta, xc, n, d_in, d_out, bits, grid, step, score);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_rank<<<blocks_for(d_in, 256), 256, 0, s>>>(score, d_in, k, chosen);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (k > 0) {
-    k_compact<<<blocks_for(d_in, 256), 256, 0, s>>>(chosen, d_in, k, idx_out);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+  const unsigned strips = ((unsigned)((d_in + 15) / 16) + 7) / 8 * 8;
+  auto scores = [&](auto kernel) { kernel<<<strips, 1024, 0, s>>>(delta, xc, n, d_in, d_out, step, aligned, x_aligned, score, score_out); };
+  switch (bits) {
+    case 1: scores(k_scores<1, false>); break;
+    case 2: eq1 ? scores(k_scores<2, true>) : scores(k_scores<2, false>); break;
+    case 3: eq1 ? scores(k_scores<3, true>) : scores(k_scores<3, false>); break;
+    default: eq1 ? scores(k_scores<4, true>) : scores(k_scores<4, false>); break;
   }
-  if (score_out) e = hipMemcpyAsync(score_out, score, (size_t)d_in * sizeof(double), hipMemcpyDeviceToDevice, s);
-  return e;
+  if ((e = hipGetLastError()) != hipSuccess || k == 0) return e;
+  k_rank<<<blocks_for(d_in, 64), 1024, 0, s>>>(score, d_in, k, chosen);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  k_compact<<<1, 1024, 0, s>>>(chosen, d_in, k, idx_out);
+  return hipGetLastError();
 }
 
 }  // namespace mes
