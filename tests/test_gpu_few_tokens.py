@@ -1,0 +1,93 @@
+"""Calls of up to 32 tokens, around every edge of the one-launch path's dispatch: tokens per tile, experts per register
+set, wavefronts per row tile (row counts), chunks per wavefront, salient pairs.  Bars as for the streaming path: exact
+products, fp32 sums, one rounding."""
+import numpy as np
+import pytest
+import torch
+
+import parity_checks as PC
+
+from inputs import synth
+from oracle import mes_oracle as O
+from test_gpu_parity import gated_case, oracle_experts, rel_fro, run_case, TOL
+
+pytestmark = pytest.mark.gpu
+mes = pytest.importorskip("paper_2406_09041_amd")
+DEV = "cuda:0"
+
+
+def segments(tokens, experts, empty=0):
+    """`experts` owners of `tokens` tokens (the first ones the surplus), an empty expert before and after them."""
+    off = [0] * (1 + empty)
+    for e in range(experts):
+        off.append(off[-1] + tokens // experts + (1 if e < tokens % experts else 0))
+    return off + [off[-1]] * empty
+
+
+@pytest.mark.parametrize("bits,grid", [(1, 0), (2, 0), (2, 1), (3, 0), (4, 1)])
+@pytest.mark.parametrize("tokens,experts", [(1, 1), (15, 4), (16, 5), (16, 8), (16, 9), (16, 16), (17, 1), (32, 4), (31, 5), (32, 8), (32, 9), (33, 2)])
+def test_tokens_and_experts(tokens, experts, bits, grid):
+    run_case(synth.small_case(520, 76, segments(tokens, experts, 1), 33, bits, seed=tokens + experts), grid)
+
+
+@pytest.mark.parametrize("d_in,d_out,tokens,experts,k,bits", [
+    (8, 4, 1, 1, 0, 2),              # less than one tile of anything
+    (128, 16, 2, 2, 2, 2),           # exactly one row tile, one chunk
+    (1024, 1024, 3, 3, 64, 2),       # one chunk per wavefront
+    (1032, 20, 5, 2, 8, 3),          # a ninth chunk of eight columns; 8 chunks per wavefront at most
+    (4096, 2064, 4, 1, 64, 2),       # 129 row tiles: half a round of teams of eight
+    (256, 8208, 16, 3, 40, 1),       # 513 row tiles: teams of four
+    (136, 16416, 7, 7, 5, 2),        # 1026 row tiles: teams of two or one
+    (640, 80, 16, 16, 128, 2),       # 64 salient pairs, all there is room for
+    (640, 80, 16, 16, 129, 2),       # 80: the streaming path
+    (8320, 512, 9, 2, 64, 4),        # 65 chunks on 32 row tiles: the streaming path
+    (8320, 1024, 9, 2, 64, 4),       # ... on 64: nine chunks for the first wavefront
+    (2560, 512, 20, 2, 64, 2),       # two token tiles, three chunks
+    (4608, 512, 20, 2, 64, 2),       # two token tiles, five chunks: the streaming path
+])
+def test_shapes(d_in, d_out, tokens, experts, k, bits):
+    run_case(synth.small_case(d_in, d_out, segments(tokens, experts), k, bits, seed=d_in % 89 + k))
+
+
+@pytest.mark.parametrize("d_in,d_out,tokens,experts,k,bits,grid", [(264, 72, 5, 2, 5, 2, 0), (1160, 2080, 16, 9, 24, 3, 1),
+                                                                   (520, 4112, 1, 1, 0, 1, 0), (512, 100, 30, 3, 64, 4, 0)])
+def test_gated(d_in, d_out, tokens, experts, k, bits, grid):
+    seg = segments(tokens, experts, 1)
+    wg, wu, _, h = gated_case(d_in, d_out, seg, k, bits, seed=7 + bits, grid=grid)
+    h_ref = O.gated_mlp_input(wg.x.double().numpy(), wg.w_base.double().numpy(), oracle_experts(wg, grid),
+                              wu.w_base.double().numpy(), oracle_experts(wu, grid), seg)
+    assert rel_fro(h, h_ref) <= TOL
+    PC.assert_streaming_rows(h.double().cpu().numpy(), h_ref, ("gated", d_in, d_out, bits))
+
+
+@pytest.mark.parametrize("d_in,d_outs,tokens,experts,k,bits", [(264, (72, 40, 100), 9, 3, 5, 2), (1024, (1040, 16, 1024), 16, 8, 64, 3)])
+def test_layers_that_share_their_activations(d_in, d_outs, tokens, experts, k, bits):
+    """Bit for bit the single calls (a row tile's sum does not depend on what else is in the launch, as long as the same
+    number of wavefronts share it), and the oracle's bars."""
+    seg = segments(tokens, experts, 1)
+    wls = [synth.small_case(d_in, d, seg, k, bits, seed=50 + i) for i, d in enumerate(d_outs)]
+    x = wls[0].x.to(DEV)
+    packed = [(mes.mes_pack_base(wl.w_base.to(DEV)), [mes.mes_pack_delta(ex.delta.to(DEV), ex.salient_idx, bits) for ex in wl.experts]) for wl in wls]
+    ys = mes.DeltaLinearMulti(packed, max_tokens=tokens)(x, seg)
+    for wl, pk, y in zip(wls, packed, ys):
+        y_ref = O.delta_linear(wls[0].x.double().numpy(), wl.w_base.double().numpy(), oracle_experts(wl), seg)
+        PC.assert_streaming_rows(y.double().cpu().numpy(), y_ref, (d_in, wl.d_out))
+        assert torch.equal(y, mes.mes_delta_linear(pk[0], pk[1], x, seg))
+
+
+def test_same_result_every_time_and_for_any_row_of_the_batch():
+    """Run to run the bits are the same; a token's row does not depend on the other rows, non-finite ones included."""
+    wl = synth.small_case(1032, 200, [0, 6, 16], 8, 2, seed=3)
+    w_t = mes.mes_pack_base(wl.w_base.to(DEV))
+    ge = [mes.mes_pack_delta(ex.delta.to(DEV), ex.salient_idx, 2) for ex in wl.experts]
+    x = wl.x.to(DEV)
+    y = mes.mes_delta_linear(w_t, ge, x, wl.seg_offsets)
+    for _ in range(5):
+        assert torch.equal(y, mes.mes_delta_linear(w_t, ge, x, wl.seg_offsets))
+    bad = x.clone()
+    bad[3] = float("inf")
+    bad[9, 5] = float("nan")
+    yb = mes.mes_delta_linear(w_t, ge, bad, wl.seg_offsets)
+    keep = [i for i in range(16) if i not in (3, 9)]
+    assert torch.equal(y[keep], yb[keep])
+    assert not torch.isfinite(yb[[3, 9]].float()).any()
