@@ -182,6 +182,19 @@ __device__ __forceinline__ void stage_barrier() {
   asm volatile("s_barrier" ::: "memory");
 }
 
+// Expert slots one sweep over the chunks handles, by the number of experts that own tokens of the group.  Their code
+// words for one chunk pass through registers and are parked in LDS, used or not, so groups of few experts take smaller
+// bodies.  The largest body: 16 slots (all a group may have) at 1 and 2 bits; at 3 bits the registers hold 13, at 4 the
+// LDS 10 (8 wavefronts x slots x 256 b bytes next to the two activation stages).  Groups of more experts than that take two
+// sweeps of 8, the cheaper split.  4096 rows x 14336 columns, 64 tokens, us per call:
+//   3 bits, 13 experts: 100 in one sweep of 13, 118 in two of 8; 16 experts: 134 in sweeps of 13 and 3, 125 in two of 8;
+//   4 bits, 10 experts: 97 against 118; 13 experts: 132 against 128;  2 bits, 6 experts: 61 with 8 slots, 63 with 16.
+constexpr int full_slots(int bits) { return bits <= 2 ? 16 : bits == 3 ? 13 : 10; }
+constexpr int pass_slots(int bits, int n_act) { return n_act <= 4 ? 4 : n_act <= 8 || n_act > full_slots(bits) ? 8 : full_slots(bits); }
+// Register buffers for code words in flight: two, requested two chunks ahead; the largest bodies at 3 and 4 bits have
+// registers for one, requested one chunk ahead.  (Their chunks take long enough for the words to arrive.)
+constexpr int code_buffers(int bits, int na) { return bits >= 3 && na > 8 ? 1 : 2; }
+
 // Per-wavefront state of the streaming loop.
 //  - Base weights are double buffered in registers: while chunk c is multiplied out of buffer c % 2, the
 //    4 KiB of chunk c + 1 are in flight into the other buffer.
@@ -198,6 +211,7 @@ struct Stream {
   static constexpr int kSlotLds = code_block_bytes(BITS);       // LDS bytes of one parked slot
   static constexpr int kParkWave = NA * kSlotLds;               // ... of all slots of a sweep
   static constexpr int NL = (kParkWave + 1023) / 1024;          // loads of 1 KiB that bring them in
+  static constexpr int CB = code_buffers(BITS, NA);             // register buffers for them
 
   const LinearParams& p;
   const PerLinear& L;
@@ -226,7 +240,7 @@ struct Stream {
   uint32_t slot_tok[TT];
   float rs_acc = 0.0f;        // lane = token: sum of its activations over the chunks done so far
   u32x4 base[2][4];
-  u32x4 code[2][NL];
+  u32x4 code[CB][NL];
   f32x4 acc_base[TT], acc_raw[TT];
 
   // Salient fp16 columns ride along with the stream: the (visit, 32-column block) pairs of this workgroup
@@ -369,7 +383,7 @@ struct Stream {
   __device__ __forceinline__ void load_code_regs(int c) {
     const uint32_t off = (uint32_t)c * code_stride;
 #pragma unroll
-    for (int i = 0; i < NL; ++i) code[BUF][i] = ld128_at(code_at[i] + off);
+    for (int i = 0; i < NL; ++i) code[BUF % CB][i] = ld128_at(code_at[i] + off);
   }
 
   // Register buffer BUF (the chunk that starts now) -> this wavefront's LDS area.
@@ -378,18 +392,20 @@ struct Stream {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       if (NL * 1024 == kParkWave || i * 1024 + lane * 16 < kParkWave)
-        *reinterpret_cast<u32x4*>(parkp + i * 1024 + lane * 16) = code[BUF][i];
+        *reinterpret_cast<u32x4*>(parkp + i * 1024 + lane * 16) = code[BUF % CB][i];
     }
   }
 
   // Tile tt's share of the requests of one chunk: code words of chunk c2 (two ahead) into the register buffer
-  // that was just parked, base weights of chunk cn (one ahead) into the other base buffer.
+  // that was just parked, base weights of chunk cn (one ahead) into the other base buffer.  With one code buffer the
+  // words are those of chunk cn, asked for by the first half of the tiles and parked at the end of this chunk.
   template <int BUF, bool NOBASE>
   __device__ __forceinline__ void request_share(int tt, int cn, int c2) {
-    const uint32_t off = (uint32_t)c2 * code_stride;
+    const uint32_t off = (uint32_t)(CB == 2 ? c2 : cn) * code_stride;
+    constexpr int kSpread = CB == 2 || TT == 1 ? TT : TT / 2;
 #pragma unroll
     for (int i = 0; i < NL; ++i)
-      if (i * TT / NL == tt) code[BUF][i] = ld128_at(code_at[i] + off);
+      if (i * kSpread / NL == tt) code[BUF % CB][i] = ld128_at(code_at[i] + off);
     if constexpr (!NOBASE) {
       const char* src = base_at + (size_t)((uint32_t)cn * base_stride);
 #pragma unroll
@@ -460,9 +476,6 @@ struct Stream {
   }
 };
 
-// Active experts one sweep handles: their code words for one chunk are parked in LDS (8 wavefronts x slots x
-// 256 b bytes next to the two activation stages must fit the 160 KiB of a compute unit).
-constexpr int max_pass_slots(int bits) { return bits >= 3 ? 8 : 16; }
 
 // LDS of a workgroup, carved up by hand, the two activation stages first: below 64 KiB their addresses fit the
 // offset field of the LDS instructions, so one lane-offset register serves every operand read.
@@ -538,7 +551,7 @@ __device__ __forceinline__ void stream_rows(const LinearParams& p, char* lds, in
   stage_copy<NW>(ws.xt + (size_t)chunk_at(0) * kStageBytes, stage0, extra0, wave, lane);
   ws.template load_base<0>(chunk_at(0));
   ws.template load_code_regs<0>(chunk_at(0));
-  ws.template load_code_regs<1>(chunk_at(1));
+  if constexpr (S::CB == 2) ws.template load_code_regs<1>(chunk_at(1));
   // Every slot's step for this wavefront's 16 output channels (for the salient weights and the epilogue) is fetched
   // now and kept in LDS: in registers it would be live across the whole stream.  Likewise the two tables of the
   // salient requests.
@@ -583,7 +596,7 @@ __device__ __forceinline__ void stream_rows(const LinearParams& p, char* lds, in
     ws.begin_sweep(sweep * NA);
     stage_copy<NW>(ws.xt + (size_t)chunk_at(0) * kStageBytes, stage0, extra0, wave, lane);
     ws.template load_code_regs<0>(chunk_at(0));
-    ws.template load_code_regs<1>(chunk_at(1));
+    if constexpr (S::CB == 2) ws.template load_code_regs<1>(chunk_at(1));
     ws.template park<0>();
     stage_barrier<0>();
     for (int i = 0; i < len; i += 2) {
@@ -646,14 +659,17 @@ __device__ __forceinline__ void stream_rows(const LinearParams& p, char* lds, in
   }
 }
 
-// The kernel: finds its (row group, column split, token group) and runs it with as few expert slots per sweep as
-// the group needs -- a group whose tokens belong to four experts or fewer (most groups of a batch that is sorted by
-// expert) moves a quarter of the code words of a full one through registers and LDS.
-// CLASSES: 0 = every group of the launch is such a short one, 1 = none is, 2 = both kinds (the workgroup looks).
-template <int BITS, int TT, int NW, int CLASSES>
+// The kernel: finds its (row group, column split, token group) and runs it with the body for as many expert slots per
+// sweep as the group needs (pass_slots) -- a group whose tokens belong to four experts or fewer (most groups of a batch
+// that is sorted by expert) moves a quarter of the code words of a full one through registers and LDS.
+// NA: the body all groups of the launch take, or they differ and the workgroup looks: kMixShort (4 or 8 slots) or
+// kMixFull (some group takes the full body; at 1 and 2 bits the groups of 5 to 8 experts then take it too: the same
+// sums, and two bodies in flight instead of three measured 1 % faster, 302 against 305 us for 256 tokens on 4096 x 28672).
+constexpr int kMixShort = 0, kMixFull = 1;
+template <int BITS, int TT, int NW, int NA>
 __global__ __launch_bounds__(64 * NW) void k_delta_linear(const LaunchParams mp) {
-  constexpr int NA = max_pass_slots(BITS);
-  __shared__ __attribute__((aligned(16))) char lds[LdsPlan<BITS, CLASSES == 0 ? 4 : NA, NW>::kTotal];
+  constexpr int kFull = full_slots(BITS);
+  __shared__ __attribute__((aligned(16))) char lds[LdsPlan<BITS, NA == kMixShort ? 8 : NA == kMixFull ? kFull : NA, NW>::kTotal];
   // flat workgroup id -> (class, split, row group, token group), see LaunchParams; ids go round-robin to the XCDs
   const int first_wgs = mp.n_first * mp.wg_per_group;
   const bool second = (int)blockIdx.x >= first_wgs;
@@ -662,10 +678,19 @@ __global__ __launch_bounds__(64 * NW) void k_delta_linear(const LaunchParams mp)
   const int rg = (bq2 % mp.rg8) * 8 + (b & 7), sp = bq2 / mp.rg8;
   if (rg >= mp.rgs) return;   // padding of the row groups to a multiple of eight
   const LinearParams& p = mp.g[(second ? mp.n_first : 0) + bq - bq2 * m];
-  if constexpr (CLASSES == 0) stream_rows<BITS, TT, 4, NW>(p, lds, rg, sp);
-  else if constexpr (CLASSES == 1) stream_rows<BITS, TT, NA, NW>(p, lds, rg, sp);
-  else if (p.n_act <= 4) stream_rows<BITS, TT, 4, NW>(p, lds, rg, sp);
-  else stream_rows<BITS, TT, NA, NW>(p, lds, rg, sp);
+  if constexpr (NA > kMixFull) {
+    stream_rows<BITS, TT, NA, NW>(p, lds, rg, sp);
+  } else {
+    const int na = pass_slots(BITS, p.n_act);
+    if (na == 4) {
+      stream_rows<BITS, TT, 4, NW>(p, lds, rg, sp);
+    } else if constexpr (NA == kMixShort) {
+      stream_rows<BITS, TT, 8, NW>(p, lds, rg, sp);
+    } else {
+      if (BITS <= 2 || na == kFull) stream_rows<BITS, TT, kFull, NW>(p, lds, rg, sp);
+      else stream_rows<BITS, TT, 8, NW>(p, lds, rg, sp);
+    }
+  }
 }
 
 // Split columns only: y = sum over splits (in split order) of the fp32 partial tiles, rounded to bf16.  One
@@ -767,30 +792,31 @@ WorkspaceLayout workspace_layout(int d_in, const int* d_out, int n_linears, bool
 // Token groups a workspace sized for `max_tokens` holds.
 inline int groups_for(int max_tokens) { return max_tokens <= kTokGroup ? 1 : max_tokens <= 2 * kTokGroup ? 2 : kMaxGroups; }
 
+template <int BITS, int NW, int NA>
+void launch_tt(const LaunchParams& mp, int tt, int grid, hipStream_t s) {
+  if (tt == 1) k_delta_linear<BITS, 1, NW, NA><<<grid, 64 * NW, 0, s>>>(mp);
+  else if (tt == 2) k_delta_linear<BITS, 2, NW, NA><<<grid, 64 * NW, 0, s>>>(mp);
+  else k_delta_linear<BITS, 4, NW, NA><<<grid, 64 * NW, 0, s>>>(mp);
+}
+
+// na: the body all groups take, or how they differ (built for four token tiles only: fewer are a special case of it)
 template <int BITS, int NW>
-hipError_t launch_tt(const LaunchParams& mp, int tt, int classes, int grid, hipStream_t s) {
-  if (classes == 2) {   // both kinds of groups: built for four token tiles only (fewer tiles are a special case of it)
-    k_delta_linear<BITS, 4, NW, 2><<<grid, 64 * NW, 0, s>>>(mp);
-    return hipGetLastError();
-  }
-  switch (tt * 2 + classes) {
-    case 2: k_delta_linear<BITS, 1, NW, 0><<<grid, 64 * NW, 0, s>>>(mp); break;
-    case 3: k_delta_linear<BITS, 1, NW, 1><<<grid, 64 * NW, 0, s>>>(mp); break;
-    case 4: k_delta_linear<BITS, 2, NW, 0><<<grid, 64 * NW, 0, s>>>(mp); break;
-    case 5: k_delta_linear<BITS, 2, NW, 1><<<grid, 64 * NW, 0, s>>>(mp); break;
-    case 8: k_delta_linear<BITS, 4, NW, 0><<<grid, 64 * NW, 0, s>>>(mp); break;
-    default: k_delta_linear<BITS, 4, NW, 1><<<grid, 64 * NW, 0, s>>>(mp); break;
-  }
-  return hipGetLastError();
+void launch_na(const LaunchParams& mp, int tt, int na, int grid, hipStream_t s) {
+  if (na == kMixShort) k_delta_linear<BITS, 4, NW, kMixShort><<<grid, 64 * NW, 0, s>>>(mp);
+  else if (na == kMixFull) k_delta_linear<BITS, 4, NW, kMixFull><<<grid, 64 * NW, 0, s>>>(mp);
+  else if (na == 4) launch_tt<BITS, NW, 4>(mp, tt, grid, s);
+  else if (na == 8) launch_tt<BITS, NW, 8>(mp, tt, grid, s);
+  else launch_tt<BITS, NW, full_slots(BITS)>(mp, tt, grid, s);
 }
 
 template <int BITS>
-hipError_t launch_nw(const LaunchParams& mp, int tt, int classes, int nw, int grid, hipStream_t s) {
+hipError_t launch_nw(const LaunchParams& mp, int tt, int na, int nw, int grid, hipStream_t s) {
   switch (nw) {
-    case 6: return launch_tt<BITS, 6>(mp, tt, classes, grid, s);
-    case 7: return launch_tt<BITS, 7>(mp, tt, classes, grid, s);
-    default: return launch_tt<BITS, 8>(mp, tt, classes, grid, s);
+    case 6: launch_na<BITS, 6>(mp, tt, na, grid, s); break;
+    case 7: launch_na<BITS, 7>(mp, tt, na, grid, s); break;
+    default: launch_na<BITS, 8>(mp, tt, na, grid, s); break;
   }
+  return hipGetLastError();
 }
 
 hipError_t launch_reduce(const LaunchParams& mp, int tt, int nw, hipStream_t s) {
@@ -866,7 +892,7 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
   mp.rgs = rgs;
   mp.rg8 = (rgs + 7) / 8;
   // Token groups: up to 64 consecutive tokens that belong to at most kMaxSlots experts (the kernel sweeps the
-  // chunks once per max_pass_slots of them).
+  // chunks once per pass_slots of them).
   const int max_slots = kMaxSlots;
   bool first_kernel = true;   // measurement hook: the start event goes before the first streaming kernel / GEMM
   // The streaming (decode) path.  Token groups are collected from all the token ranges it covers (the stretches
@@ -884,7 +910,12 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
       }
     for (int g = ng; g < kMaxGroups; ++g) mp.g[g] = mp.g[0];   // never selected
     mp.n_groups = ng;
-    const int classes = n_first == 0 ? 0 : n_first == ng ? 1 : 2;
+    bool same = true, full = false;
+    for (int g = 0; g < ng; ++g) {
+      same = same && pass_slots(d0.bits, mp.g[g].n_act) == pass_slots(d0.bits, mp.g[0].n_act);
+      full = full || pass_slots(d0.bits, mp.g[g].n_act) > 8;
+    }
+    const int na = same ? pass_slots(d0.bits, mp.g[0].n_act) : full ? kMixFull : kMixShort;
     mp.n_first = n_first > 0 ? n_first : ng;
     mp.wg_per_group = mp.rg8 * 8 * pl.nsplit;
     hipError_t e;
@@ -902,10 +933,10 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
     first_kernel = false;
     const int grid = mp.rg8 * 8 * pl.nsplit * ng;
     switch (d0.bits) {
-      case 1: e = launch_nw<1>(mp, tt_max, classes, pl.nw, grid, s); break;
-      case 2: e = launch_nw<2>(mp, tt_max, classes, pl.nw, grid, s); break;
-      case 4: e = launch_nw<4>(mp, tt_max, classes, pl.nw, grid, s); break;
-      default: e = launch_nw<3>(mp, tt_max, classes, pl.nw, grid, s); break;
+      case 1: e = launch_nw<1>(mp, tt_max, na, pl.nw, grid, s); break;
+      case 2: e = launch_nw<2>(mp, tt_max, na, pl.nw, grid, s); break;
+      case 4: e = launch_nw<4>(mp, tt_max, na, pl.nw, grid, s); break;
+      default: e = launch_nw<3>(mp, tt_max, na, pl.nw, grid, s); break;
     }
     if (e != hipSuccess) return e;
     if (c.ev_stop && (e = hipEventRecord(c.ev_stop, s)) != hipSuccess) return e;   // re-recorded by every later one

@@ -1,0 +1,39 @@
+"""The streaming kernel's bodies by number of experts (4, 8 or as many slots as a bit width has room for; two sweeps
+beyond): every count around the edges, and launches whose token groups take different bodies."""
+import pytest
+import torch
+
+from inputs import synth
+from test_gpu_parity import run_case
+
+pytestmark = pytest.mark.gpu
+mes = pytest.importorskip("paper_2406_09041_amd")
+DEV = "cuda:0"
+
+
+def offsets(counts):
+    off = [0]
+    for c in counts:
+        off.append(off[-1] + c)
+    return off
+
+
+@pytest.mark.parametrize("bits,experts", [(1, 5), (1, 9), (2, 4), (2, 8), (2, 16), (3, 8), (3, 9), (3, 13), (3, 14), (3, 16),
+                                          (4, 8), (4, 9), (4, 10), (4, 11), (4, 16)])
+def test_expert_counts(bits, experts):
+    """64 tokens (the streaming path at any count), five column chunks, enough salient pairs to ride along all of them."""
+    counts = [64 // experts + (1 if e < 64 % experts else 0) for e in range(experts)]
+    run_case(synth.small_case(584, 200, offsets(counts), 40, bits, seed=experts))
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("counts", [[64, 30, 34] + [11] * 5 + [9] + [5] * 10 + [14], [20, 20, 24] + [8] * 8, [8] * 8 + [5] * 12 + [4]])
+def test_groups_with_different_bodies_in_one_launch(bits, counts):
+    """Bit for bit the result of one launch per token group: a group's body depends on its own experts only."""
+    wl = synth.small_case(1160, 328, offsets(counts), 24, bits, seed=5, device=DEV)
+    w_t = mes.mes_pack_base(wl.w_base)
+    ge = [mes.mes_pack_delta(ex.delta, ex.salient_idx, bits) for ex in wl.experts]
+    y = mes.mes_delta_linear(w_t, ge, wl.x, wl.seg_offsets)
+    y1 = mes.mes_delta_linear(w_t, ge, wl.x, wl.seg_offsets, workspace=mes.make_workspace(wl.d_in, wl.d_out, 64, torch.device(DEV)))
+    assert torch.equal(y, y1)
+    run_case(synth.small_case(1160, 328, offsets(counts), 24, bits, seed=5))
