@@ -420,7 +420,8 @@ __global__ void k_unpack_delta(const uint32_t* __restrict__ codes, const float* 
 template <int BITS, bool EQ1>
 __global__ __launch_bounds__(1024) void k_scores(const float* __restrict__ delta, const float* __restrict__ xc, int n,
                                                  int d_in, int d_out, const float* __restrict__ step, bool aligned,
-                                                 bool x_aligned, double* __restrict__ score, double* __restrict__ score_out) {
+                                                 bool x_aligned, double* __restrict__ score, double* __restrict__ score_out,
+                                                 int* __restrict__ rank) {
   const int strips = (d_in + 15) / 16, per_xcd = (strips + 7) / 8;
   const int strip = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= per_xcd || strip >= strips) return;
@@ -480,19 +481,22 @@ __global__ __launch_bounds__(1024) void k_scores(const float* __restrict__ delta
     for (int w = 0; w < 16; ++w) { te += sum[0][w][tid]; tx += sum[1][w][tid]; }
     score[16 * strip + tid] = tx * te;
     if (score_out) score_out[16 * strip + tid] = tx * te;
+    rank[16 * strip + tid] = 0;                            // for k_rank to add to
   }
 }
 
-// chosen[i] = fewer than k channels come before channel i (a larger score, or the same one at a lower index).  A block
-// ranks 64 channels, one per lane; its 16 wavefronts share out the channels compared with, which are the same for
-// all lanes and come through scalar loads.  (4096 channels: 14 us; one thread per
-// channel comparing with all of them: 281 us.)
-__global__ __launch_bounds__(1024) void k_rank(const double* __restrict__ score, int d_in, int k, int* __restrict__ chosen) {
+// rank[i] += channels among this wavefront's share that come before channel i (a larger score, or the same one at a lower
+// index).  A block ranks 64 channels, one per lane; the channels compared with are dealt to the 4 wavefronts of gridDim.y
+// blocks, are the same for all lanes and come through scalar loads.  The shares add up with integer atomics (k_scores
+// cleared the sums): the result does not depend on their order.  4096 channels with 16 blocks per 64 channels: 6 us, one block
+// of 16 wavefronts 14 us (64 blocks leave most of the chip idle), the same through LDS 27 us, one thread per channel
+// comparing with all of them 281 us.
+__global__ __launch_bounds__(256) void k_rank(const double* __restrict__ score, int d_in, int* __restrict__ rank_out) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i0 = 64 * blockIdx.x, i = i0 + lane;
   const double s = score[i < d_in ? i : d_in - 1];
-  const int per = (d_in + 15) / 16;
-  const int lo = wave * per < d_in ? wave * per : d_in, hi = lo + per < d_in ? lo + per : d_in;
+  const int shares = 4 * gridDim.y, per = (d_in + shares - 1) / shares, share = 4 * blockIdx.y + wave;
+  const int lo = share * per < d_in ? share * per : d_in, hi = lo + per < d_in ? lo + per : d_in;
   const int a = lo > i0 ? lo : (i0 < hi ? i0 : hi);        // [lo, a): before the block's channels, [b, hi): after them
   const int b = a > i0 + 64 ? a : (i0 + 64 < hi ? i0 + 64 : hi);
   int rank = 0;
@@ -504,24 +508,21 @@ __global__ __launch_bounds__(1024) void k_rank(const double* __restrict__ score,
   }
 #pragma unroll 8
   for (int o = b; o < hi; ++o) rank += score[o] > s;
-  __shared__ int part[16][64];
+  __shared__ int part[4][64];
   part[wave][lane] = rank;
   __syncthreads();
-  if (wave == 0 && i < d_in) {
-    for (int w = 1; w < 16; ++w) rank += part[w][lane];
-    chosen[i] = rank < k;
-  }
+  if (wave == 0 && i < d_in) atomicAdd(rank_out + i, part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane]);
 }
 
-// The chosen channels in ascending order: one block, 1024 channels at a time, positions by counting lane masks
-// (4096 channels: 4 us; every thread counting the chosen ones before it: 198 us).
-__global__ __launch_bounds__(1024) void k_compact(const int* __restrict__ chosen, int d_in, int k, int32_t* __restrict__ idx_out) {
+// The chosen channels (fewer than k come before them) in ascending order: one block, 1024 channels at a time, positions by
+// counting lane masks (4096 channels: 4 us; every thread counting the chosen ones before it: 198 us).
+__global__ __launch_bounds__(1024) void k_compact(const int* __restrict__ rank, int d_in, int k, int32_t* __restrict__ idx_out) {
   __shared__ int count[2][16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int before = 0;
   for (int base = 0, buf = 0; base < d_in; base += 1024, buf ^= 1) {
     const int i = base + tid;
-    const bool c = i < d_in && chosen[i] != 0;
+    const bool c = i < d_in && rank[i] < k;
     const unsigned long long m = __ballot(c);
     if (lane == 0) count[buf][wave] = __popcll(m);
     __syncthreads();
@@ -632,20 +633,20 @@ hipError_t launch_unpack_delta(const mes_delta& d, float* delta_hat, uint8_t* co
 
 hipError_t launch_select(const float* delta, const float* xc, int n, int d_in, int d_out, int bits, int grid,
                          int policy, int k, int32_t* idx_out, double* score_out, void* ws, hipStream_t s) {
-  // workspace: double score[d_in] | float step[d_out] | int chosen[d_in]
+  // workspace: double score[d_in] | float step[d_out] | int rank[d_in]
   char* p = reinterpret_cast<char*>(ws);
   double* score = reinterpret_cast<double*>(p);
   p += (size_t)ceil_to(d_in, 32) * sizeof(double);
   float* step = reinterpret_cast<float*>(p);
   p += (size_t)ceil_to(d_out, 64) * sizeof(float);
-  int* chosen = reinterpret_cast<int*>(p);
+  int* rank = reinterpret_cast<int*>(p);
   const bool aligned = aligned16(delta), x_aligned = aligned16(xc), eq1 = grid == MES_GRID_EQ1;
   hipError_t e;
   if (policy == MES_STEP_MEANABS) k_row_meanabs<<<blocks_for(d_out, 64), 256, 0, s>>>(delta, d_in, d_out, nullptr, 0, aligned, step);
   else k_row_maxabs<<<d_out, 256, 0, s>>>(delta, d_in, bits, grid, aligned, step);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const unsigned strips = ((unsigned)((d_in + 15) / 16) + 7) / 8 * 8;
-  auto scores = [&](auto kernel) { kernel<<<strips, 1024, 0, s>>>(delta, xc, n, d_in, d_out, step, aligned, x_aligned, score, score_out); };
+  auto scores = [&](auto kernel) { kernel<<<strips, 1024, 0, s>>>(delta, xc, n, d_in, d_out, step, aligned, x_aligned, score, score_out, rank); };
   switch (bits) {
     case 1: scores(k_scores<1, false>); break;
     case 2: eq1 ? scores(k_scores<2, true>) : scores(k_scores<2, false>); break;
@@ -653,9 +654,9 @@ hipError_t launch_select(const float* delta, const float* xc, int n, int d_in, i
     default: eq1 ? scores(k_scores<4, true>) : scores(k_scores<4, false>); break;
   }
   if ((e = hipGetLastError()) != hipSuccess || k == 0) return e;
-  k_rank<<<blocks_for(d_in, 64), 1024, 0, s>>>(score, d_in, k, chosen);
+  k_rank<<<dim3(blocks_for(d_in, 64), 16), 256, 0, s>>>(score, d_in, rank);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_compact<<<1, 1024, 0, s>>>(chosen, d_in, k, idx_out);
+  k_compact<<<1, 1024, 0, s>>>(rank, d_in, k, idx_out);
   return hipGetLastError();
 }
 
