@@ -495,15 +495,11 @@ hipError_t launch_prefill_segments(const mes_linear* lin, int n_linears, const i
       tp.n_tq = pl.n_tq;
       tp.xt = reinterpret_cast<u32x4*>(ws);
       hipError_t e = hipSuccess;
-      if (l == 0) {   // the input channels: the same for every layer of the call
-        tp.kb_begin = 0;
-        tp.n_blk = (size_t)tp.n_kb_main * pl.n_tq;
-        k_prefill_tile_x<<<(unsigned)((tp.n_blk + 3) / 4), 256, 0, s>>>(tp);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-      }
-      if (pl.n_ssteps > 0) {   // this layer's gathered salient channels, behind them
-        tp.kb_begin = tp.n_kb_main;
-        tp.n_blk = (size_t)4 * pl.n_ssteps * pl.n_tq;
+      // the input channels, the same for every layer of the call, go with the first one; every layer has its own
+      // gathered salient channels, behind them (one launch for both: a second one took 5 us)
+      tp.kb_begin = l == 0 ? 0 : tp.n_kb_main;
+      tp.n_blk = (size_t)(tp.n_kb_main + 4 * pl.n_ssteps - tp.kb_begin) * pl.n_tq;
+      if (tp.n_blk > 0) {
         k_prefill_tile_x<<<(unsigned)((tp.n_blk + 3) / 4), 256, 0, s>>>(tp);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }

@@ -45,23 +45,26 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 
 // x [n_tokens, d_in] bf16 row-major -> fragment order: block (kb, tq) holds, for lane l, the 8 values
 // x[16 tq + (l & 15)][32 kb + 8 (l >> 4) ...]; zero beyond the last token and the last column.
-__global__ void k_tile_x(const uint16_t* __restrict__ x, int n_tokens, int d_in, int n_tq, u32x4* __restrict__ xt) {
+// The first block writes the salient-column mask instead: one bit per column, set for the columns in sidx (a launch of
+// its own took 4 us).
+__global__ __launch_bounds__(256) void k_tile_x(const uint16_t* __restrict__ x, int n_tokens, int d_in, int n_tq, u32x4* __restrict__ xt,
+                                                const int32_t* __restrict__ sidx, int k, int n_words, uint32_t* __restrict__ mask) {
+  if (blockIdx.x == 0) {
+    for (int w = threadIdx.x; w < n_words; w += 256) mask[w] = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < k; i += 256) {
+      const int c = sidx[i];
+      if (c >= 0 && c < 32 * n_words) atomicOr(&mask[c >> 5], 1u << (c & 31));
+    }
+    return;
+  }
   const int lane = threadIdx.x & 63;
-  const size_t blk = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const size_t blk = (size_t)(blockIdx.x - 1) * 4 + (threadIdx.x >> 6);
   const int tq = (int)(blk % n_tq), kb = (int)(blk / n_tq);
   const int t = 16 * tq + (lane & 15), c = 32 * kb + 8 * (lane >> 4);
   u32x4 v = {0, 0, 0, 0};
   if (t < n_tokens && c < d_in) v = *reinterpret_cast<const u32x4*>(x + (size_t)t * d_in + c);
   xt[blk * 64 + lane] = v;
-}
-
-__global__ void k_salient_mask(const int32_t* __restrict__ sidx, int k, int n_words, uint32_t* __restrict__ mask) {
-  for (int w = threadIdx.x; w < n_words; w += blockDim.x) mask[w] = 0;
-  __syncthreads();
-  for (int i = threadIdx.x; i < k; i += blockDim.x) {
-    const int c = sidx[i];
-    if (c >= 0 && c < 32 * n_words) atomicOr(&mask[c >> 5], 1u << (c & 31));
-  }
 }
 
 // E and D for 8 consecutive input channels of one row, as two packed bf16 operands.
@@ -517,10 +520,9 @@ hipError_t launch_step_grad(const float* delta, int d_in, int d_out, const int32
   hipError_t e;
   if (n_tokens > 0) {
     const size_t n_blk = (size_t)(L.d_in_pad / 32) * L.n_tq;   // a multiple of 4
-    k_tile_x<<<(unsigned)(n_blk / 4), 256, 0, s>>>(reinterpret_cast<const uint16_t*>(x), n_tokens, d_in, L.n_tq,
-                                                    reinterpret_cast<u32x4*>(w + L.xt_at));
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_salient_mask<<<1, 256, 0, s>>>(sidx, k, L.d_in_pad / 32, reinterpret_cast<uint32_t*>(w + L.mask_at));
+    k_tile_x<<<(unsigned)(n_blk / 4) + 1, 256, 0, s>>>(reinterpret_cast<const uint16_t*>(x), n_tokens, d_in, L.n_tq,
+                                                        reinterpret_cast<u32x4*>(w + L.xt_at), sidx, k, L.d_in_pad / 32,
+                                                        reinterpret_cast<uint32_t*>(w + L.mask_at));
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const dim3 g(L.d_out_pad / kRows, L.n_tb, L.n_split);
     if (ev_start && (e = hipEventRecord(ev_start, s)) != hipSuccess) return e;
