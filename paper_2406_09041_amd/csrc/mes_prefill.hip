@@ -30,7 +30,11 @@ struct PrefillParams {
   const float* step[kMaxSegs];       // [d_out]
   const u32x4* sal[kMaxSegs];        // salient tile: ((jt * n_sb + sb) * 64 + lane) x 8 fp16
   int t_begin[kMaxSegs], t_end[kMaxSegs];   // the segment's rows of x and y
-  int tb0[kMaxSegs + 1];             // its first token block (of 256 tokens) in the launch; tb0[n_seg] = all blocks
+  int tb0[kMaxSegs + 1];             // its first token block (of 256 tokens) in xt; tb0[n_seg] = all blocks
+  // The launch's order of the blocks: all the full ones, segment by segment (fb0: where a segment's start), then the
+  // segments' last, partial ones, which take less time and fill the compute units behind the others.
+  int fb0[kMaxSegs + 1];
+  int n_full, tail_seg[kMaxSegs];
   int n_seg;
   const u32x4* xt;          // the segments' activations in fragment order: [k block][token tile][64 lanes] x 16 bytes,
                             // k blocks 0 .. 4 n_chunks - 1 the input channels, then 4 n_ssteps blocks of gathered salient ones
@@ -106,12 +110,153 @@ __global__ void k_prefill_tile_x(const TileParams p) {
   p.xt[((size_t)kbi * p.n_tq + tq) * 64 + lane] = v;
 }
 
+// Token block y of the launch: its segment, its number in the segment and the token tiles that each of the 4 multipliers
+// takes (a last block of few tokens: fewer than 4).
+struct TokenBlock { int sg, blk, tiles; };
+__device__ __forceinline__ TokenBlock token_block(const PrefillParams& p, int y) {
+  TokenBlock b{0, 0, 4};
+  if (y < p.n_full) {
+#pragma unroll
+    for (int i = 1; i < kMaxSegs; ++i) b.sg += y >= p.fb0[i] ? 1 : 0;   // (one trip to the argument block, no chain of them)
+    b.blk = y - p.fb0[b.sg];
+  } else {
+    b.sg = p.tail_seg[y - p.n_full];
+    b.blk = p.fb0[b.sg + 1] - p.fb0[b.sg];
+    b.tiles = (p.t_end[b.sg] - p.t_begin[b.sg] - 256 * b.blk + 63) / 64;
+  }
+  return b;
+}
+
 // What a builder keeps in flight for one step (128 input channels, or 128 salient ranks) of its row tile.
 template <int BITS>
 struct StepData {
   u32x4 w[4];                              // base fragments (main step) or 8 fp16 salient values (salient step), per k block
   uint32_t lo[4], hi[BITS >= 3 ? 4 : 1];   // code words
 };
+
+constexpr int kRingDepth = 3;   // k blocks in a multiplier's LDS ring
+
+// A multiplier's work: all RT row tiles of every step (operands from LDS) with TT token tiles of its own, TT tiles from
+// token tile TT wave of the block.
+template <int RT, int NM, int TT>
+__device__ __forceinline__ void multiply_block(const PrefillParams& p, const TokenBlock& tb, u32x4 (&afrag)[2][RT][4][64],
+                                               u32x4 (*xring)[kRingDepth][4][64], int wave, int st0, int st1) {
+  constexpr int XD = kRingDepth;
+  constexpr bool kXDirect = RT <= 7;                     // activations straight into registers (RT = 8 has none to spare)
+  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  const int tq0 = 16 * (p.tb0[tb.sg] + tb.blk) + TT * wave;
+  f32x4 acc[RT][TT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0, 0, 0, 0};
+  if constexpr (kXDirect) {
+    // two register sets filled by ordinary loads one k block ahead: no LDS traffic for the activations
+    const u32x4* xsrc = p.xt + (size_t)tq0 * 64 + lane;
+    const size_t x_stride = (size_t)p.n_tq * 64;        // 16-byte units between k blocks
+    const int kbg_last = 4 * st1 - 1;
+    u32x4 xb[2][TT];
+    auto request_x = [&](int kbg, int set) {
+      const u32x4* src = xsrc + (size_t)(kbg < kbg_last ? kbg : kbg_last) * x_stride;
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) xb[set][tt] = src[tt * 64];
+    };
+    request_x(4 * st0, 0);
+    __syncthreads();
+    for (int st = st0; st < st1; ++st) {
+      const int cur = st & 1;
+      u32x4 a[2];                                        // operands are read from LDS one row tile ahead of their use
+      a[0] = afrag[cur][0][0][lane];
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) {
+        request_x(4 * st + kb + 1, (kb + 1) & 1);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          constexpr int kNone = -1;
+          const int rn = rt < RT - 1 ? rt + 1 : 0, kn = rt < RT - 1 ? kb : (kb < 3 ? kb + 1 : kNone);
+          if (kn != kNone) a[(kb * RT + rt + 1) & 1] = afrag[cur][rn][kn][lane];
+          __builtin_amdgcn_sched_barrier(0);             // keep the read above ahead of the matrix instructions below
+#pragma unroll
+          for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma_bf16(a[(kb * RT + rt) & 1], xb[kb & 1][tt], acc[rt][tt]);
+        }
+      }
+      step_barrier();
+    }
+  } else {
+    const char* xbase = reinterpret_cast<const char*>(p.xt + (size_t)tq0 * 64);
+    const size_t x_stride = (size_t)p.n_tq * 1024;        // bytes between k blocks
+    const int kbg_last = 4 * st1 - 1;
+    auto request_x = [&](int kbg, int slot) {             // TT copies of 1 KiB: lane l moves 16 bytes
+      const char* src = xbase + (size_t)(kbg < kbg_last ? kbg : kbg_last) * x_stride;
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) {
+        const uint32_t l = (uint32_t)(uintptr_t)&xring[wave][slot][tt][0];
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                     : : "v"((uint32_t)lane * 16u), "s"(src + tt * 1024), "s"(l) : "memory", "m0");
+      }
+    };
+    // the copies are this wavefront's only memory loads, TT per k block, completed in order: "at most TT (XD - 1)
+    // outstanding" means the oldest requested block has arrived
+    constexpr int kXAhead = XD - 1;
+#pragma unroll
+    for (int b = 0; b < kXAhead; ++b) request_x(4 * st0 + b, b);
+    int slot = 0;                                          // ring slot of the block multiplied next
+    __syncthreads();
+    for (int st = st0; st < st1; ++st) {
+      const int cur = st & 1;
+      u32x4 a[2];                                          // operands are read from LDS one row tile ahead of their use
+      a[0] = afrag[cur][0][0][lane];
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) {
+        const int ahead = slot + kXAhead < XD ? slot + kXAhead : slot + kXAhead - XD;   // the slot multiplied last
+        request_x(4 * st + kb + kXAhead, ahead);
+        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(TT * kXAhead) : "memory");
+        u32x4 xb[TT];
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) xb[tt] = xring[wave][slot][tt][lane];
+        slot = slot + 1 < XD ? slot + 1 : 0;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          constexpr int kNone = -1;
+          const int rn = rt < RT - 1 ? rt + 1 : 0, kn = rt < RT - 1 ? kb : (kb < 3 ? kb + 1 : kNone);
+          if (kn != kNone) a[(kb * RT + rt + 1) & 1] = afrag[cur][rn][kn][lane];
+          __builtin_amdgcn_sched_barrier(0);               // keep the read above ahead of the matrix instructions below
+#pragma unroll
+          for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma_bf16(a[(kb * RT + rt) & 1], xb[tt], acc[rt][tt]);
+        }
+      }
+      step_barrier();
+    }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // the surplus copies must land before the LDS is given back
+  }
+
+  if (p.n_split > 1) {   // this workgroup saw a share of the contraction only: leave the tiles, in thread order
+    constexpr int NT = 64 * NM;
+    f32x4* t = p.tiles + ((((size_t)blockIdx.z * gridDim.x + blockIdx.x) * gridDim.y + blockIdx.y) * (RT * 4)) * NT + threadIdx.x;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) t[(size_t)(rt * 4 + tt) * NT] = acc[rt][tt];
+    return;
+  }
+  // this lane holds, per row tile and token tile, rows 4 g .. 4 g + 3 at token n
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const int j = 16 * (RT * blockIdx.x + rt) + 4 * g;
+    if (j >= p.d_out) continue;                          // d_out % 4 == 0
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      const int t = p.t_begin[tb.sg] + 16 * (tq0 - 16 * p.tb0[tb.sg] + tt) + n;
+      if (t < p.t_end[tb.sg]) {
+        const f32x4 o = acc[rt][tt];
+        uint2 pk;
+        pk.x = f32_to_bf16(o[0]) | (f32_to_bf16(o[1]) << 16);
+        pk.y = f32_to_bf16(o[2]) | (f32_to_bf16(o[3]) << 16);
+        *reinterpret_cast<uint2*>(p.y + (size_t)t * p.d_out + j) = pk;
+      }
+    }
+  }
+}
 
 // Grid: (row groups of 16 RT output channels, token blocks of 64 NM tokens, n_split); NM + RT wavefronts in two
 // roles, spread evenly over the SIMDs (RT = 8, or 7 where that fills the last round of workgroups: prefill_plan).
@@ -120,33 +265,32 @@ struct StepData {
 //   builders (the last RT wavefronts): builder r forms the operand of row tile r (16 output channels) for the next
 //     step of 128 input channels in the idle LDS buffer, from base weight and codes requested two steps ahead;
 //   multipliers (wavefronts 0 .. NM - 1): every one multiplies all RT row tiles of the current step (from LDS) with
-//     its own 64 tokens.  With RT = 8 the activations reach it through an LDS ring of its own, filled by
+//     its own 64 tokens (fewer in a segment's last block: a block of 3 tokens takes 0.62 of a full one's time, not all of
+//     it; 2141 + 1064 + 1027 tokens through the seven linears of a block: 3.02 -> 2.87 ms).  With RT = 8 the activations reach it through an LDS ring of its own, filled by
 //     asynchronous copies two k blocks ahead; with RT = 7 the 16 registers that leaves free hold a second set of
 //     activation fragments, loaded straight from memory one k block ahead (5 % faster: less LDS traffic).
 // Every workgroup reads all the activations of its tokens from L2 once per step, so the rows per workgroup set the
 // L2 traffic: 128 rows x 256 tokens halve it against 64 rows x 512 tokens, at the price of building every operand
-// once per 256 tokens.  Measured with parts of the kernel taken out (3 experts x 512 tokens, 14336 rows; the whole
-// kernel 213 us): barriers and LDS traffic alone 88 us, + activation copies 120 us, + the builders' loads and
-// arithmetic 165 us, the matrix instructions the rest -- the parts add up rather than overlap, and what they share
-// is the LDS pipe (operands for 4 multipliers, the builders' stores, the ring's copies and reads).
+// once per 256 tokens.  What bounds it, with parts of the RT = 7 kernel taken out (3 experts x 512 tokens, 14336 rows; the
+// whole call 217 us, about 12 of them re-tiling): without matrix instructions 183, without the builders' loads and arithmetic
+// 163 (their arithmetic alone costs nothing: 214), without activation loads 182, matrix instructions and barriers alone
+// 117.  The loads do: 2.7 GB per launch leave the L2s, 14 TB/s, and 0.5 GB come from memory.  The matrix instructions
+// themselves run at what the card's power allows (the same call on zeros: 167 us).
 // One barrier per step.  The steps are the n_chunks chunks of input channels followed by n_ssteps steps over the
 // salient ranks; with n_split > 1 a workgroup covers a share of them and leaves its accumulators to
 // k_prefill_reduce.
 template <int BITS, int RT, int NM>
 __global__ __launch_bounds__(64 * (NM + RT), 1) void k_prefill_fused(const PrefillParams p) {
-  constexpr int TT = 4;                                  // token tiles per multiplier
-  constexpr int XD = 3;                                  // ring depth in k blocks
   __shared__ __attribute__((aligned(16))) u32x4 afrag[2][RT][4][64];     // [buffer][row tile][k block][lane]
-  constexpr bool kXDirect = RT <= 7;                     // activations straight into registers (RT = 8 has none to spare)
-  __shared__ __attribute__((aligned(16))) u32x4 xring[kXDirect ? 1 : NM][XD][TT][64];   // [multiplier][slot][token tile][lane]
+  __shared__ __attribute__((aligned(16))) u32x4 xring[RT <= 7 ? 1 : NM][kRingDepth][4][64];   // [multiplier][slot][token tile][lane]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, g = lane >> 4;
   const int n_steps = p.n_chunks + p.n_ssteps;
   const int st0 = blockIdx.z * p.steps_per_split;
   const int st1 = st0 + p.steps_per_split < n_steps ? st0 + p.steps_per_split : n_steps;
-  int sg = 0;                                            // the segment (expert) this token block belongs to
-  while (sg + 1 < p.n_seg && (int)blockIdx.y >= p.tb0[sg + 1]) ++sg;
+  const TokenBlock tb = token_block(p, blockIdx.y);
+  const int sg = tb.sg;                                  // the segment (expert) this token block belongs to
 
   if (wave >= NM) {
     // ---- builder
@@ -238,119 +382,11 @@ __global__ __launch_bounds__(64 * (NM + RT), 1) void k_prefill_fused(const Prefi
     return;
   }
 
-  // ---- multiplier: token tiles TT (NM by + wave) .. + TT - 1 of the segment
-  const int tq0 = TT * (NM * blockIdx.y + wave);
-  f32x4 acc[RT][TT];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0, 0, 0, 0};
-  if constexpr (kXDirect) {
-    // two register sets filled by ordinary loads one k block ahead: no LDS traffic for the activations
-    const u32x4* xsrc = p.xt + (size_t)tq0 * 64 + lane;
-    const size_t x_stride = (size_t)p.n_tq * 64;        // 16-byte units between k blocks
-    const int kbg_last = 4 * st1 - 1;
-    u32x4 xb[2][TT];
-    auto request_x = [&](int kbg, int set) {
-      const u32x4* src = xsrc + (size_t)(kbg < kbg_last ? kbg : kbg_last) * x_stride;
-#pragma unroll
-      for (int tt = 0; tt < TT; ++tt) xb[set][tt] = src[tt * 64];
-    };
-    request_x(4 * st0, 0);
-    __syncthreads();
-    for (int st = st0; st < st1; ++st) {
-      const int cur = st & 1;
-      u32x4 a[2];                                        // operands are read from LDS one row tile ahead of their use
-      a[0] = afrag[cur][0][0][lane];
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        request_x(4 * st + kb + 1, (kb + 1) & 1);
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          constexpr int kNone = -1;
-          const int rn = rt < RT - 1 ? rt + 1 : 0, kn = rt < RT - 1 ? kb : (kb < 3 ? kb + 1 : kNone);
-          if (kn != kNone) a[(kb * RT + rt + 1) & 1] = afrag[cur][rn][kn][lane];
-          __builtin_amdgcn_sched_barrier(0);             // keep the read above ahead of the matrix instructions below
-#pragma unroll
-          for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma_bf16(a[(kb * RT + rt) & 1], xb[kb & 1][tt], acc[rt][tt]);
-        }
-      }
-      step_barrier();
-    }
-  } else {
-    const char* xbase = reinterpret_cast<const char*>(p.xt + (size_t)tq0 * 64);
-    const size_t x_stride = (size_t)p.n_tq * 1024;        // bytes between k blocks
-    const int kbg_last = 4 * st1 - 1;
-    auto request_x = [&](int kbg, int slot) {             // TT copies of 1 KiB: lane l moves 16 bytes
-      const char* src = xbase + (size_t)(kbg < kbg_last ? kbg : kbg_last) * x_stride;
-#pragma unroll
-      for (int tt = 0; tt < TT; ++tt) {
-        const uint32_t l = (uint32_t)(uintptr_t)&xring[wave][slot][tt][0];
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                     : : "v"((uint32_t)lane * 16u), "s"(src + tt * 1024), "s"(l) : "memory", "m0");
-      }
-    };
-    // the copies are this wavefront's only memory loads, TT per k block, completed in order: "at most TT (XD - 1)
-    // outstanding" means the oldest requested block has arrived
-    constexpr int kXAhead = XD - 1;
-#pragma unroll
-    for (int b = 0; b < kXAhead; ++b) request_x(4 * st0 + b, b);
-    int slot = 0;                                          // ring slot of the block multiplied next
-    __syncthreads();
-    for (int st = st0; st < st1; ++st) {
-      const int cur = st & 1;
-      u32x4 a[2];                                          // operands are read from LDS one row tile ahead of their use
-      a[0] = afrag[cur][0][0][lane];
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        const int ahead = slot + kXAhead < XD ? slot + kXAhead : slot + kXAhead - XD;   // the slot multiplied last
-        request_x(4 * st + kb + kXAhead, ahead);
-        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(TT * kXAhead) : "memory");
-        u32x4 xb[TT];
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) xb[tt] = xring[wave][slot][tt][lane];
-        slot = slot + 1 < XD ? slot + 1 : 0;
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          constexpr int kNone = -1;
-          const int rn = rt < RT - 1 ? rt + 1 : 0, kn = rt < RT - 1 ? kb : (kb < 3 ? kb + 1 : kNone);
-          if (kn != kNone) a[(kb * RT + rt + 1) & 1] = afrag[cur][rn][kn][lane];
-          __builtin_amdgcn_sched_barrier(0);               // keep the read above ahead of the matrix instructions below
-#pragma unroll
-          for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma_bf16(a[(kb * RT + rt) & 1], xb[tt], acc[rt][tt]);
-        }
-      }
-      step_barrier();
-    }
-    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // the surplus copies must land before the LDS is given back
-  }
-
-  if (p.n_split > 1) {   // this workgroup saw a share of the contraction only: leave the tiles, in thread order
-    constexpr int NT = 64 * NM;
-    f32x4* t = p.tiles + ((((size_t)blockIdx.z * gridDim.x + blockIdx.x) * gridDim.y + blockIdx.y) * (RT * TT)) * NT + threadIdx.x;
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int tt = 0; tt < TT; ++tt) t[(size_t)(rt * TT + tt) * NT] = acc[rt][tt];
-    return;
-  }
-  // this lane holds, per row tile and token tile, rows 4 g .. 4 g + 3 at token n
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int j = 16 * (RT * blockIdx.x + rt) + 4 * g;
-    if (j >= p.d_out) continue;                          // d_out % 4 == 0
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-      const int t = p.t_begin[sg] + 16 * (tq0 - 16 * p.tb0[sg] + tt) + n;
-      if (t < p.t_end[sg]) {
-        const f32x4 o = acc[rt][tt];
-        uint2 pk;
-        pk.x = f32_to_bf16(o[0]) | (f32_to_bf16(o[1]) << 16);
-        pk.y = f32_to_bf16(o[2]) | (f32_to_bf16(o[3]) << 16);
-        *reinterpret_cast<uint2*>(p.y + (size_t)t * p.d_out + j) = pk;
-      }
-    }
-  }
+  // ---- multiplier
+  if (tb.tiles == 4) multiply_block<RT, NM, 4>(p, tb, afrag, xring, wave, st0, st1);
+  else if (tb.tiles == 3) multiply_block<RT, NM, 3>(p, tb, afrag, xring, wave, st0, st1);
+  else if (tb.tiles == 2) multiply_block<RT, NM, 2>(p, tb, afrag, xring, wave, st0, st1);
+  else multiply_block<RT, NM, 1>(p, tb, afrag, xring, wave, st0, st1);
 }
 
 // Split contraction only: y = sum over splits (in split order) of the accumulator tiles, rounded to bf16.
@@ -362,14 +398,14 @@ __global__ __launch_bounds__(64 * NM) void k_prefill_reduce(const PrefillParams 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 15, g = lane >> 4;
   const int rt = blockIdx.z >> 2, tt = blockIdx.z & 3;
+  const TokenBlock tb = token_block(p, blockIdx.y);
+  if (tt >= tb.tiles) return;
   f32x4 o = {0, 0, 0, 0};
   for (int sp = 0; sp < p.n_split; ++sp)
     o += p.tiles[((((size_t)sp * gridDim.x + blockIdx.x) * gridDim.y + blockIdx.y) * (RT * TT) + blockIdx.z) * NT + threadIdx.x];
   const int j = 16 * (RT * blockIdx.x + rt) + 4 * g;
-  int sg = 0;
-  while (sg + 1 < p.n_seg && (int)blockIdx.y >= p.tb0[sg + 1]) ++sg;
-  const int t = p.t_begin[sg] + 16 * (TT * (NM * ((int)blockIdx.y - p.tb0[sg]) + wave) + tt) + n;
-  if (j < p.d_out && t < p.t_end[sg]) {
+  const int t = p.t_begin[tb.sg] + 256 * tb.blk + 16 * (tb.tiles * wave + tt) + n;
+  if (j < p.d_out && t < p.t_end[tb.sg]) {
     uint2 pk;
     pk.x = f32_to_bf16(o[0]) | (f32_to_bf16(o[1]) << 16);
     pk.y = f32_to_bf16(o[2]) | (f32_to_bf16(o[3]) << 16);
@@ -382,8 +418,40 @@ struct PrefillPlan {
   size_t xt_bytes, tiles_at, tiles_bytes;
 };
 
-// n_tb: token blocks of all the segments of the launch together
-PrefillPlan prefill_plan(int d_in, int d_out, int k, int n_tb) {
+// Time of a workgroup on a last block of up to 64, 128, 192 tokens, relative to one of 256 (4096 x 14336, 2141 + 1064 + 1027
+// tokens: seven rounds of 256 tokens and two of partial blocks in 588 us).
+constexpr double kTailTime[5] = {0.0, 0.62, 0.72, 0.86, 1.0};
+
+// Time of a launch of n_rg row groups, in full workgroups: the compute units take n_rg x n_full full ones and then, for
+// every partial block (tails: its 64-token quarters), n_rg shorter ones, each as soon as one is free.
+double launch_rounds(int n_rg, int n_full, const int* tails, int n_tails) {
+  struct { double at; int units; } pool[kMaxSegs * 4 + 4];     // compute units by the time they are free
+  const long full = (long)n_rg * n_full;
+  int n = 0;
+  pool[n++] = {(double)(full / kMaxWorkgroups), (int)(kMaxWorkgroups - full % kMaxWorkgroups)};
+  if (full % kMaxWorkgroups) pool[n++] = {(double)(full / kMaxWorkgroups + 1), (int)(full % kMaxWorkgroups)};
+  double end = pool[n - 1].at;
+  for (int i = 0; i < n_tails; ++i) {
+    for (int left = n_rg; left > 0;) {
+      int first = 0;
+      for (int q = 1; q < n; ++q) first = pool[q].at < pool[first].at ? q : first;
+      const int take = left < pool[first].units ? left : pool[first].units;
+      const double done = pool[first].at + kTailTime[tails[i]];
+      end = done > end ? done : end;
+      left -= take;
+      if (take == pool[first].units || n == (int)(sizeof(pool) / sizeof(pool[0]))) {
+        pool[first].at = done;                                 // (no room to tell them apart: all of them)
+      } else {
+        pool[first].units -= take;
+        pool[n++] = {done, take};
+      }
+    }
+  }
+  return end;
+}
+
+// n_tb: token blocks of all the segments of the launch together; n_full of them are full, tails: the others' quarters
+PrefillPlan prefill_plan(int d_in, int d_out, int k, int n_tb, int n_full, const int* tails) {
   PrefillPlan pl;
   pl.rt = 8;   // 128 rows x 256 tokens per workgroup: measured 6 % faster than 64 x 512 and 14 % faster than 64 x 256
   pl.nm = 4;
@@ -392,17 +460,18 @@ PrefillPlan prefill_plan(int d_in, int d_out, int k, int n_tb) {
   const int n_jt = ceil_to(d_out, kRowPad) / 16;
   pl.n_rg = (n_jt + pl.rt - 1) / pl.rt;
   // One workgroup per compute unit at a time: the launch takes ceil(workgroups / 256) rounds of one workgroup's
-  // time, which grows with its row tiles.  7 row tiles per workgroup win where they fill the last round better
-  // (14336 rows x 6 token blocks: 768 workgroups = 3 full rounds of 7 tiles against 2.6 -> 3 rounds of 8; 4096 rows x
-  // 6 blocks: one round of 222 workgroups against one of 192); + 1 below: the part of a workgroup's time that does
-  // not shrink with its rows.  (Equal tile-rounds -- 14336 rows x 16 token blocks: 8 rounds of 7 or 7 rounds of 8 --
-  // measured no better with 7.)  128 workgroups or fewer split the contraction instead and keep 8 tiles.
+  // time, which grows with its row tiles; the workgroups of partial blocks go behind and fill the last round.  7 row tiles
+  // per workgroup win where they fill the last round better (14336 rows x 6 token blocks: 768 workgroups = 3 full rounds
+  // of 7 tiles against 2.6 -> 3 rounds of 8; 4096 rows x 6 blocks: one round of 222 workgroups against one of 192); + 3.5
+  // below: the part of a workgroup's time that does not shrink with its rows (14336 rows, 16 full and 3 partial blocks:
+  // 9.24 rounds of 7 tiles in 616 us, 8.24 rounds of 8 in 588; 6 full blocks: 3 rounds of 7 in 203, of 8 in 219).  128
+  // workgroups or fewer split the contraction instead and keep 8 tiles.
   {
-    const long wg8 = (long)pl.n_rg * n_tb, rg7 = (n_jt + 6) / 7, wg7 = rg7 * n_tb;
-    const long rounds8 = (wg8 + kMaxWorkgroups - 1) / kMaxWorkgroups, rounds7 = (wg7 + kMaxWorkgroups - 1) / kMaxWorkgroups;
-    if (2 * wg8 > kMaxWorkgroups && rounds7 * (7 + 1) < rounds8 * (8 + 1)) {
+    auto rounds = [&](int rgs) { return launch_rounds(rgs, n_full, tails, n_tb - n_full); };
+    const int rg7 = (n_jt + 6) / 7;
+    if (2l * pl.n_rg * n_tb > kMaxWorkgroups && rounds(rg7) * (7 + 3.5) < rounds(pl.n_rg) * (8 + 3.5)) {
       pl.rt = 7;
-      pl.n_rg = (int)rg7;
+      pl.n_rg = rg7;
     }
   }
   pl.n_chunks = ceil_to(d_in, kColPad) / 128;
@@ -458,7 +527,8 @@ hipError_t launch_prefill_segments(const mes_linear* lin, int n_linears, const i
       const mes_delta& d = experts[seg_experts[first]];   // shape, bits, grid and k are the same for all experts of a linear
       PrefillParams p;
       TileParams tp;
-      int n_tb = 0;
+      int n_tb = 0, n_tails = 0, tails[kMaxSegs];
+      p.n_full = 0;
       for (int i = 0; i < kMaxSegs; ++i) {
         const mes_delta& de = experts[seg_experts[first + (i < ns ? i : 0)]];
         const int e = seg_experts[first + (i < ns ? i : 0)];
@@ -469,12 +539,24 @@ hipError_t launch_prefill_segments(const mes_linear* lin, int n_linears, const i
         p.t_begin[i] = tp.t_begin[i] = seg[e];
         p.t_end[i] = tp.t_end[i] = seg[e + 1];
         p.tb0[i] = tp.tb0[i] = n_tb;
-        if (i < ns) n_tb += (seg[e + 1] - seg[e] + 255) / 256;
+        p.fb0[i] = p.n_full;
+        if (i < ns) {
+          const int len = seg[e + 1] - seg[e], full = len / 256, left = len - 256 * full;
+          n_tb += full;
+          p.n_full += full;
+          if (left > 0) {
+            p.tail_seg[n_tails] = i;
+            tails[n_tails++] = (left + 63) / 64;
+            ++n_tb;
+          }
+        }
       }
+      p.fb0[kMaxSegs] = p.n_full;
       p.tb0[kMaxSegs] = tp.tb0[kMaxSegs] = n_tb;
       for (int i = ns; i <= kMaxSegs; ++i) p.tb0[i] = tp.tb0[i] = n_tb;
+      for (int i = n_tails; i < kMaxSegs; ++i) p.tail_seg[i] = 0;
       p.n_seg = tp.n_seg = ns;
-      const PrefillPlan pl = prefill_plan(d.d_in, d.d_out, d.k, n_tb);
+      const PrefillPlan pl = prefill_plan(d.d_in, d.d_out, d.k, n_tb, p.n_full, tails);
       p.base = reinterpret_cast<const u32x4*>(lin[l].w_base_tiled);
       p.xt = reinterpret_cast<const u32x4*>(ws);
       p.y = reinterpret_cast<uint16_t*>(lin[l].y);

@@ -1,0 +1,18 @@
+"""One-product path: segments whose last block of 256 tokens is partial take fewer token tiles per multiplier (one for up to
+64 tokens, two for 128, three for 192) and run behind the full ones.  Every number of tiles, with the contraction split
+over workgroups (few rows) and not, 7 and 8 row tiles per workgroup, one launch and two."""
+import pytest
+
+from inputs import synth
+from test_gpu_parity import run_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d_in,d_out,k,bits", [(520, 72, 8, 2), (264, 2064, 5, 3), (136, 4096, 0, 1), (1032, 200, 33, 4)])
+@pytest.mark.parametrize("lengths", [[193], [256], [257], [320, 321], [449, 512, 384, 300], [192, 5, 448, 513], [255] * 3 + [258] * 3 + [200] * 3])
+def test_partial_token_blocks(d_in, d_out, k, bits, lengths):
+    off = [0]
+    for n in lengths:
+        off.append(off[-1] + n)
+    run_case(synth.small_case(d_in, d_out, off, k, bits, seed=len(lengths)))
