@@ -329,8 +329,8 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
     const int t = p.t0 + 16 * tt + n, j = 16 * jt + 4 * g;
     if (t < p.T && j < L.d_out) {
       uint2 pk;
-      pk.x = f32_to_bf16(o[0]) | (f32_to_bf16(o[1]) << 16);
-      pk.y = f32_to_bf16(o[2]) | (f32_to_bf16(o[3]) << 16);
+      pk.x = pack_bf16(o[0], o[1]);
+      pk.y = pack_bf16(o[2], o[3]);
       *reinterpret_cast<uint2*>(L.y + (size_t)t * L.d_out + j) = pk;
     }
   }

@@ -50,11 +50,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 }
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-__device__ __forceinline__ uint32_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-  return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
 __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
@@ -250,8 +245,8 @@ __device__ __forceinline__ void multiply_block(const PrefillParams& p, const Tok
       if (t < p.t_end[tb.sg]) {
         const f32x4 o = acc[rt][tt];
         uint2 pk;
-        pk.x = f32_to_bf16(o[0]) | (f32_to_bf16(o[1]) << 16);
-        pk.y = f32_to_bf16(o[2]) | (f32_to_bf16(o[3]) << 16);
+        pk.x = pack_bf16(o[0], o[1]);
+        pk.y = pack_bf16(o[2], o[3]);
         *reinterpret_cast<uint2*>(p.y + (size_t)t * p.d_out + j) = pk;
       }
     }
@@ -407,8 +402,8 @@ __global__ __launch_bounds__(64 * NM) void k_prefill_reduce(const PrefillParams 
   const int t = p.t_begin[tb.sg] + 256 * tb.blk + 16 * (tb.tiles * wave + tt) + n;
   if (j < p.d_out && t < p.t_end[tb.sg]) {
     uint2 pk;
-    pk.x = f32_to_bf16(o[0]) | (f32_to_bf16(o[1]) << 16);
-    pk.y = f32_to_bf16(o[2]) | (f32_to_bf16(o[3]) << 16);
+    pk.x = pack_bf16(o[0], o[1]);
+    pk.y = pack_bf16(o[2], o[3]);
     *reinterpret_cast<uint2*>(p.y + (size_t)t * p.d_out + j) = pk;
   }
 }
