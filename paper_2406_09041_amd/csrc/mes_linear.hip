@@ -919,14 +919,6 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
     mp.n_first = n_first > 0 ? n_first : ng;
     mp.wg_per_group = mp.rg8 * 8 * pl.nsplit;
     hipError_t e;
-    if (c.T <= 32 && few_tokens_fits(mp.g[0])) {   // a handful of tokens: one launch for everything (mes_few.hip)
-      if (c.ev_start && first_kernel && (e = hipEventRecord(c.ev_start, s)) != hipSuccess) return e;
-      first_kernel = false;
-      if ((e = launch_few_tokens(mp.g[0], s)) != hipSuccess) return e;
-      if (c.ev_stop && (e = hipEventRecord(c.ev_stop, s)) != hipSuccess) return e;
-      ng = 0; tt_max = 1; items_max = 0;
-      return hipSuccess;
-    }
     k_prepare<<<dim3(items_max, ng), 256, 0, s>>>(mp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (c.ev_start && first_kernel && (e = hipEventRecord(c.ev_start, s)) != hipSuccess) return e;
@@ -1015,9 +1007,20 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
         p.tiles = (nt + 15) / 16;
         p.n_stage_items = p.tiles * p.n_chunks;
         p.n_items = p.n_stage_items + c.n_linears * p.n_vis;
+        t0 += nt;
+        // A handful of tokens: one launch does everything for the group (mes_few.hip), now, instead of a place in the
+        // streaming launch.  A call of few tokens is several groups if more than kMaxSlots experts own them; each decides
+        // for itself, so the route does not depend on how many groups the workspace holds.
+        if (c.T <= 32 && few_tokens_fits(p)) {
+          hipError_t e;
+          if (c.ev_start && first_kernel && (e = hipEventRecord(c.ev_start, s)) != hipSuccess) return e;
+          first_kernel = false;
+          if ((e = launch_few_tokens(p, s)) != hipSuccess) return e;
+          if (c.ev_stop && (e = hipEventRecord(c.ev_stop, s)) != hipSuccess) return e;
+          continue;
+        }
         tt_max = tt > tt_max ? tt : tt_max;
         items_max = p.n_items > items_max ? p.n_items : items_max;
-        t0 += nt;
       }
       ++ng;
       if (ng == max_groups) {

@@ -91,3 +91,37 @@ def test_same_result_every_time_and_for_any_row_of_the_batch():
     keep = [i for i in range(16) if i not in (3, 9)]
     assert torch.equal(y[keep], yb[keep])
     assert not torch.isfinite(yb[[3, 9]].float()).any()
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("tokens,experts", [(17, 17), (20, 20), (32, 32), (32, 18), (30, 24)])
+def test_more_experts_than_a_token_group_holds(tokens, experts, bits):
+    """More than 16 experts make several token groups of a call, however few its tokens.  Every entry point, with room for
+    one, two and four groups (a server sizes its workspace once, for its largest batch): all rows are written, the oracle's
+    bars hold, and the bits do not depend on the workspace."""
+    d_in, d_out, k = 392, 76, 9
+    seg = segments(tokens, experts)
+    wls = [synth.small_case(d_in, d, seg, k, bits, seed=60 + i) for i, d in enumerate((d_out, d_out, 40))]
+    x64, x = wls[0].x.double().numpy(), wls[0].x.to(DEV)
+    packed = [(mes.mes_pack_base(wl.w_base.to(DEV)), [mes.mes_pack_delta(ex.delta.to(DEV), ex.salient_idx, bits) for ex in wl.experts]) for wl in wls]
+    oes = [oracle_experts(wl) for wl in wls]
+    w64 = [wl.w_base.double().numpy() for wl in wls]
+    refs = [O.delta_linear(x64, w, oe, seg) for w, oe in zip(w64, oes)]
+    refs.append(O.gated_mlp_input(x64, w64[0], oes[0], w64[1], oes[1], seg))
+
+    def unwritten(d):
+        return torch.full((tokens, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+
+    runs = []
+    for room in (1, 128, 256):
+        one = mes.DeltaLinear(*packed[0], max_tokens=room)(x, seg, unwritten(d_out))
+        ys = mes.DeltaLinearMulti(packed, max_tokens=room)(x, seg, [unwritten(wl.d_out) for wl in wls])
+        h = mes.DeltaLinearGated(*packed[0], *packed[1], max_tokens=room)(x, seg, unwritten(d_out))
+        runs.append([one, *ys, h])
+    y = unwritten(d_out)
+    mes.mes_delta_linear_noalloc(*packed[0], x, seg, y)
+    for got, ref in zip([*runs[0], y], [refs[0], *refs, refs[0]]):
+        PC.assert_streaming_rows(got.double().cpu().numpy(), ref, (tokens, experts, bits))
+    for run in runs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(run, runs[0]))
+    assert torch.equal(y, runs[0][0])
