@@ -360,14 +360,13 @@ void launch_slots(const LinearParams& p, int grid, int team_log, int mine, hipSt
 
 }  // namespace
 
-// Row tiles of a launch, wavefronts per row tile (as a power of two) and workgroups.  One workgroup runs per compute unit;
+// Wavefronts per row tile (as a power of two) and workgroups of a launch.  One workgroup runs per compute unit;
 // the teams are as large as fills the 256 of them once, a second round of workgroups pays the start-up again (about 3.5
 // chunks' worth).
-struct FewPlan { int n_tiles, team_log, grid, mine; };   // mine: chunks per wavefront
+struct FewPlan { int team_log, grid, mine; };   // mine: chunks per wavefront
 
 static FewPlan few_plan(const LinearParams& p) {
-  FewPlan f{0, 0, 0, 0};
-  for (int l = 0; l < (p.pair ? 1 : p.n_linears); ++l) f.n_tiles += (p.lin[l].d_out + 15) / 16;
+  FewPlan f{0, 0, 0};
   double best = 1e30;
   for (int t = p.pair ? 2 : 3; t >= 0; --t) {
     const int teams = (kFewWaves >> t) / (p.pair ? 2 : 1), mine = ((p.n_chunks - 1) >> t) + 1;
@@ -379,24 +378,24 @@ static FewPlan few_plan(const LinearParams& p) {
   return f;
 }
 
-// Which token groups take this path (us per call, streaming path -> here):
-//  - one token tile.  It wins by the two launches and the start-up it saves, and by the one sweep it needs where the
-//    streaming path's LDS holds fewer experts than the batch has:  4096 x 4096 with 1 / 4 / 8 / 16 experts 22.8 -> 14.1,
-//    24.8 -> 17.9, 30.2 -> 21.4, 43.0 -> 34.3; 14336 x 4096 with one 41.6 -> 31.9; 1024 x 1024 17.3 -> 8.5.
-//    Every row tile's wavefronts prepare the activations again, so the streaming path keeps what is a long stream
-//    anyway: more than 8 experts on more than 1024 row tiles (4096 x 28672, 12 experts: 125 -> 135) or more than 32 chunks per
-//    wavefront (14336 x 14336, 4 experts: 112 -> 117), and few row tiles with many chunks, whose columns it splits over
-//    more compute units (14336 x 256: 24.9 -> 25.8);
-//  - two token tiles, twice the preparation per chunk, up to 4 chunks per wavefront (4096 x 4096 with 1 / 8 experts 24.1 -> 22.0,
-//    31.1 -> 29.1, 1024 x 1024 20.3 -> 13.1; but 4096 x 6144 31.4 -> 35.5, 14336 x 4096 43.3 -> 52.3);
-//  - code words of a chunk fit the registers (4 bits: 8 experts, with two tiles 4; 3 bits with two tiles: 4);
-//  - few enough salient pairs for their place in LDS.
+// Token groups the kernel can take: one or two token tiles whose experts' code words fit the registers (one tile: 16
+// experts, at 4 bits 8; two tiles: 8 experts, at 3 and 4 bits 4), salient pairs that fit their place in LDS, 32-bit offsets
+// into x.
 bool few_tokens_fits(const LinearParams& p) {
-  if (p.tiles > 2 || p.n_vis * p.n_sb > (p.pair ? kFewPairs / 2 : kFewPairs) || p.d_in > (1 << 24)) return false;   // (32-bit offsets into x)
+  if (p.tiles > 2 || p.n_vis * p.n_sb > (p.pair ? kFewPairs / 2 : kFewPairs) || p.d_in > (1 << 24)) return false;
+  return p.tiles == 2 ? p.n_act <= (p.bits < 3 ? 8 : 4) : p.n_act <= 8 || p.bits < 4;
+}
+
+// Expected time of a group here, us: per round of workgroups a start-up, per chunk the multiplications and the
+// preparation of the activations (which every row tile's wavefronts do again, per tile of tokens), and the
+// wavefronts' shares of the salient pairs; plus a share of the weights' way from memory.  The terms are those of the
+// kernel, the numbers least squares over 1800 calls (d_in and d_out from 256 to 14336, one layer, two or three, gated
+// pairs, 1 to 32 tokens, 1 to 16 experts, 1 to 4 bits, up to 128 salient channels); 9 % off on 1250 others.
+double few_tokens_us(const LinearParams& p) {
   const FewPlan f = few_plan(p);
-  if (p.tiles == 2) return f.mine <= 4 && p.n_act <= (p.bits < 3 ? 8 : 4);
-  if (f.mine > 32 || (f.n_tiles < 64 && f.mine > 8)) return false;
-  return p.n_act <= 8 || (p.bits < 4 && f.n_tiles <= 1024);
+  const int rounds = (f.grid + 255) / 256, more = p.tiles - 1;
+  const double pairs = (double)(p.n_vis * p.n_sb) / (1 << f.team_log);
+  return 0.4 + rounds * (6.1 + 1.3 * more + f.mine * (0.9 + 0.13 * p.n_act + 1.1 * more) + pairs) + 0.28 * weights_us(p);
 }
 
 hipError_t launch_few_tokens(const LinearParams& p, hipStream_t s) {

@@ -766,6 +766,19 @@ Plan plan_for(int d_in, const int* d_out, int n_linears, bool pair) {
   return best;
 }
 
+// Expected time of one token group of few tokens on the streaming path, us (for the choice between the two paths; see
+// few_tokens_us for the calls the numbers come from; 8 % off on those not used for them).  Workgroup ids go round-robin to
+// 8 XCDs of 32 compute units and a row group's id names its XCD, so the fullest XCD counts the rounds (81 row groups x 3
+// splits are 243 workgroups, and 33 on the first XCD: two rounds).  Salient pairs that the chunks cannot carry are
+// multiplied one after the other.
+double streaming_us(const LinearParams& p, const Plan& pl, int rgs) {
+  const int rounds = ((rgs + 7) / 8 * pl.nsplit + 31) / 32, chunks = (p.n_chunks + pl.nsplit - 1) / pl.nsplit;
+  const int sweeps = p.n_act > full_slots(p.bits) ? 2 : 1;
+  const int left = (p.n_vis * p.n_sb + pl.nsplit - 1) / pl.nsplit - chunks * sweeps;
+  return 4.5 + (pl.nsplit > 1 ? 4.9 : 0.0) + 0.51 * weights_us(p) +
+         rounds * (5.4 + chunks * (0.64 + 0.10 * p.n_act + (sweeps > 1 ? 0.97 : 0.0)) + (left > 0 ? 0.62 * left : 0.0));
+}
+
 // The workspace of one token group; a launch of n groups uses n of these, one after the other.
 struct WorkspaceLayout {
   size_t xt, per_linear[kMaxLinears], partial, total;   // per linear: xs; total is a multiple of 256
@@ -898,6 +911,7 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
   // The streaming (decode) path.  Token groups are collected from all the token ranges it covers (the stretches
   // between long segments) and launched kMaxGroups at a time.
   int ng = 0, tt_max = 1, items_max = 0;
+  bool few = false;   // this call's groups take the one-launch path
   auto flush = [&]() -> hipError_t {
     if (ng == 0) return hipSuccess;
     // the groups with more experts than the short variant of the kernel holds go first (stable otherwise)
@@ -1009,9 +1023,17 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
         p.n_items = p.n_stage_items + c.n_linears * p.n_vis;
         t0 += nt;
         // A handful of tokens: one launch does everything for the group (mes_few.hip), now, instead of a place in the
-        // streaming launch.  A call of few tokens is several groups if more than kMaxSlots experts own them; each decides
-        // for itself, so the route does not depend on how many groups the workspace holds.
-        if (c.T <= 32 && few_tokens_fits(p)) {
+        // streaming launch, if that is expected to be faster.  us measured, streaming path against one launch:
+        //   one launch: 4096 x 4096 with 1 / 16 tokens of as many experts 22.8, 42.8 against 14.1, 34.4; 1024 x 1024 17.4
+        //     against 8.6; 4096 -> 14336, 3 bits, 16 tokens of 9 experts 94.9 against 78.8;
+        //   streaming: gated pairs that leave a round of its workgroups half empty (5120 -> 11008, 6 tokens of 3 experts 70.3
+        //     against 83.0) or have many experts on many rows (4096 -> 14336, 1 bit, 9 experts 88.5 against 96.3), long columns
+        //     (14336 -> 5120, 9 experts 77.3 against 91.5), most groups of two tiles on more than 4 chunks per wavefront.
+        // Over 3077 calls the choice costs 0.3 % against the better of the two.  (Equal expectations: the streaming path.)
+        // A call of few tokens is two groups if more than kMaxSlots experts own them; both take the first one's path, and
+        // the workspace has no say in it.
+        if (p.t0 == 0) few = c.T <= 32 && few_tokens_fits(p) && few_tokens_us(p) < 0.97 * streaming_us(p, pl, rgs);
+        if (few && few_tokens_fits(p)) {
           hipError_t e;
           if (c.ev_start && first_kernel && (e = hipEventRecord(c.ev_start, s)) != hipSuccess) return e;
           first_kernel = false;

@@ -228,8 +228,17 @@ __device__ __forceinline__ V keep(V v) {
 typedef __attribute__((address_space(1))) const u32x4 global_u32x4;
 __device__ __forceinline__ u32x4 ld128_at(uint64_t addr) { return *reinterpret_cast<global_u32x4*>(addr); }
 
-// The one-launch path for one tile of tokens (mes_few.hip).
+// The group's weights at 5 TB/s, us.
+inline double weights_us(const LinearParams& p) {
+  double row_tiles = 0;
+  for (int l = 0; l < p.n_linears; ++l) row_tiles += (p.lin[l].d_out + 15) / 16;
+  return row_tiles * p.n_chunks * (4096.0 + (double)p.n_act * code_block_bytes(p.bits)) / 5e6;
+}
+
+// The one-launch path for a token group of one or two tiles (mes_few.hip): whether the kernel can take the group, the
+// time it is expected to need, the launch.
 bool few_tokens_fits(const LinearParams& p);
+double few_tokens_us(const LinearParams& p);
 hipError_t launch_few_tokens(const LinearParams& p, hipStream_t s);
 
 }  // namespace mes

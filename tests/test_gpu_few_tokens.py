@@ -1,6 +1,8 @@
 """Calls of up to 32 tokens, around every edge of the one-launch path's dispatch: tokens per tile, experts per register
 set, wavefronts per row tile (row counts), chunks per wavefront, salient pairs.  Bars as for the streaming path: exact
 products, fp32 sums, one rounding."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -37,11 +39,13 @@ def test_tokens_and_experts(tokens, experts, bits, grid):
     (1032, 20, 5, 2, 8, 3),          # a ninth chunk of eight columns; 8 chunks per wavefront at most
     (4096, 2064, 4, 1, 64, 2),       # 129 row tiles: half a round of teams of eight
     (256, 8208, 16, 3, 40, 1),       # 513 row tiles: teams of four
-    (136, 16416, 7, 7, 5, 2),        # 1026 row tiles: teams of two or one
+    (136, 16416, 7, 7, 5, 2),        # 1026 row tiles, seven experts: the streaming path
+    (136, 16416, 5, 3, 5, 2),        # ... three: teams of one
     (640, 80, 16, 16, 128, 2),       # 64 salient pairs, all there is room for
     (640, 80, 16, 16, 129, 2),       # 80: the streaming path
-    (8320, 512, 9, 2, 64, 4),        # 65 chunks on 32 row tiles: the streaming path
-    (8320, 1024, 9, 2, 64, 4),       # ... on 64: nine chunks for the first wavefront
+    (8320, 512, 9, 2, 64, 4),        # 65 chunks: nine for the first wavefront
+    (8320, 1024, 9, 2, 64, 4),
+    (11144, 332, 2, 2, 8, 2),        # 88 chunks on 21 row tiles: the streaming path
     (2560, 512, 20, 2, 64, 2),       # two token tiles, three chunks
     (4608, 512, 20, 2, 64, 2),       # two token tiles, five chunks: the streaming path
 ])
@@ -125,3 +129,48 @@ def test_more_experts_than_a_token_group_holds(tokens, experts, bits):
     for run in runs[1:]:
         assert all(torch.equal(a, b) for a, b in zip(run, runs[0]))
     assert torch.equal(y, runs[0][0])
+
+
+def blank_expert(d_in, d_out, k, bits):
+    """A packed delta of zeros: right sizes, no numbers (for calls that are recorded and not run)."""
+    def zeros(n, dtype=torch.uint8):
+        return torch.zeros(n, dtype=dtype, device=DEV)
+    lib = mes.binding.lib
+    return mes.PackedDelta(d_in, d_out, k, bits, 0, zeros(lib.mes_codes_bytes(d_in, d_out, bits)), zeros(d_out, torch.float32),
+                           zeros(lib.mes_salient_bytes(d_out, k)), torch.arange(k, dtype=torch.int32, device=DEV))
+
+
+@pytest.mark.parametrize("d_in,d_outs,gated,counts,bits,k,one_launch", [
+    # measured us per call, streaming path / one launch
+    (4096, [4096], False, [1], 2, 64, True),                        # 22.8 / 14.1
+    (4096, [4096], False, [1] * 16, 2, 64, True),                   # 42.8 / 34.4
+    (1024, [1024], False, [1], 2, 64, True),                        # 17.4 / 8.6
+    (14336, [4096], False, [1], 2, 64, True),                       # 42.0 / 31.7
+    (4096, [14336, 14336], True, [1], 2, 64, True),                 # 67.7 / 56.4
+    (4096, [14336], False, [2] * 7 + [1] * 2, 3, 64, True),         # 94.9 / 78.8
+    (5120, [11008, 11008], True, [2] * 3, 1, 64, False),            # 70.3 / 83.0
+    (4096, [14336, 14336], True, [2] * 7 + [1] * 2, 1, 64, False),  # 88.5 / 96.3
+    (6152, [1112, 1112], True, [2, 2, 2, 1], 2, 64, False),         # 25.8 / 30.9
+    (14336, [5120], False, [2] + [1] * 8, 2, 33, False),            # 77.3 / 91.5
+    (6672, [2328, 5160, 10424], False, [4], 2, 64, False),          # 74.5 / 82.7
+    (4096, [4096], False, [1] * 24, 2, 64, True),                   # two groups: 64 / 56
+    (1024, [1024], False, [2] * 12 + [1] * 8, 2, 64, False),        # two groups, the first of two tiles: 34.6 / 41.3 mixed
+])
+def test_the_faster_path_is_taken(d_in, d_outs, gated, counts, bits, k, one_launch):
+    """The launches of a call (recorded in a graph that is never run): one per token group, or the streaming path's two or
+    three.  Lines are far from the rule's edge."""
+    layers = [(torch.zeros(mes.binding.base_bytes(d_in, d) // 2, dtype=torch.bfloat16, device=DEV),
+               [blank_expert(d_in, d, k, bits) for _ in counts]) for d in d_outs]
+    seg = [sum(counts[:e]) for e in range(len(counts) + 1)]
+    x = torch.zeros((seg[-1], d_in), dtype=torch.bfloat16, device=DEV)
+    ys = [torch.empty((seg[-1], d), dtype=torch.bfloat16, device=DEV) for d in d_outs]
+    call = mes.DeltaLinearGated(*layers[0], *layers[1], max_tokens=256) if gated else mes.DeltaLinearMulti(layers, max_tokens=256)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call(x, seg, ys[0] if gated else ys)
+    n = ctypes.c_size_t()
+    get_nodes = mes.binding.lib.hipGraphGetNodes      # (of the HIP runtime that the library is linked to)
+    get_nodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    assert get_nodes(graph.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    groups = -(-len(counts) // 16)
+    assert (n.value == groups) if one_launch else (2 <= n.value <= 3)
