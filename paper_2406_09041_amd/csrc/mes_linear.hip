@@ -812,14 +812,24 @@ void launch_tt(const LaunchParams& mp, int tt, int grid, hipStream_t s) {
   else k_delta_linear<BITS, 4, NW, NA><<<grid, 64 * NW, 0, s>>>(mp);
 }
 
-// na: the body all groups take, or how they differ (built for four token tiles only: fewer are a special case of it)
+// na: the body all groups take, or how they differ.  Mixed launches are built for four token tiles (fewer are a special case
+// of it), those of the full body at 3 and 4 bits also for one and two: a call of nearly as many experts as tokens is cut into
+// small groups of 16 experts (two sweeps of 8) and one of the experts left (4096 x 5288, 3 bits, 31 tokens of 26 experts: 54.8 us
+// in the four-tile kernel, two sweeps for all of them 46.3).
 template <int BITS, int NW>
 void launch_na(const LaunchParams& mp, int tt, int na, int grid, hipStream_t s) {
-  if (na == kMixShort) k_delta_linear<BITS, 4, NW, kMixShort><<<grid, 64 * NW, 0, s>>>(mp);
-  else if (na == kMixFull) k_delta_linear<BITS, 4, NW, kMixFull><<<grid, 64 * NW, 0, s>>>(mp);
-  else if (na == 4) launch_tt<BITS, NW, 4>(mp, tt, grid, s);
-  else if (na == 8) launch_tt<BITS, NW, 8>(mp, tt, grid, s);
-  else launch_tt<BITS, NW, full_slots(BITS)>(mp, tt, grid, s);
+  if (na == kMixShort) {
+    k_delta_linear<BITS, 4, NW, kMixShort><<<grid, 64 * NW, 0, s>>>(mp);
+  } else if (na == kMixFull) {
+    if constexpr (BITS >= 3) launch_tt<BITS, NW, kMixFull>(mp, tt, grid, s);
+    else k_delta_linear<BITS, 4, NW, kMixFull><<<grid, 64 * NW, 0, s>>>(mp);
+  } else if (na == 4) {
+    launch_tt<BITS, NW, 4>(mp, tt, grid, s);
+  } else if (na == 8) {
+    launch_tt<BITS, NW, 8>(mp, tt, grid, s);
+  } else {
+    launch_tt<BITS, NW, full_slots(BITS)>(mp, tt, grid, s);
+  }
 }
 
 template <int BITS>
@@ -925,11 +935,13 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
     for (int g = ng; g < kMaxGroups; ++g) mp.g[g] = mp.g[0];   // never selected
     mp.n_groups = ng;
     bool same = true, full = false;
-    for (int g = 0; g < ng; ++g) {
-      same = same && pass_slots(d0.bits, mp.g[g].n_act) == pass_slots(d0.bits, mp.g[0].n_act);
-      full = full || pass_slots(d0.bits, mp.g[g].n_act) > 8;
-    }
-    const int na = same ? pass_slots(d0.bits, mp.g[0].n_act) : full ? kMixFull : kMixShort;
+    for (int g = 0; g < ng; ++g) full = full || pass_slots(d0.bits, mp.g[g].n_act) > 8;
+    auto body = [&](int g) {   // (see kMixFull: at 1 and 2 bits 5 to 8 experts take the full body if a group of the launch does)
+      const int na = pass_slots(d0.bits, mp.g[g].n_act);
+      return full && d0.bits <= 2 && na == 8 ? full_slots(d0.bits) : na;
+    };
+    for (int g = 1; g < ng; ++g) same = same && body(g) == body(0);
+    const int na = same ? body(0) : full ? kMixFull : kMixShort;
     mp.n_first = n_first > 0 ? n_first : ng;
     mp.wg_per_group = mp.rg8 * 8 * pl.nsplit;
     hipError_t e;

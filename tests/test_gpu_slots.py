@@ -4,7 +4,8 @@ import pytest
 import torch
 
 from inputs import synth
-from test_gpu_parity import run_case
+from oracle import mes_oracle as O
+from test_gpu_parity import check_rows, oracle_experts, run_case
 
 pytestmark = pytest.mark.gpu
 mes = pytest.importorskip("paper_2406_09041_amd")
@@ -37,3 +38,21 @@ def test_groups_with_different_bodies_in_one_launch(bits, counts):
     y1 = mes.mes_delta_linear(w_t, ge, wl.x, wl.seg_offsets, workspace=mes.make_workspace(wl.d_in, wl.d_out, 64, torch.device(DEV)))
     assert torch.equal(y, y1)
     run_case(synth.small_case(1160, 328, offsets(counts), 24, bits, seed=5))
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("counts", [[1] * 41, [1] * 42, [1] * 40, [2] * 16 + [1] * 13, [2] * 16 + [1] * 10, [2] * 16 + [1] * 7, [1] * 32 + [7, 2]])
+def test_small_groups_with_different_bodies_in_one_launch(counts, bits):
+    """Nearly as many experts as tokens: groups of 16 experts and one or two token tiles, the experts left in one more group.
+    One launch for all of them gives bit for bit what a launch per group does, and the oracle's bars hold."""
+    wl = synth.small_case(1160, 328, offsets(counts), 24, bits, seed=6, device=DEV)
+    w_t = mes.mes_pack_base(wl.w_base)
+    ge = [mes.mes_pack_delta(ex.delta, ex.salient_idx, bits) for ex in wl.experts]
+    ys = []
+    for room in (64, 256):
+        y = torch.full((wl.x.shape[0], wl.d_out), float("nan"), dtype=torch.bfloat16, device=DEV)
+        ys.append(mes.DeltaLinear(w_t, ge, max_tokens=room)(wl.x, wl.seg_offsets, y))
+    assert torch.equal(ys[0], ys[1])
+    oe = oracle_experts(wl)
+    w64 = wl.w_base.double().cpu().numpy()
+    check_rows(wl, ys[1], O.delta_linear(wl.x.double().cpu().numpy(), w64, oe, wl.seg_offsets), oe, w64)
