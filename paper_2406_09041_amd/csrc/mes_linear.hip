@@ -766,17 +766,19 @@ Plan plan_for(int d_in, const int* d_out, int n_linears, bool pair) {
   return best;
 }
 
-// Expected time of one token group of few tokens on the streaming path, us (for the choice between the two paths; see
-// few_tokens_us for the calls the numbers come from; 8 % off on those not used for them).  Workgroup ids go round-robin to
-// 8 XCDs of 32 compute units and a row group's id names its XCD, so the fullest XCD counts the rounds (81 row groups x 3
-// splits are 243 workgroups, and 33 on the first XCD: two rounds).  Salient pairs that the chunks cannot carry are
-// multiplied one after the other.
-double streaming_us(const LinearParams& p, const Plan& pl, int rgs) {
-  const int rounds = ((rgs + 7) / 8 * pl.nsplit + 31) / 32, chunks = (p.n_chunks + pl.nsplit - 1) / pl.nsplit;
-  const int sweeps = p.n_act > full_slots(p.bits) ? 2 : 1;
-  const int left = (p.n_vis * p.n_sb + pl.nsplit - 1) / pl.nsplit - chunks * sweeps;
-  return 4.5 + (pl.nsplit > 1 ? 4.9 : 0.0) + 0.51 * weights_us(p) +
-         rounds * (5.4 + chunks * (0.64 + 0.10 * p.n_act + (sweeps > 1 ? 0.97 : 0.0)) + (left > 0 ? 0.62 * left : 0.0));
+// Expected time of a token group of few tokens, or of two in one launch, on the streaming path, us (for the choice between
+// the two paths; see few_tokens_us for the calls the numbers come from; 8 % off on those not used for them, two groups 13 %,
+// 9 % of it too low).  Workgroup ids go round-robin to 8 XCDs of 32 compute units and a row group's id names its XCD, so the
+// fullest XCD counts the rounds (81 row groups x 3 splits are 243 workgroups, and 33 on the first XCD: two rounds).  Salient
+// pairs that the chunks cannot carry are multiplied one after the other.
+double streaming_us(const LinearParams& a, const LinearParams* b, const Plan& pl, int rgs) {
+  const int groups = b ? 2 : 1, rounds = (groups * ((rgs + 7) / 8) * pl.nsplit + 31) / 32;
+  const int chunks = (a.n_chunks + pl.nsplit - 1) / pl.nsplit;
+  auto sweeps = [](const LinearParams& p) { return p.n_act > full_slots(p.bits) ? 2 : 1; };
+  const int left = (a.n_vis * a.n_sb + pl.nsplit - 1) / pl.nsplit - chunks * sweeps(a);
+  const double experts = b ? 0.5 * (a.n_act + b->n_act) : a.n_act, extra = (b ? 0.5 * (sweeps(a) + sweeps(*b)) : sweeps(a)) - 1.0;
+  return 4.5 + (pl.nsplit > 1 ? 4.9 : 0.0) + 0.51 * (weights_us(a) + (b ? weights_us(*b) : 0.0)) +
+         rounds * (5.4 + chunks * (0.64 + 0.10 * experts + 0.97 * extra) + (left > 0 ? 0.62 * left : 0.0));
 }
 
 // The workspace of one token group; a launch of n groups uses n of these, one after the other.
@@ -1042,9 +1044,22 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
         //     against 83.0) or have many experts on many rows (4096 -> 14336, 1 bit, 9 experts 88.5 against 96.3), long columns
         //     (14336 -> 5120, 9 experts 77.3 against 91.5), most groups of two tiles on more than 4 chunks per wavefront.
         // Over 3077 calls the choice costs 0.3 % against the better of the two.  (Equal expectations: the streaming path.)
-        // A call of few tokens is two groups if more than kMaxSlots experts own them; both take the first one's path, and
-        // the workspace has no say in it.
-        if (p.t0 == 0) few = c.T <= 32 && few_tokens_fits(p) && few_tokens_us(p) < 0.97 * streaming_us(p, pl, rgs);
+        // A call of few tokens is two groups if more than kMaxSlots experts own them.  Where one launch can take the first, that
+        // has a token of each of its experts, and the second is one tile too.  Both take the same path, one launch each or
+        // one streaming launch with both, whatever the workspace has room for.  (1024 x 1024, 2 bits, 32 tokens of as many
+        // experts: 32.4 us streaming against 33.6; 4096 x 4096, 24 of 24: 63.0 against 55.9.  900 such calls: 0.88 of the
+        // streaming path's time, 14 of them more than 3 % slower, 19 % at worst.)
+        if (p.t0 == 0 && c.T <= 32 && few_tokens_fits(p)) {
+          if (nt == c.T) {
+            few = few_tokens_us(p) < 0.97 * streaming_us(p, nullptr, pl, rgs);
+          } else {
+            LinearParams second = p;
+            second.n_act = -na;
+            for (int e = 0; e < c.n_experts; ++e) second.n_act += c.seg[e + 1] > c.seg[e] ? 1 : 0;
+            second.n_vis = d0.k > 0 ? second.n_act : 0;
+            few = few_tokens_us(p) + few_tokens_us(second) < streaming_us(p, &second, pl, rgs);
+          }
+        }
         if (few && few_tokens_fits(p)) {
           hipError_t e;
           if (c.ev_start && first_kernel && (e = hipEventRecord(c.ev_start, s)) != hipSuccess) return e;

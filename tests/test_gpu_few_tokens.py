@@ -153,7 +153,9 @@ def blank_expert(d_in, d_out, k, bits):
     (6152, [1112, 1112], True, [2, 2, 2, 1], 2, 64, False),         # 25.8 / 30.9
     (14336, [5120], False, [2] + [1] * 8, 2, 33, False),            # 77.3 / 91.5
     (6672, [2328, 5160, 10424], False, [4], 2, 64, False),          # 74.5 / 82.7
-    (4096, [4096], False, [1] * 24, 2, 64, True),                   # two groups: 64 / 56
+    (4096, [4096], False, [1] * 24, 2, 64, True),                   # two groups: 63.0 / 55.9
+    (2048, [1024, 1024], True, [1] * 21, 2, 64, False),             # two groups: 30.6 / 51.2
+    (4832, [444], False, [1] * 25, 2, 8, False),                    # two groups: 33 / 41
     (1024, [1024], False, [2] * 12 + [1] * 8, 2, 64, False),        # two groups, the first of two tiles: 34.6 / 41.3 mixed
 ])
 def test_the_faster_path_is_taken(d_in, d_outs, gated, counts, bits, k, one_launch):
