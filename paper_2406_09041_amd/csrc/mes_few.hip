@@ -39,6 +39,13 @@ __device__ __forceinline__ CodeRegs<BITS> ld_codes(const char* blk, int lane) {
   return r;
 }
 
+// Numbers pass between the lanes of one wavefront through LDS without a barrier.  The hardware keeps a wavefront's LDS
+// accesses in order; this has the compiler keep them in order too (no instruction, no wait).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
 constexpr int kFewWaves = 8;    // per workgroup
 constexpr int kFewPairs = 64;   // salient pairs a launch takes (half of them for each layer of a gated pair)
 
@@ -158,6 +165,7 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
       m = max(m, (uint32_t)__shfl_xor((int)m, 16));         // the token's four lanes
       m = max(m, (uint32_t)__shfl_xor((int)m, 32));
       const int s = chunk_exponent(__uint_as_float(m << 16));
+      wave_lds_fence();                                     // the other lanes have read the last chunk's pieces
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
         float xv[8];
@@ -178,6 +186,7 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
       }
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) acc_base[tt] = mfma_bf16(b.w[kb], b.x[tt][kb], acc_base[tt]);
+      wave_lds_fence();                                     // ... and written this one's
       v8i piece[2];
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
