@@ -106,9 +106,11 @@ size_t mes_codes_bytes(int d_in, int d_out, int bits);   /* packed low-bit codes
 size_t mes_salient_bytes(int d_out, int k);              /* tiled fp16 salient columns          */
 size_t mes_pack_workspace_bytes(void);
 size_t mes_select_workspace_bytes(int n, int d_in, int d_out);
-/* Workspace of mes_delta_linear / _multi.  Tokens are streamed in groups of 64 and one launch serves as many groups
- * as the workspace has slices for: one slice for max_tokens <= 64, two for <= 128, four above that (a slice: the
- * group's prepared activations, gathered salient activations and split-column partial sums).  A larger workspace
+/* Workspace of mes_delta_linear / _multi.  Tokens are streamed in groups of up to 64 of at most 16 experts, and one
+ * launch serves as many groups as the workspace has slices for: one slice for max_tokens <= 64, two for <= 128, four
+ * above that (a slice: the group's prepared activations, gathered salient activations and split-column partial sums).
+ * Calls of up to 32 tokens may take one launch per group that needs no scratch (the slice is asked for all the same);
+ * which of the two is expected to be faster decides, from the call alone.  A larger workspace
  * than a call needs is fine; a smaller one (at least one slice) is accepted and costs launches, not correctness.
  * Asked for with max_tokens >= 192 it also includes room for the long-segment
  * path (the segment's activations re-tiled, about 4 d_in bytes per token, and up to 64 MiB of partial sums): an
@@ -174,8 +176,8 @@ mes_status mes_delta_linear(const void* w_base_tiled, const mes_delta* experts, 
                             void* workspace, size_t workspace_bytes, void* stream);
 
 /* The same hot path for several linear layers that read the SAME activations and routing (Eq. 4 applied to
- * each layer; e.g. the query / key / value projections, or the gate / up projections, of one block): one
- * preparation of x and one streaming launch serve all of them, y_l[t] = x[t] (W_l + Delta~_{l,e})^T.
+ * each layer; e.g. the query / key / value projections, or the gate / up projections, of one block): the launches of
+ * a call serve all of them together, y_l[t] = x[t] (W_l + Delta~_{l,e})^T.
  * linears: HOST array [n_linears], 1 <= n_linears <= MES_MAX_FUSED.  Every layer has its own base, its own
  * n_experts expert deltas (with their own salient channels) and its own output; d_out may differ between
  * layers, d_in, k, bits and grid must be the same for all layers and experts.

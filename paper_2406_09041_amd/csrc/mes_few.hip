@@ -1,9 +1,9 @@
 // The serving hot path for a handful of tokens (Eq. 4, as in mes_linear.hip) in ONE launch: no preparation of the
 // activations before it, no reduction of split columns after it.
 //
-// A call of one decoded token moves 40 MB through a 4096 x 4096 layer, 8 us at the rate of a large copy; the
-// three launches of the streaming path, each with its own start-up, took 22 us for it; this one takes 14.  With one 16-token tile the
-// activations are so few that every workgroup can afford to prepare them for itself:
+// A call of one decoded token moves 38 MB through a 4096 x 4096 layer, 8 us at the rate of a large copy; the
+// three launches of the streaming path, each with its own start-up, took 22 us for it; this one takes 13.4.  With one or two
+// 16-token tiles the activations are so few that every workgroup can afford to prepare them for itself:
 //   - a workgroup owns 16 output channels (of two layers if they are a gated pair) and ALL the columns; its wavefronts
 //     deal the 128-column chunks among themselves, each with its own accumulators, and meet in LDS at the end, where
 //     the sums are added in wavefront order: the result does not depend on timing;

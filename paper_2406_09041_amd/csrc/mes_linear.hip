@@ -184,15 +184,19 @@ __device__ __forceinline__ void stage_barrier() {
 
 // Expert slots one sweep over the chunks handles, by the number of experts that own tokens of the group.  Their code
 // words for one chunk pass through registers and are parked in LDS, used or not, so groups of few experts take smaller
-// bodies.  The largest body: 16 slots (all a group may have) at 1 and 2 bits; at 3 bits the registers hold 13, at 4 the
-// LDS 10 (8 wavefronts x slots x 256 b bytes next to the two activation stages).  Groups of more experts than that take two
+// bodies.  The largest body: 16 slots (all a group may have) at 1 and 2 bits; at 3 bits the registers hold 13 (14 spill 9 or
+// 10 of them; with 13 the workgroups of 6 wavefronts put one or two aside before the loop and take them back behind it), at 4
+// the LDS 10 (8 wavefronts x slots x 256 b bytes next to the two activation stages).  Groups of more experts than that take two
 // sweeps of 8, the cheaper split.  4096 rows x 14336 columns, 64 tokens, us per call:
 //   3 bits, 13 experts: 100 in one sweep of 13, 118 in two of 8; 16 experts: 134 in sweeps of 13 and 3, 125 in two of 8;
 //   4 bits, 10 experts: 97 against 118; 13 experts: 132 against 128;  2 bits, 6 experts: 61 with 8 slots, 63 with 16.
 constexpr int full_slots(int bits) { return bits <= 2 ? 16 : bits == 3 ? 13 : 10; }
 constexpr int pass_slots(int bits, int n_act) { return n_act <= 4 ? 4 : n_act <= 8 || n_act > full_slots(bits) ? 8 : full_slots(bits); }
 // Register buffers for code words in flight: two, requested two chunks ahead; the largest bodies at 3 and 4 bits have
-// registers for one, requested one chunk ahead.  (Their chunks take long enough for the words to arrive.)
+// registers for one, requested one chunk ahead.  Their chunks take long enough for the words to arrive, also from memory
+// that was just written: two sweeps of 8 against this on experts copied in from host memory right before the call, 14336 ->
+// 4096 at 3 bits with 13 experts 133 against 115 us (in turn with other experts, no copy: 119 against 103), at 4 bits with 10
+// 133 against 109 (121 against 98), 5128 -> 3204 at 3 bits with 13, 6 wavefronts, 107 against 87 (93 against 75).
 constexpr int code_buffers(int bits, int na) { return bits >= 3 && na > 8 ? 1 : 2; }
 
 // Per-wavefront state of the streaming loop.

@@ -424,7 +424,7 @@ __global__ __launch_bounds__(1024) void k_scores(const float* __restrict__ delta
                                                  int* __restrict__ rank) {
   const int strips = (d_in + 15) / 16, per_xcd = (strips + 7) / 8;
   const int strip = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= per_xcd || strip >= strips) return;
+  if (strip >= strips) return;                             // (the strips are dealt to the 8 XCDs evenly)
   const int tid = threadIdx.x, rl = tid >> 2, c = 16 * strip + 4 * (tid & 3);
   const bool in = c < d_in;                                // d_in % 8 == 0
   double err[4] = {0, 0, 0, 0}, xs[4] = {0, 0, 0, 0};
