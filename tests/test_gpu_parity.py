@@ -148,7 +148,11 @@ def run_case(wl, grid=0, policy=1):
     for p, o in zip(ge, oe):
         check_pack(p, o, wl.d_out, wl.d_in, wl.k, wl.bits)
     y = mes.mes_delta_linear(w_t, ge, wl.x.to(DEV), wl.seg_offsets)
+    # ... and in a workspace for a larger batch than this one: every element written, the same bits
+    roomy = torch.full_like(y, float("nan"))
+    mes.DeltaLinear(w_t, ge, max_tokens=max(256, 2 * y.shape[0]))(wl.x.to(DEV), wl.seg_offsets, roomy)
     torch.cuda.synchronize()
+    assert torch.equal(roomy, y), (wl.d_in, wl.d_out, wl.bits, grid, wl.seg_offsets)
     w64 = wl.w_base.double().numpy()
     y_ref = O.delta_linear(wl.x.double().numpy(), w64, oe, wl.seg_offsets)
     check_rows(wl, y, y_ref, oe, w64, what=(wl.d_in, wl.d_out, wl.bits, grid, wl.seg_offsets))
@@ -307,7 +311,7 @@ def test_config4_sampled_rows_at_full_size():
 @pytest.mark.parametrize("bits", [1, 2, 3, 4])
 def test_more_experts_than_one_pass_holds(bits):
     """40 experts, most with one or two tokens, in one 64-token batch: the token group has to be cut where the
-    kernel's expert slots run out (16, 10 at 3 bits, 8 at 4 bits), with empty experts sprinkled in."""
+    kernel's expert slots run out (16; at 3 and 4 bits in two sweeps), with empty experts sprinkled in."""
     seg = [0]
     for e in range(40):
         seg.append(seg[-1] + (1, 2, 0, 1, 3, 1, 2, 1)[e % 8])      # 55 tokens, 35 experts with tokens
