@@ -820,7 +820,7 @@ void launch_tt(const LaunchParams& mp, int tt, int grid, hipStream_t s) {
 
 // na: the body all groups take, or how they differ.  Mixed launches are built for four token tiles (fewer are a special case
 // of it), those of the full body at 3 and 4 bits also for one and two: a call of nearly as many experts as tokens is cut into
-// small groups of 16 experts (two sweeps of 8) and one of the experts left (4096 x 5288, 3 bits, 31 tokens of 26 experts: 54.8 us
+// small groups of 16 experts (two sweeps of 8) and one of the experts left (896 x 5288, 3 bits, 31 tokens of 26 experts: 54.8 us
 // in the four-tile kernel, two sweeps for all of them 46.3).
 template <int BITS, int NW>
 void launch_na(const LaunchParams& mp, int tt, int na, int grid, hipStream_t s) {
