@@ -7,6 +7,8 @@
 // over the gathered salient activations, adds bf16(Delta_S + z s) (Delta_S: the stored fp16 values).
 // The rounding of the operands to bf16 adds a relative error of about 2^-9 / sqrt(3) to y, the same size as the
 // rounding of y itself.
+#include <type_traits>
+
 #include "mes_internal.h"
 
 namespace mes {
@@ -19,30 +21,53 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 
-constexpr int kMaxWorkgroups = 256;  // one workgroup per compute unit; fewer row groups than that split the contraction
+constexpr int kMaxWorkgroups = 256;  // one workgroup per compute unit; launches of fewer split the contraction
 
 constexpr int kMaxSegs = 8;          // long segments (experts) served by one launch
+constexpr int kMaxBlocks = 128;      // token blocks of one launch
+constexpr int kBlockTiles = 32;      // token tiles (16 tokens) of a full block
+constexpr int kWaves = 8;
 
-struct PrefillParams {
+// Per layer of a call; per segment (= per expert with a long segment): codes, step, sal.
+struct PrefillLinear {
   const u32x4* base;        // tiled base weight: block (chunk c, row tile jt) = [4 k blocks][64 lanes] x 16 bytes
-  // per segment (= per expert with a long segment), n_seg of them:
+  uint16_t* y;              // bf16 [T, d_out]
   const uint32_t* codes[kMaxSegs];   // packed codes: block (c, jt) = 64 * bits words
   const float* step[kMaxSegs];       // [d_out]
   const u32x4* sal[kMaxSegs];        // salient tile: ((jt * n_sb + sb) * 64 + lane) x 8 fp16
-  int t_begin[kMaxSegs], t_end[kMaxSegs];   // the segment's rows of x and y
-  int tb0[kMaxSegs + 1];             // its first token block (of 256 tokens) in xt; tb0[n_seg] = all blocks
-  // The launch's order of the blocks: all the full ones, segment by segment (fb0: where a segment's start), then the
-  // segments' last, partial ones, which take less time and fill the compute units behind the others.
-  int fb0[kMaxSegs + 1];
-  int n_full, tail_seg[kMaxSegs];
-  int n_seg;
+  int d_out, n_jt;
+  int rg_begin, rg_end;     // its row groups among the launch's
+};
+
+struct PrefillParams {
+  PrefillLinear lin[MES_MAX_FUSED];
+  int t_begin[kMaxSegs], t_end[kMaxSegs];   // a segment's rows of x and y
+  int tile0[kMaxSegs];                      // its first token tile in xt
+  uint32_t blocks[kMaxBlocks];              // token blocks, the longest first: see token_block()
   const u32x4* xt;          // the segments' activations in fragment order: [k block][token tile][64 lanes] x 16 bytes,
-                            // k blocks 0 .. 4 n_chunks - 1 the input channels, then 4 n_ssteps blocks of gathered salient ones
-  uint16_t* y;              // bf16 [T, d_out]
-  f32x4* tiles;             // split contraction only: accumulator tiles, [split][row group][token block][16 tiles][thread]
-  int d_out, n_jt, n_chunks, n_sb, n_ssteps, n_tq, steps_per_split, n_split;
+                            // k blocks 0 .. 4 n_chunks - 1 the input channels, then 4 n_ssteps per layer of gathered salient ones
+  f32x4* tiles;             // split contraction only: accumulator tiles, [split][row group][token block][4 RT][thread]
+  int n_linears, n_rg, n_blk, n_chunks, n_sb, n_ssteps, n_tq, steps_per_split, n_split;
   float z;
 };
+
+// A token block: its segment, its first token tile (in xt) and how many it has.
+struct TokenBlock { int sg, tile0, tiles; };
+inline uint32_t pack_block(int sg, int tile0, int tiles) { return (uint32_t)sg | (uint32_t)tiles << 3 | (uint32_t)tile0 << 9; }
+__device__ __forceinline__ TokenBlock token_block(const PrefillParams& p, int b) {
+  const uint32_t v = p.blocks[b];
+  return TokenBlock{(int)(v & 7), (int)(v >> 9), (int)((v >> 3) & 63)};
+}
+// Token tiles a wavefront takes of a block: of up to 16 tiles four columns of wavefronts share the tokens, and the two of a
+// column the k blocks; of more, eight.
+__host__ __device__ constexpr int wave_tiles(int tiles) { return tiles > 24 ? 4 : tiles > 16 ? 3 : (tiles + 3) / 4; }
+
+__device__ __forceinline__ int linear_of(const PrefillParams& p, int rg) {
+  int l = 0;
+#pragma unroll
+  for (int i = 0; i + 1 < MES_MAX_FUSED; ++i) l += (i + 1 < p.n_linears && rg >= p.lin[i].rg_end) ? 1 : 0;
+  return l;
+}
 
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   const bf16x2 h = __builtin_convertvector(f32x2{a, b}, bf16x2);   // round to nearest even
@@ -55,179 +80,360 @@ __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
 }
 
 // The barrier between two steps: waits for this wavefront's LDS traffic only.  (__syncthreads() would also wait for
-// the memory loads in flight: the weights a builder has just requested for a later step, the activation copies a
-// multiplier keeps ahead of itself -- a full memory round trip per step.)
+// the memory loads in flight: weights and activations of later steps, a full memory round trip per step.)
 __device__ __forceinline__ void step_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Loads as (wave-uniform address) + (32-bit lane offset).
+typedef __attribute__((address_space(1))) const char global_char;
+__device__ __forceinline__ u32x4 load128(uint64_t uniform, uint32_t off) {
+  return *reinterpret_cast<__attribute__((address_space(1))) const u32x4*>(reinterpret_cast<global_char*>(uniform) + off);
+}
+__device__ __forceinline__ uint32_t load32(uint64_t uniform, uint32_t off) {
+  return *reinterpret_cast<__attribute__((address_space(1))) const uint32_t*>(reinterpret_cast<global_char*>(uniform) + off);
+}
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+}
+// A lane offset of this step: the compiler cannot widen it to 64 bits ahead of the loop, which would take the loads off the
+// scalar base + 32-bit offset form and cost vector arithmetic and registers.
+__device__ __forceinline__ uint32_t here(uint32_t v) { asm volatile("" : "+v"(v)); return v; }
 
 struct TileParams {
   const uint16_t* x;
-  const int32_t* sidx[kMaxSegs];
-  int t_begin[kMaxSegs], t_end[kMaxSegs], tb0[kMaxSegs + 1];
-  int n_seg, k, d_in, n_kb_main, n_tq;
-  int kb_begin;             // this launch writes the k blocks kb_begin .. kb_begin + n_blk / n_tq - 1
-  size_t n_blk;
+  const int32_t* sidx[MES_MAX_FUSED][kMaxSegs];
+  int t_begin[kMaxSegs], t_end[kMaxSegs], tile0[kMaxSegs];
+  int n_seg, k, d_in, n_chunks, n_ssteps, n_tq;
+  int u_begin, n_units;     // this launch writes the units u_begin .. u_begin + n_units - 1 (a unit: four k blocks, see below)
   u32x4* xt;
 };
 
-// The segments' rows of x -> fragment order.  Block (kbi, tq), lane l: token 16 tq' + (l & 15) of the segment that
-// token tile tq belongs to (tq' counted from the segment's first tile); for kbi < n_kb_main the 8 input channels
-// 32 kbi + 8 (l >> 4) .., else the 8 salient channels of that segment's expert with ranks
-// 32 (kbi - n_kb_main) + 8 (l >> 4) ..; zero beyond the segment's last token, the last channel or rank.
-__global__ void k_prefill_tile_x(const TileParams p) {
-  const int lane = threadIdx.x & 63;
-  const size_t blk = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (blk >= p.n_blk) return;
-  const int tq = (int)(blk % p.n_tq), kbi = p.kb_begin + (int)(blk / p.n_tq);
+// The segments' rows of x -> fragment order.  A wavefront writes one unit of one token tile tq: unit u < n_chunks are the k
+// blocks of input channels 128 u .. 128 u + 127, the units behind them, n_ssteps per layer, those of 128 of the layer's
+// salient channels.  Block (kb, tq), lane l: token 16 tq' + (l & 15) of the segment that tq belongs to (tq' counted from
+// the segment's first tile); the 8 input channels 32 kb + 8 (l >> 4) .., or the 8 salient channels of that segment's expert
+// with ranks 32 kb + 8 (l >> 4) ..; zero beyond the segment's last token, the last channel or rank.
+// Bound by memory latency: every lane has four loads in flight, 256 bytes of each of 16 rows per wavefront.
+__global__ __launch_bounds__(256) void k_prefill_tile_x(const TileParams p) {
+  const int lane = threadIdx.x & 63, g = lane >> 4;
+  const long w = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (w >= (long)p.n_units * p.n_tq) return;
+  const int tq = (int)(w / p.n_units), u = p.u_begin + (int)(w - (long)tq * p.n_units);
   int sg = 0;
-  while (sg + 1 < p.n_seg && tq >= 16 * p.tb0[sg + 1]) ++sg;
-  const int t = p.t_begin[sg] + 16 * (tq - 16 * p.tb0[sg]) + (lane & 15);
-  u32x4 v = {0, 0, 0, 0};
-  if (t < p.t_end[sg]) {
-    const uint16_t* row = p.x + (size_t)t * p.d_in;
-    if (kbi < p.n_kb_main) {
-      const int c = 32 * kbi + 8 * (lane >> 4);
-      if (c < p.d_in) v = *reinterpret_cast<const u32x4*>(row + c);
-    } else {
-      const int r0 = 32 * (kbi - p.n_kb_main) + 8 * (lane >> 4);
-      const int32_t* sidx = p.sidx[sg];
+#pragma unroll
+  for (int i = 1; i < kMaxSegs; ++i) sg += (i < p.n_seg && tq >= p.tile0[i]) ? 1 : 0;
+  const int t = p.t_begin[sg] + 16 * (tq - p.tile0[sg]) + (lane & 15);
+  const bool live = t < p.t_end[sg];
+  const uint16_t* row = p.x + (size_t)(live ? t : p.t_begin[sg]) * p.d_in;
+  u32x4 v[4];
+  if (u < p.n_chunks) {
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      const int c = 128 * u + 32 * kb + 8 * g;
+      v[kb] = u32x4{0, 0, 0, 0};
+      if (live && c < p.d_in) v[kb] = *reinterpret_cast<const u32x4*>(row + c);
+    }
+  } else {
+    const int l = (u - p.n_chunks) / p.n_ssteps, r_begin = 128 * (u - p.n_chunks - l * p.n_ssteps) + 8 * g;
+    const int32_t* sidx = p.sidx[l][sg];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      const int r0 = r_begin + 32 * kb;
       uint32_t h[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         h[q] = 0;
-        if (r0 + q < p.k) {
+        if (live && r0 + q < p.k) {
           const int c = sidx[r0 + q];
           if (c >= 0 && c < p.d_in) h[q] = row[c];   // a corrupt list can never address outside the row
         }
       }
-      v = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+      v[kb] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
     }
   }
-  p.xt[((size_t)kbi * p.n_tq + tq) * 64 + lane] = v;
-}
-
-// Token block y of the launch: its segment, its number in the segment and the token tiles that each of the 4 multipliers
-// takes (a last block of few tokens: fewer than 4).
-struct TokenBlock { int sg, blk, tiles; };
-__device__ __forceinline__ TokenBlock token_block(const PrefillParams& p, int y) {
-  TokenBlock b{0, 0, 4};
-  if (y < p.n_full) {
 #pragma unroll
-    for (int i = 1; i < kMaxSegs; ++i) b.sg += y >= p.fb0[i] ? 1 : 0;   // (one trip to the argument block, no chain of them)
-    b.blk = y - p.fb0[b.sg];
-  } else {
-    b.sg = p.tail_seg[y - p.n_full];
-    b.blk = p.fb0[b.sg + 1] - p.fb0[b.sg];
-    b.tiles = (p.t_end[b.sg] - p.t_begin[b.sg] - 256 * b.blk + 63) / 64;
-  }
-  return b;
+  for (int kb = 0; kb < 4; ++kb) p.xt[((size_t)(4 * u + kb) * p.n_tq + tq) * 64 + lane] = v[kb];
 }
 
-// What a builder keeps in flight for one step (128 input channels, or 128 salient ranks) of its row tile.
-template <int BITS>
+// What a wavefront keeps in flight of a later step's weights: its NOP of the step's 4 RT operands.
+template <int BITS, int NOP>
 struct StepData {
-  u32x4 w[4];                              // base fragments (main step) or 8 fp16 salient values (salient step), per k block
-  uint32_t lo[4], hi[BITS >= 3 ? 4 : 1];   // code words
+  u32x4 w[NOP];                                // base fragment (main step) or 8 fp16 salient values (salient step)
+  uint32_t lo[NOP], hi[BITS >= 3 ? NOP : 1];   // code words
 };
 
-constexpr int kRingDepth = 3;   // k blocks in a multiplier's LDS ring
-
-// A multiplier's work: all RT row tiles of every step (operands from LDS) with TT token tiles of its own, TT tiles from
-// token tile TT wave of the block.
-template <int RT, int NM, int TT>
-__device__ __forceinline__ void multiply_block(const PrefillParams& p, const TokenBlock& tb, u32x4 (&afrag)[2][RT][4][64],
-                                               u32x4 (*xring)[kRingDepth][4][64], int wave, int st0, int st1) {
-  constexpr int XD = kRingDepth;
-  constexpr bool kXDirect = RT <= 7;                     // activations straight into registers (RT = 8 has none to spare)
+// One workgroup's share of the launch: RT row tiles (16 output channels each) of row group rg of a layer x one token block,
+// the steps st0 .. st1 - 1.  A step is 128 input channels (or 128 salient ranks), 4 k blocks.  All eight wavefronts do both
+// halves of the work:
+//   multiply: every wavefront has token tiles of its own (TT of them) and takes all RT operands of its k blocks from LDS;
+//     activations come straight from memory, already in fragment order, XD - 1 k blocks ahead.  KS = 1: all 4 k blocks of a
+//     step, 8 x TT token tiles per workgroup.  KS = 2 (blocks of up to 16 tiles): wavefronts w and w + 4 share the token tiles
+//     and take two k blocks each; the sums meet in LDS at the end.  So both wavefronts of a SIMD multiply, whatever the block.
+//   build: wavefront w forms the operands (row tiles w / 4 + 2 i, k block w % 4) of the next step in the idle LDS buffer,
+//     bf16(W + (u - z) s) from a base fragment and a code word that were asked for a step before.  The vector instructions
+//     for it are dealt out between the matrix instructions.
+// Both wavefronts of a SIMD thereby have matrix instructions ready most of the time, and a weight is formed once per 512
+// tokens; a workgroup with builders and multipliers as roles of different wavefronts formed it once per 256, had one
+// multiplier per SIMD and lost that one's waits.
+template <int BITS, int RT, int TT, int KS>
+__device__ __forceinline__ void multiply_rows(const PrefillParams& p, const PrefillLinear& L, int l, const TokenBlock& tb, u32x4* lds,
+                                              int wave, int rg, int blk, int st0, int st1) {
+  constexpr int NOP = (4 * RT + kWaves - 1) / kWaves;
+  constexpr int NBW = 4 / KS;                            // k blocks of a step this wavefront multiplies
+  constexpr int OPB = NOP / NBW;                         // operands built under one of them
+  // sets of activation fragments: what the registers hold (512 of them per lane and SIMD, two wavefronts)
+  constexpr int XD = TT == 0 ? 1 : KS == 2 ? (TT <= 2 ? 4 : 2) : (RT == 7 && BITS <= 2 ? 4 : 3);
+  constexpr int U = NBW % XD == 0 ? 1 : (2 * NBW) % XD == 0 ? 2 : 3;   // steps until the sets come round
+  static_assert((U * NBW) % XD == 0, "the sets are named at compile time");
+  static_assert(NOP % NBW == 0, "every k block has the same number of operands to build");
+  constexpr int TA = TT > 0 ? TT : 1;
+  constexpr int kBuf = RT * 4 * 1024, kSpare = 2 * kBuf;
   const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
-  const int tq0 = 16 * (p.tb0[tb.sg] + tb.blk) + TT * wave;
-  f32x4 acc[RT][TT];
+  const int half = KS == 2 ? wave >> 2 : 0, col = KS == 2 ? wave & 3 : wave;
+  const uint32_t lane16 = (uint32_t)lane * 16u;
+  const int sg = tb.sg;
+  char* const ldsc = reinterpret_cast<char*>(lds);
+
+  // ---- weights
+  const int bkb = wave & 3, brt = wave >> 2;
+  const int n_jt = L.n_jt, n_sb = p.n_sb, n_chunks = p.n_chunks;
+  const float z = p.z;
+  uint32_t jt[NOP];
+  float s[NOP];
+#pragma unroll
+  for (int i = 0; i < NOP; ++i) {                        // stored matrices are padded to whole groups of 4 row tiles: a last
+    const int j = RT * (rg - L.rg_begin) + brt + 2 * i;  // group may repeat tiles (its rows are never stored)
+    jt[i] = j < n_jt ? j : n_jt - 1;
+    const int row = 16 * (int)jt[i] + n;
+    s[i] = L.step[sg][row < L.d_out ? row : L.d_out - 1];
+  }
+  // the code block's lane 16 kb + n owns columns 32 kb + 8 g + 0 .. 7 of row n
+  uint32_t wl = lane16, co = (BITS == 1 ? 16 * bkb + n : 2 * (16 * bkb + n) + (g >> 1)) * 4u;
+  uint32_t coh = BITS == 3 ? 512u + (16 * bkb + n) * 4u : 512u + co;
+  const uint64_t codes = reinterpret_cast<uint64_t>(L.codes[sg]);
+  const uint64_t base = reinterpret_cast<uint64_t>(L.base) + bkb * 1024;
+  const uint64_t sal = reinterpret_cast<uint64_t>(L.sal[sg]);
+  using SD = StepData<BITS, NOP>;
+  uint64_t w_at, c_at;                                   // where the weights of the step asked for next are
+  uint32_t w_mul;
+  auto aim = [&](int st) {
+    st = st < st1 ? st : st1 - 1;
+    const bool main_step = st < n_chunks;                // (a salient step re-reads code words it never uses)
+    const uint32_t c = main_step ? st : n_chunks - 1;
+    int sb = 4 * (st - n_chunks) + bkb;
+    sb = sb < n_sb ? sb : n_sb - 1;                      // past the last salient block: repeated, zeroed when built
+    c_at = uniform64(codes + (uint64_t)c * (uint32_t)(n_jt * 256 * BITS));
+    const uint64_t wm = base + (uint64_t)c * (uint32_t)n_jt * 4096, ws = sal + (uint64_t)(uint32_t)sb * 1024;
+    w_at = uniform64(main_step ? wm : ws);
+    w_mul = __builtin_amdgcn_readfirstlane(main_step ? 4096 : n_sb * 1024);
+  };
+  auto fetch = [&](SD& d, int i) {
+    d.w[i] = load128(w_at + (uint64_t)jt[i] * w_mul, wl);
+    const uint64_t cw = c_at + jt[i] * (256u * BITS);
+    d.lo[i] = load32(cw, co);
+    if constexpr (BITS >= 3) d.hi[i] = load32(cw, coh);
+  };
+  auto store_operand = [&](int i, int buf, const u32x4& v) {
+    const int rt = brt + 2 * i;                          // (odd RT: half of the wavefronts have one operand less, and put
+    const int at = 2 * i + 1 < RT || rt < RT ? buf * kBuf + (rt * 4 + bkb) * 1024 : kSpare;   // theirs where nobody reads)
+    *reinterpret_cast<u32x4*>(ldsc + at + lane16) = v;
+  };
+  // An operand's way from weights and codes to LDS, in parts of one to three vector instructions: 0 the code fields, 1 .. 16
+  // four parts for each pair of values, 17 the store, 18 the request for the same place's weights of the step after next.
+  constexpr int kParts = 19;
+  u32x4 out;
+  uint32_t c0, c1;
+  float nzs, v0, v1, w1;
+  auto fp4 = [](uint32_t v, int q) -> f32x2 {            // byte q's two code fields, u / 2 as fp4 numbers, times two
+    switch (q) {
+      case 0: return __builtin_bit_cast(f32x2, __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(v, 2.0f, 0));
+      case 1: return __builtin_bit_cast(f32x2, __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(v, 2.0f, 1));
+      case 2: return __builtin_bit_cast(f32x2, __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(v, 2.0f, 2));
+      default: return __builtin_bit_cast(f32x2, __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(v, 2.0f, 3));
+    }
+  };
+  auto build_part = [&](SD& d, int i, int part, int buf) {
+    if (part == 0) {
+      nzs = -(z * s[i]);
+      c0 = BITS == 1 ? (d.lo[i] >> g) & 0x11111111u : (d.lo[i] >> (2 * (g & 1))) & 0x33333333u;
+      if constexpr (BITS >= 3) {                         // whole codes, the even columns' in the bytes of c0, the odd ones' in c1
+        const uint32_t c = c0 | (BITS == 3 ? (d.hi[i] >> g) & 0x11111111u : (d.hi[i] >> (2 * (g & 1))) & 0x33333333u) << 2;
+        c0 = c & 0x0f0f0f0fu;
+        c1 = (c >> 4) & 0x0f0f0f0fu;
+      }
+    } else if (part <= 16) {
+      const int q = (part - 1) >> 2;
+      const uint32_t ww = d.w[i][q];
+      switch ((part - 1) & 3) {
+        case 0:
+          if constexpr (BITS >= 3) {
+            v0 = (float)((c0 >> (8 * q)) & 0xffu);
+            v1 = (float)((c1 >> (8 * q)) & 0xffu);
+          } else {
+            const f32x2 u = fp4(c0, q);
+            v0 = u[0]; v1 = u[1];
+          }
+          break;
+        case 1: v0 = __builtin_fmaf(v0, s[i], nzs); v1 = __builtin_fmaf(v1, s[i], nzs); break;   // (u - z) s
+        case 2: v0 = bf16_lo(ww) + v0; w1 = bf16_hi(ww); break;
+        default: out[q] = pack_bf16(v0, w1 + v1); break;
+      }
+    } else if (part == 17) {
+      store_operand(i, buf, out);
+    } else {
+      fetch(d, i);
+    }
+  };
+  auto build_any = [&](SD& d, int i, int st, int buf) {  // a whole operand of any step (past the last: repeated, never read)
+    st = st < st1 ? st : st1 - 1;
+    if (st < n_chunks) {
+#pragma unroll
+      for (int part = 0; part < 17; ++part) build_part(d, i, part, buf);
+    } else {
+      out = u32x4{0, 0, 0, 0};
+      if (4 * (st - n_chunks) + bkb < n_sb) {            // ranks past k hold 0 and meet activations that are 0
+        const float zs = z * s[i];
+        const f16x8 h = __builtin_bit_cast(f16x8, d.w[i]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[q] = pack_bf16((float)h[2 * q] + zs, (float)h[2 * q + 1] + zs);
+      }
+    }
+    store_operand(i, buf, out);
+  };
+
+  // ---- activations: this wavefront's k blocks one after the other, the last one repeated
+  const uint64_t x_stride = (uint64_t)p.n_tq * 1024;     // from a k block to the next
+  const uint64_t x_jump = (uint64_t)(4 * p.n_ssteps * l) * x_stride;   // over the other layers' salient channels
+  uint32_t toff[TA];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) {                      // tiles past the block's last one repeat it, and are not stored
+    const int t = TT * col + tt;
+    toff[tt] = __builtin_amdgcn_readfirstlane((uint32_t)(tb.tile0 + (t < tb.tiles ? t : tb.tiles - 1)) * 1024u);
+  }
+  u32x4 xb[XD][TA];
+  uint64_t x_at = uniform64(reinterpret_cast<uint64_t>(p.xt) + (uint64_t)(4 * st0 + NBW * half) * x_stride + (st0 >= n_chunks ? x_jump : 0));
+  int x_left = (st1 - st0) * NBW - 1, x_cross = (n_chunks - st0) * NBW;   // blocks behind the next one; until the salient ones
+  auto request_x = [&](int j, int set) {                 // j: the block's number among those of its step
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) xb[set][tt] = load128(x_at + toff[tt], wl);
+    const uint64_t by = (KS == 2 && j == NBW - 1 ? 3 * x_stride : x_stride) + (--x_cross == 0 ? x_jump : 0);
+    x_at += x_left > 0 ? by : 0;
+    --x_left;
+  };
+
+  f32x4 acc[RT][TA];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = f32x4{0, 0, 0, 0};
-  if constexpr (kXDirect) {
-    // two register sets filled by ordinary loads one k block ahead: no LDS traffic for the activations
-    const u32x4* xsrc = p.xt + (size_t)tq0 * 64 + lane;
-    const size_t x_stride = (size_t)p.n_tq * 64;        // 16-byte units between k blocks
-    const int kbg_last = 4 * st1 - 1;
-    u32x4 xb[2][TT];
-    auto request_x = [&](int kbg, int set) {
-      const u32x4* src = xsrc + (size_t)(kbg < kbg_last ? kbg : kbg_last) * x_stride;
+
+  SD sd;
+  {
+    SD s0;
+    aim(st0);
 #pragma unroll
-      for (int tt = 0; tt < TT; ++tt) xb[set][tt] = src[tt * 64];
-    };
-    request_x(4 * st0, 0);
-    __syncthreads();
-    for (int st = st0; st < st1; ++st) {
-      const int cur = st & 1;
-      u32x4 a[2];                                        // operands are read from LDS one row tile ahead of their use
-      a[0] = afrag[cur][0][0][lane];
+    for (int i = 0; i < NOP; ++i) fetch(s0, i);
+    aim(st0 + 1);
+    if constexpr (TT > 0) {
 #pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        request_x(4 * st + kb + 1, (kb + 1) & 1);
+      for (int j = 0; j < XD - 1 - NBW; ++j) request_x(j % NBW, j);
+    }
+    // in the loop's order, so that the loop's waits let the same loads stay in flight in its first round
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          constexpr int kNone = -1;
-          const int rn = rt < RT - 1 ? rt + 1 : 0, kn = rt < RT - 1 ? kb : (kb < 3 ? kb + 1 : kNone);
-          if (kn != kNone) a[(kb * RT + rt + 1) & 1] = afrag[cur][rn][kn][lane];
+    for (int b = 0; b < NBW; ++b) {
+      if constexpr (TT > 0)
+        if (b - NBW + XD - 1 >= 0) request_x((b + XD - 1) % NBW, b - NBW + XD - 1);
+#pragma unroll
+      for (int o = 0; o < OPB; ++o) fetch(sd, b * OPB + o);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < NOP; ++i) build_any(s0, i, st0, st0 & 1);
+  }
+  step_barrier();
+
+  // One step: multiplies the operands of step st, builds those of st + 1, asks for the weights of st + 2.  MAIN: step st + 1
+  // is one of the main steps.  u: the step's number modulo U.
+  auto step = [&](auto main_step, int u, int st) {
+    constexpr bool MAIN = decltype(main_step)::value;
+    aim(st + 2);
+    wl = here(wl); co = here(co);
+    if constexpr (BITS >= 3) coh = here(coh);
+    const int nbuf = (st + 1) & 1;
+    const char* cur = ldsc + (st & 1) * kBuf + (half * NBW) * 1024 + lane16;
+    auto a_at = [&](int b, int rt) { return *reinterpret_cast<const u32x4*>(cur + (rt * 4 + b) * 1024); };
+    u32x4 a[2];                                          // operands are read from LDS one row tile ahead of their use
+    if constexpr (TT > 0) a[0] = a_at(0, 0);
+#pragma unroll
+    for (int b = 0; b < NBW; ++b) {
+      if constexpr (TT > 0) request_x((b + XD - 1) % NBW, (u * NBW + b + XD - 1) % XD);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        if constexpr (TT > 0) {
+          const int at = b * RT + rt, next = at + 1;
+          if (next < NBW * RT) a[next & 1] = a_at(next / RT, next % RT);
           __builtin_amdgcn_sched_barrier(0);             // keep the read above ahead of the matrix instructions below
 #pragma unroll
-          for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma_bf16(a[(kb * RT + rt) & 1], xb[kb & 1][tt], acc[rt][tt]);
+          for (int tt = 0; tt < TT; ++tt) {
+            acc[rt][tt] = mfma_bf16(a[at & 1], xb[(u * NBW + b) % XD][tt], acc[rt][tt]);
+            if constexpr (MAIN) {
+              constexpr int P = OPB * kParts, M = RT * TT;
+              const int m = rt * TT + tt;
+#pragma unroll
+              for (int pp = P * m / M; pp < P * (m + 1) / M; ++pp) build_part(sd, b * OPB + pp / kParts, pp % kParts, nbuf);
+              __builtin_amdgcn_sched_barrier(0);         // and the parts where they were dealt to
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (MAIN) {
+          if (TT == 0 && rt == 0) {
+#pragma unroll
+            for (int pp = 0; pp < OPB * kParts; ++pp) build_part(sd, b * OPB + pp / kParts, pp % kParts, nbuf);
+          }
+        } else {
+#pragma unroll
+          for (int o = 0; o < OPB; ++o)
+            if (rt == 2 + 2 * o) {
+              build_any(sd, b * OPB + o, st + 1, nbuf);
+              fetch(sd, b * OPB + o);
+            }
         }
       }
-      step_barrier();
     }
-  } else {
-    const char* xbase = reinterpret_cast<const char*>(p.xt + (size_t)tq0 * 64);
-    const size_t x_stride = (size_t)p.n_tq * 1024;        // bytes between k blocks
-    const int kbg_last = 4 * st1 - 1;
-    auto request_x = [&](int kbg, int slot) {             // TT copies of 1 KiB: lane l moves 16 bytes
-      const char* src = xbase + (size_t)(kbg < kbg_last ? kbg : kbg_last) * x_stride;
+    step_barrier();
+  };
+  int st = st0;
+  for (; st + U < st1 && st + U < n_chunks; st += U) {
 #pragma unroll
-      for (int tt = 0; tt < TT; ++tt) {
-        const uint32_t l = (uint32_t)(uintptr_t)&xring[wave][slot][tt][0];
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                     : : "v"((uint32_t)lane * 16u), "s"(src + tt * 1024), "s"(l) : "memory", "m0");
-      }
-    };
-    // the copies are this wavefront's only memory loads, TT per k block, completed in order: "at most TT (XD - 1)
-    // outstanding" means the oldest requested block has arrived
-    constexpr int kXAhead = XD - 1;
+    for (int u = 0; u < U; ++u) step(std::true_type{}, u, st + u);
+  }
+  for (; st < st1; st += U) {
 #pragma unroll
-    for (int b = 0; b < kXAhead; ++b) request_x(4 * st0 + b, b);
-    int slot = 0;                                          // ring slot of the block multiplied next
-    __syncthreads();
-    for (int st = st0; st < st1; ++st) {
-      const int cur = st & 1;
-      u32x4 a[2];                                          // operands are read from LDS one row tile ahead of their use
-      a[0] = afrag[cur][0][0][lane];
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        const int ahead = slot + kXAhead < XD ? slot + kXAhead : slot + kXAhead - XD;   // the slot multiplied last
-        request_x(4 * st + kb + kXAhead, ahead);
-        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(TT * kXAhead) : "memory");
-        u32x4 xb[TT];
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) xb[tt] = xring[wave][slot][tt][lane];
-        slot = slot + 1 < XD ? slot + 1 : 0;
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          constexpr int kNone = -1;
-          const int rn = rt < RT - 1 ? rt + 1 : 0, kn = rt < RT - 1 ? kb : (kb < 3 ? kb + 1 : kNone);
-          if (kn != kNone) a[(kb * RT + rt + 1) & 1] = afrag[cur][rn][kn][lane];
-          __builtin_amdgcn_sched_barrier(0);               // keep the read above ahead of the matrix instructions below
-#pragma unroll
-          for (int tt = 0; tt < TT; ++tt) acc[rt][tt] = mfma_bf16(a[(kb * RT + rt) & 1], xb[tt], acc[rt][tt]);
-        }
-      }
-      step_barrier();
+    for (int u = 0; u < U; ++u) {
+      if (st + u >= st1) break;
+      step(std::false_type{}, u, st + u);
     }
-    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // the surplus copies must land before the LDS is given back
   }
 
+  if constexpr (TT == 0) return;
+  if constexpr (KS == 2) {                               // the other half's sums (the operands are done with)
+    f32x4* xch = reinterpret_cast<f32x4*>(lds) + (size_t)col * (RT * TT * 64);
+    if (half == 1) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) xch[(rt * TT + tt) * 64 + lane] = acc[rt][tt];
+    }
+    __syncthreads();
+    if (half == 1) return;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) acc[rt][tt] += xch[(rt * TT + tt) * 64 + lane];
+  }
   if (p.n_split > 1) {   // this workgroup saw a share of the contraction only: leave the tiles, in thread order
-    constexpr int NT = 64 * NM;
-    f32x4* t = p.tiles + ((((size_t)blockIdx.z * gridDim.x + blockIdx.x) * gridDim.y + blockIdx.y) * (RT * 4)) * NT + threadIdx.x;
+    constexpr int NT = 64 * kWaves;
+    f32x4* t = p.tiles + (((size_t)blockIdx.z * p.n_rg + rg) * p.n_blk + blk) * (RT * 4) * NT + threadIdx.x;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
@@ -237,201 +443,113 @@ __device__ __forceinline__ void multiply_block(const PrefillParams& p, const Tok
   // this lane holds, per row tile and token tile, rows 4 g .. 4 g + 3 at token n
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    const int j = 16 * (RT * blockIdx.x + rt) + 4 * g;
-    if (j >= p.d_out) continue;                          // d_out % 4 == 0
+    const int j = 16 * (RT * (rg - L.rg_begin) + rt) + 4 * g;
+    if (j >= L.d_out) continue;                          // d_out % 4 == 0
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
-      const int t = p.t_begin[tb.sg] + 16 * (tq0 - 16 * p.tb0[tb.sg] + tt) + n;
-      if (t < p.t_end[tb.sg]) {
+      const int tile = TT * col + tt;
+      const int t = p.t_begin[sg] + 16 * (tb.tile0 + tile - p.tile0[sg]) + n;
+      if (tile < tb.tiles && t < p.t_end[sg]) {
         const f32x4 o = acc[rt][tt];
         uint2 pk;
         pk.x = pack_bf16(o[0], o[1]);
         pk.y = pack_bf16(o[2], o[3]);
-        *reinterpret_cast<uint2*>(p.y + (size_t)t * p.d_out + j) = pk;
+        *reinterpret_cast<uint2*>(L.y + (size_t)t * L.d_out + j) = pk;
       }
     }
   }
 }
 
-// Grid: (row groups of 16 RT output channels, token blocks of 64 NM tokens, n_split); NM + RT wavefronts in two
-// roles, spread evenly over the SIMDs (RT = 8, or 7 where that fills the last round of workgroups: prefill_plan).
-// The token blocks of up to 8 long segments (each with its own expert's codes, steps and salient values) share one
-// launch, so that the compute units go from one expert's work to the next without a launch in between:
-//   builders (the last RT wavefronts): builder r forms the operand of row tile r (16 output channels) for the next
-//     step of 128 input channels in the idle LDS buffer, from base weight and codes requested two steps ahead;
-//   multipliers (wavefronts 0 .. NM - 1): every one multiplies all RT row tiles of the current step (from LDS) with
-//     its own 64 tokens (fewer in a segment's last block: a block of 3 tokens takes 0.62 of a full one's time, not all of
-//     it; 2141 + 1064 + 1027 tokens through the seven linears of a block: 3.02 -> 2.87 ms).  With RT = 8 the activations reach it through an LDS ring of its own, filled by
-//     asynchronous copies two k blocks ahead; with RT = 7 the 16 registers that leaves free hold a second set of
-//     activation fragments, loaded straight from memory one k block ahead (5 % faster: less LDS traffic).
-// Every workgroup reads all the activations of its tokens from L2 once per step, so the rows per workgroup set the
-// L2 traffic: 128 rows x 256 tokens halve it against 64 rows x 512 tokens, at the price of building every operand
-// once per 256 tokens.  What bounds it, with parts of the RT = 7 kernel taken out (3 experts x 512 tokens, 14336 rows; the
-// whole call 217 us, about 12 of them re-tiling): without matrix instructions 183, without the builders' loads and arithmetic
-// 163 (their arithmetic alone costs nothing: 214), without activation loads 182, matrix instructions and barriers alone
-// 117.  The loads do: 2.7 GB per launch leave the L2s, 14 TB/s, and 0.5 GB come from memory.  The matrix instructions
-// themselves run at what the card's power allows (the same call on zeros: 167 us).
-// One barrier per step.  The steps are the n_chunks chunks of input channels followed by n_ssteps steps over the
-// salient ranks; with n_split > 1 a workgroup covers a share of them and leaves its accumulators to
-// k_prefill_reduce.
-template <int BITS, int RT, int NM>
-__global__ __launch_bounds__(64 * (NM + RT), 1) void k_prefill_fused(const PrefillParams p) {
-  __shared__ __attribute__((aligned(16))) u32x4 afrag[2][RT][4][64];     // [buffer][row tile][k block][lane]
-  __shared__ __attribute__((aligned(16))) u32x4 xring[RT <= 7 ? 1 : NM][kRingDepth][4][64];   // [multiplier][slot][token tile][lane]
-  const int lane = threadIdx.x & 63;
+// Grid: (row groups of 16 RT output channels of all layers of the call, token blocks of up to 512 tokens, n_split); 512
+// threads, one workgroup per compute unit.
+template <int BITS, int RT>
+__global__ __launch_bounds__(64 * kWaves) void k_prefill_fused(const PrefillParams p) {
+  // two operand buffers of 4 RT KiB and, behind them, the operand too many; at the end 16 RT KiB of sums (KS = 2)
+  __shared__ __attribute__((aligned(16))) u32x4 lds[RT * 4 * 4 * 64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = lane & 15, g = lane >> 4;
+  const int rg = blockIdx.x, blk = blockIdx.y;
   const int n_steps = p.n_chunks + p.n_ssteps;
   const int st0 = blockIdx.z * p.steps_per_split;
   const int st1 = st0 + p.steps_per_split < n_steps ? st0 + p.steps_per_split : n_steps;
-  const TokenBlock tb = token_block(p, blockIdx.y);
-  const int sg = tb.sg;                                  // the segment (expert) this token block belongs to
-
-  if (wave >= NM) {
-    // ---- builder
-    const int rt = wave - NM;
-    int jt = RT * blockIdx.x + rt;                       // stored matrices are padded to whole groups of 4 row tiles:
-    jt = jt < p.n_jt ? jt : p.n_jt - 1;                  // a last group of 8 may repeat tiles (its rows are never stored)
-    const int row = 16 * jt + n < p.d_out ? 16 * jt + n : p.d_out - 1;
-    const float s = p.step[sg][row];
-    const float zs = p.z * s;
-    StepData<BITS> sd[2];
-    // Straight-line on purpose (addresses are selected, not branched on): the compiler then knows exactly which
-    // loads are in flight and never waits for the ones just requested.
-    auto fetch = [&](int slot, int st) {
-      st = st < st1 ? st : st1 - 1;
-      StepData<BITS>& d = sd[slot];
-      const bool main_step = st < p.n_chunks;
-      const size_t blk = (size_t)(main_step ? st : p.n_chunks - 1) * p.n_jt + jt;   // a salient step re-reads code words it never uses
-      const uint32_t* cw = p.codes[sg] + blk * (64 * BITS);
-      const int ss = main_step ? 0 : st - p.n_chunks;
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        int sb = 4 * ss + kb;
-        sb = sb < p.n_sb ? sb : p.n_sb - 1;              // past the last salient block: repeated, zeroed in build()
-        const u32x4* src = main_step ? p.base + (blk * 4 + kb) * 64 : p.sal[sg] + ((size_t)jt * p.n_sb + sb) * 64;
-        d.w[kb] = src[lane];
-        const int cl = 16 * kb + n;                      // the code block's lane cl owns columns 32 kb + 8 g + 0..7
-        if constexpr (BITS == 1) {
-          d.lo[kb] = cw[cl];
-        } else {
-          d.lo[kb] = cw[2 * cl + (g >> 1)];
-          if constexpr (BITS == 3) d.hi[kb] = cw[128 + cl];
-          if constexpr (BITS == 4) d.hi[kb] = cw[128 + 2 * cl + (g >> 1)];
-        }
-      }
-    };
-    auto build = [&](int slot, int st) {                // sd[slot] (of step st) -> LDS buffer st & 1
-      const int buf = st & 1;                           // a step past the end repeats the last one, into the idle buffer
-      st = st < st1 ? st : st1 - 1;
-      const StepData<BITS>& d = sd[slot];
-      if (st < p.n_chunks) {
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-          uint32_t lo = d.lo[kb], hi = 0;
-          constexpr uint32_t lo_mask = BITS == 1 ? 1u : 3u, hi_mask = BITS == 3 ? 1u : (BITS == 4 ? 3u : 0u);
-          if constexpr (BITS == 1) lo >>= g; else lo >>= 2 * (g & 1);
-          if constexpr (BITS == 3) hi = d.hi[kb] >> g;
-          if constexpr (BITS == 4) hi = d.hi[kb] >> (2 * (g & 1));
-          float v[8];
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const uint32_t u = ((lo >> (4 * q)) & lo_mask) | (((hi >> (4 * q)) & hi_mask) << 2);
-            const uint32_t ww = d.w[kb][q >> 1];
-            const float w = (q & 1) ? bf16_hi(ww) : bf16_lo(ww);
-            v[q] = w + __builtin_fmaf((float)u, s, -zs);   // W + (u - z) s
-          }
-          afrag[buf][rt][kb][lane] = u32x4{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
-        }
-      } else {
-        const int ss = st - p.n_chunks;
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-          u32x4 out = {0, 0, 0, 0};
-          if (4 * ss + kb < p.n_sb) {                    // ranks past k hold 0 and meet activations that are 0
-            const f16x8 h = __builtin_bit_cast(f16x8, d.w[kb]);
-            float v[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = (float)h[q] + zs;
-            out = u32x4{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
-          }
-          afrag[buf][rt][kb][lane] = out;
-        }
-      }
-    };
-    fetch(0, st0);
-    fetch(1, st0 + 1);
-    build(0, st0);
-    fetch(0, st0 + 2);
-    __syncthreads();
-    // iteration st builds step st + 1 (slot alternates 1, 0, 1, ...) and requests step st + 3 into the same slot
-    for (int st = st0; st < st1; st += 2) {
-      build(1, st + 1);
-      fetch(1, st + 3);
-      step_barrier();
-      if (st + 1 >= st1) break;
-      build(0, st + 2);
-      fetch(0, st + 4);
-      step_barrier();
-    }
-    return;
+  const int l = linear_of(p, rg);
+  const PrefillLinear& L = p.lin[l];
+  const TokenBlock tb = token_block(p, blk);
+  if (tb.tiles > 16) {
+    const int tt = wave_tiles(tb.tiles);
+    if (tt * wave >= tb.tiles) multiply_rows<BITS, RT, 0, 1>(p, L, l, tb, lds, wave, rg, blk, st0, st1);   // builds only
+    else if (tt == 4) multiply_rows<BITS, RT, 4, 1>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
+    else multiply_rows<BITS, RT, 3, 1>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
+  } else if (tb.tiles > 12) {
+    multiply_rows<BITS, RT, 4, 2>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
+  } else if (tb.tiles > 8) {
+    multiply_rows<BITS, RT, 3, 2>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
+  } else if (tb.tiles > 4) {
+    multiply_rows<BITS, RT, 2, 2>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
+  } else {
+    multiply_rows<BITS, RT, 1, 2>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
   }
-
-  // ---- multiplier
-  if (tb.tiles == 4) multiply_block<RT, NM, 4>(p, tb, afrag, xring, wave, st0, st1);
-  else if (tb.tiles == 3) multiply_block<RT, NM, 3>(p, tb, afrag, xring, wave, st0, st1);
-  else if (tb.tiles == 2) multiply_block<RT, NM, 2>(p, tb, afrag, xring, wave, st0, st1);
-  else multiply_block<RT, NM, 1>(p, tb, afrag, xring, wave, st0, st1);
 }
 
 // Split contraction only: y = sum over splits (in split order) of the accumulator tiles, rounded to bf16.
-// Grid (row groups, token blocks, 4 RT tiles), NM wavefronts laid out like the multipliers of the main kernel; one
-// tile (row tile rt = z / 4, token tile tt = z % 4) per workgroup.
-template <int RT, int NM>
-__global__ __launch_bounds__(64 * NM) void k_prefill_reduce(const PrefillParams p) {
-  constexpr int NT = 64 * NM, TT = 4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = lane & 15, g = lane >> 4;
-  const int rt = blockIdx.z >> 2, tt = blockIdx.z & 3;
-  const TokenBlock tb = token_block(p, blockIdx.y);
-  if (tt >= tb.tiles) return;
+// Grid (row groups, token blocks, 4 RT tiles), wavefronts laid out like those of the main kernel that hold sums; one tile (row tile
+// rt = z / 4, token tile tt = z % 4) of each per workgroup.
+template <int RT>
+__global__ __launch_bounds__(64 * kWaves) void k_prefill_reduce(const PrefillParams p) {
+  constexpr int NT = 64 * kWaves;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
+  const int rg = blockIdx.x, blk = blockIdx.y, rt = blockIdx.z >> 2, tt = blockIdx.z & 3;
+  const TokenBlock tb = token_block(p, blk);
+  const int TT = wave_tiles(tb.tiles), tile = TT * wave + tt;
+  if (tt >= TT || tile >= tb.tiles) return;
+  const PrefillLinear& L = p.lin[linear_of(p, rg)];
   f32x4 o = {0, 0, 0, 0};
   for (int sp = 0; sp < p.n_split; ++sp)
-    o += p.tiles[((((size_t)sp * gridDim.x + blockIdx.x) * gridDim.y + blockIdx.y) * (RT * TT) + blockIdx.z) * NT + threadIdx.x];
-  const int j = 16 * (RT * blockIdx.x + rt) + 4 * g;
-  const int t = p.t_begin[tb.sg] + 256 * tb.blk + 16 * (tb.tiles * wave + tt) + n;
-  if (j < p.d_out && t < p.t_end[tb.sg]) {
+    o += p.tiles[((((size_t)sp * p.n_rg + rg) * p.n_blk + blk) * (RT * 4) + blockIdx.z) * NT + threadIdx.x];
+  const int j = 16 * (RT * (rg - L.rg_begin) + rt) + 4 * g;
+  const int t = p.t_begin[tb.sg] + 16 * (tb.tile0 + tile - p.tile0[tb.sg]) + n;
+  if (j < L.d_out && t < p.t_end[tb.sg]) {
     uint2 pk;
     pk.x = pack_bf16(o[0], o[1]);
     pk.y = pack_bf16(o[2], o[3]);
-    *reinterpret_cast<uint2*>(p.y + (size_t)t * p.d_out + j) = pk;
+    *reinterpret_cast<uint2*>(L.y + (size_t)t * L.d_out + j) = pk;
   }
 }
 
-struct PrefillPlan {
-  int rt, nm, n_rg, n_tb, n_tq, n_split, steps_per_split, n_chunks, n_ssteps;
-  size_t xt_bytes, tiles_at, tiles_bytes;
+// ---- plan -----------------------------------------------------------------------------------------------
+
+// Time of a workgroup with up to 4, 8, ... 32 token tiles, us, 33 steps at 2 bits on a full chip, by row tiles (7, 8); 11 of
+// it do not depend on the steps.
+constexpr double kBlockTime[2][8] = {{44, 56, 62, 79, 92, 100, 115, 122}, {44, 59, 68, 82, 106, 109, 130, 136}};
+constexpr double kFixedTime = 11;
+inline double block_time(int rt, int tiles, int steps) {
+  return kFixedTime + (kBlockTime[rt - 7][(tiles - 1) / 4] - kFixedTime) * steps / 33.0;
+}
+
+struct Blocks {
+  TokenBlock b[kMaxBlocks];
+  int n;
 };
 
-// Time of a workgroup on a last block of up to 64, 128, 192 tokens, relative to one of 256 (4096 x 14336, 2141 + 1064 + 1027
-// tokens: seven rounds of 256 tokens and two of partial blocks in 588 us).
-constexpr double kTailTime[5] = {0.0, 0.62, 0.72, 0.86, 1.0};
+struct PrefillPlan {
+  int rt, n_split, steps_per_split;
+  Blocks blocks;
+};
 
-// Time of a launch of n_rg row groups, in full workgroups: the compute units take n_rg x n_full full ones and then, for
-// every partial block (tails: its 64-token quarters), n_rg shorter ones, each as soon as one is free.
-double launch_rounds(int n_rg, int n_full, const int* tails, int n_tails) {
-  struct { double at; int units; } pool[kMaxSegs * 4 + 4];     // compute units by the time they are free
-  const long full = (long)n_rg * n_full;
-  int n = 0;
-  pool[n++] = {(double)(full / kMaxWorkgroups), (int)(kMaxWorkgroups - full % kMaxWorkgroups)};
-  if (full % kMaxWorkgroups) pool[n++] = {(double)(full / kMaxWorkgroups + 1), (int)(full % kMaxWorkgroups)};
-  double end = pool[n - 1].at;
-  for (int i = 0; i < n_tails; ++i) {
-    for (int left = n_rg; left > 0;) {
+// When the compute units are done that take, from a list, every token block's n_rg workgroups, each as soon as one is free.
+double launch_time(const Blocks& bl, int n_rg, int rt, int steps, int n_split) {
+  struct { double at; int units; } pool[48];                   // compute units by the time they are free
+  int n = 1;
+  pool[0] = {0.0, kMaxWorkgroups};
+  double end = 0.0;
+  for (int i = 0; i < bl.n;) {
+    int same = i + 1;
+    while (same < bl.n && (bl.b[same].tiles - 1) / 4 == (bl.b[i].tiles - 1) / 4) ++same;
+    const double t = block_time(rt, bl.b[i].tiles, steps);
+    for (long left = (long)(same - i) * n_rg * n_split; left > 0;) {
       int first = 0;
       for (int q = 1; q < n; ++q) first = pool[q].at < pool[first].at ? q : first;
-      const int take = left < pool[first].units ? left : pool[first].units;
-      const double done = pool[first].at + kTailTime[tails[i]];
+      const int take = left < pool[first].units ? (int)left : pool[first].units;
+      const double done = pool[first].at + t;
       end = done > end ? done : end;
       left -= take;
       if (take == pool[first].units || n == (int)(sizeof(pool) / sizeof(pool[0]))) {
@@ -441,73 +559,109 @@ double launch_rounds(int n_rg, int n_full, const int* tails, int n_tails) {
         pool[n++] = {done, take};
       }
     }
+    i = same;
   }
   return end;
 }
 
-// n_tb: token blocks of all the segments of the launch together; n_full of them are full, tails: the others' quarters
-PrefillPlan prefill_plan(int d_in, int d_out, int k, int n_tb, int n_full, const int* tails) {
-  PrefillPlan pl;
-  pl.rt = 8;   // 128 rows x 256 tokens per workgroup: measured 6 % faster than 64 x 512 and 14 % faster than 64 x 256
-  pl.nm = 4;
-  pl.n_tb = n_tb;
-  pl.n_tq = pl.n_tb * 4 * pl.nm;
-  const int n_jt = ceil_to(d_out, kRowPad) / 16;
-  pl.n_rg = (n_jt + pl.rt - 1) / pl.rt;
-  // One workgroup per compute unit at a time: the launch takes ceil(workgroups / 256) rounds of one workgroup's
-  // time, which grows with its row tiles; the workgroups of partial blocks go behind and fill the last round.  7 row tiles
-  // per workgroup win where they fill the last round better (14336 rows x 6 token blocks: 768 workgroups = 3 full rounds
-  // of 7 tiles against 2.6 -> 3 rounds of 8; 4096 rows x 6 blocks: one round of 222 workgroups against one of 192); + 3.5
-  // below: the part of a workgroup's time that does not shrink with its rows (14336 rows, 16 full and 3 partial blocks:
-  // 9.24 rounds of 7 tiles in 616 us, 8.24 rounds of 8 in 588; 6 full blocks: 3 rounds of 7 in 203, of 8 in 219).  128
-  // workgroups or fewer split the contraction instead and keep 8 tiles.
-  {
-    auto rounds = [&](int rgs) { return launch_rounds(rgs, n_full, tails, n_tb - n_full); };
-    const int rg7 = (n_jt + 6) / 7;
-    if (2l * pl.n_rg * n_tb > kMaxWorkgroups && rounds(rg7) * (7 + 3.5) < rounds(pl.n_rg) * (8 + 3.5)) {
-      pl.rt = 7;
-      pl.n_rg = rg7;
+// The segments' tokens as blocks of at most `most` tiles, the longest first.  even: a segment's blocks alike, else full ones
+// and what is left.  The last `halved` full blocks become two each.  False: too many for one launch.
+bool cut_blocks(Blocks& bl, const int* seg_tiles, int n_seg, int most, bool even, int halved) {
+  bl.n = 0;
+  int tile0 = 0, full = 0;
+  if (halved > 0)
+    for (int i = 0; i < n_seg; ++i) full += seg_tiles[i] / kBlockTiles;
+  for (int i = 0; i < n_seg; ++i) {
+    const int r = seg_tiles[i], nb = (r + most - 1) / most;
+    for (int b = 0; b < nb; ++b) {
+      const int lo = even ? (int)((long)r * b / nb) : b * most, end = even ? (int)((long)r * (b + 1) / nb) : lo + most, hi = end < r ? end : r;
+      const bool halve = halved > 0 && hi - lo == kBlockTiles && full-- <= halved;
+      if (bl.n + (halve ? 2 : 1) > kMaxBlocks) return false;
+      const int mid = halve ? (lo + hi) / 2 : hi;
+      bl.b[bl.n++] = {i, tile0 + lo, mid - lo};
+      if (halve) bl.b[bl.n++] = {i, tile0 + mid, hi - mid};
+    }
+    tile0 += r;
+  }
+  for (int i = 1; i < bl.n; ++i) {                             // insertion: stable, and nearly sorted already
+    const TokenBlock v = bl.b[i];
+    int j = i;
+    for (; j > 0 && (bl.b[j - 1].tiles - 1) / 4 < (v.tiles - 1) / 4; --j) bl.b[j] = bl.b[j - 1];
+    bl.b[j] = v;
+  }
+  return true;
+}
+
+// Row tiles per workgroup, token blocks and column splits of a launch: whichever of a few candidates is expected to be done
+// first.  A workgroup has a compute unit to itself, so what counts is how the workgroups' times fill the 256 of them.
+// seg_tiles: 16-token tiles of every segment; d_out: of every layer.
+bool prefill_plan(PrefillPlan& best, const int* seg_tiles, int n_seg, const int* d_out, int n_linears, int steps) {
+  double best_time = 1e30;
+  Blocks bl;
+  double elements = 0;
+  for (int l = 0; l < n_linears; ++l) elements += d_out[l];
+  int tiles = 0;
+  for (int i = 0; i < n_seg; ++i) tiles += seg_tiles[i];
+  elements *= 16.0 * tiles;
+  for (int rt = 8; rt >= 7; --rt) {
+    int n_rg = 0;
+    for (int l = 0; l < n_linears; ++l) n_rg += (ceil_to(d_out[l], kRowPad) / 16 + rt - 1) / rt;
+    auto consider = [&](int most, bool even, int halved) {
+      if (!cut_blocks(bl, seg_tiles, n_seg, most, even, halved)) return;
+      // fewer workgroups than compute units: share the steps out, at least four to each
+      const long wgs = (long)n_rg * bl.n;
+      for (int want = 1; want <= 8 && want * wgs <= kMaxWorkgroups && (want == 1 || 4 * want <= steps); ++want) {
+        const int per = (steps + want - 1) / want, n_split = (steps + per - 1) / per;
+        // (partial sums: written and read at about 4 TB/s, and another launch)
+        const double t = launch_time(bl, n_rg, rt, per, n_split) + (n_split > 1 ? 4.0 + n_split * elements * 8.0 / 4e6 : 0.0);
+        if (t < 0.99 * best_time) { best_time = t; best.rt = rt; best.n_split = n_split; best.steps_per_split = per; best.blocks = bl; }
+      }
+      if (wgs > kMaxWorkgroups) {
+        const double t = launch_time(bl, n_rg, rt, steps, 1);
+        if (t < 0.99 * best_time) { best_time = t; best.rt = rt; best.n_split = 1; best.steps_per_split = steps; best.blocks = bl; }
+      }
+    };
+    consider(32, false, 0);
+    int full = 0;
+    for (int i = 0; i < n_seg; ++i) full += seg_tiles[i] / kBlockTiles;
+    const int over = (int)((long)full * n_rg % kMaxWorkgroups), h = over / n_rg;   // full workgroups of the last round
+    if (over > 0 && h > 0) consider(32, false, h);
+    if (over > 0 && h < full) consider(32, false, h + 1);
+    if (full * (long)n_rg < 4 * kMaxWorkgroups) {
+      consider(32, true, 0);
+      consider(24, true, 0);
+      consider(16, true, 0);
+      if (tiles * (long)n_rg < 12 * kMaxWorkgroups) consider(12, true, 0);
     }
   }
-  pl.n_chunks = ceil_to(d_in, kColPad) / 128;
-  pl.n_ssteps = (ceil_to(k, kSalPad) / 32 + 3) / 4;
-  const int n_steps = pl.n_chunks + pl.n_ssteps;
-  const long base = (long)pl.n_rg * pl.n_tb;
-  int want = (int)(kMaxWorkgroups / base);
-  want = want < 1 ? 1 : (want > 8 ? 8 : want);
-  pl.steps_per_split = (n_steps + want - 1) / want;
-  if (pl.steps_per_split < 4) pl.steps_per_split = n_steps < 4 ? n_steps : 4;
-  pl.n_split = (n_steps + pl.steps_per_split - 1) / pl.steps_per_split;
-  pl.xt_bytes = (size_t)(4 * n_steps) * pl.n_tq * 1024;
-  pl.tiles_at = (pl.xt_bytes + 255) / 256 * 256;
-  pl.tiles_bytes = pl.n_split > 1 ? (size_t)pl.n_split * base * (4 * pl.rt) * (64 * pl.nm) * 16 : 0;
-  return pl;
+  return best_time < 1e30;
 }
 
 template <int BITS>
-hipError_t launch_fused(const PrefillParams& p, const PrefillPlan& pl, dim3 grid, hipStream_t s) {
-  if (pl.rt == 7) k_prefill_fused<BITS, 7, 4><<<grid, 64 * (4 + 7), 0, s>>>(p);
-  else k_prefill_fused<BITS, 8, 4><<<grid, 768, 0, s>>>(p);
+hipError_t launch_fused(const PrefillParams& p, int rt, dim3 grid, hipStream_t s) {
+  if (rt == 7) k_prefill_fused<BITS, 7><<<grid, 64 * kWaves, 0, s>>>(p);
+  else k_prefill_fused<BITS, 8><<<grid, 64 * kWaves, 0, s>>>(p);
   return hipGetLastError();
 }
 
 }  // namespace
 
 // Scratch for the long segments of a call of up to max_tokens tokens: their activations in fragment order (input
-// channels, then up to d_in gathered salient ones; every segment padded to whole blocks of 256 tokens, at most
+// channels, then up to d_in gathered salient ones; room for every segment padded to whole blocks of 256 tokens, at most
 // max_tokens / 192 segments) and, for a split contraction, the accumulator tiles: a split happens only while
-// splits x row groups x token blocks stays within 256 workgroups, each leaving 128 rows x 256 tokens x 4 bytes.
+// splits x row groups x token blocks stays within 256 workgroups, each leaving 128 rows x 512 tokens x 4 bytes.
 size_t prefill_scratch_bytes(int d_in, int max_tokens) {
   const size_t tok_pad = (size_t)max_tokens + (size_t)256 * (max_tokens / 192 + 1);
   const size_t xt = tok_pad * (size_t)(ceil_to(d_in, kColPad) + ceil_to(ceil_to(d_in, kSalPad), 128)) * 2;
-  const size_t tiles = (size_t)2 * kMaxWorkgroups * 128 * 256 * 4;
+  const size_t tiles = (size_t)kMaxWorkgroups * 128 * 512 * 4;
   return (xt + 255) / 256 * 256 + tiles;
 }
 
 // y rows of the n_seg long segments seg_experts[i] (expert numbers; rows seg[e] .. seg[e + 1]) of the n_linears layers
 // of a call (they read the same x and routing), each layer with its own experts' deltas, up to kMaxSegs segments per
-// launch.  The segments' activations are re-tiled once for all layers; the gathered salient activations, which
-// depend on the layer's salient sets, once per layer into the same place (the launches are stream-ordered).
+// launch.  All layers share a launch (their row groups one after the other) while the scratch holds every layer's gathered
+// salient activations behind the input channels; else each has its own, the gathered activations in the same place one
+// after the other (the launches are stream-ordered).
 // scratch: prefill_scratch_bytes(d_in, >= all their tokens).
 // ev_start / ev_stop (measurement hook, may be null): recorded immediately before the first fused kernel (only while
 // *first_kernel is set, which this clears) and immediately after every fused kernel and its reduction.
@@ -515,86 +669,110 @@ hipError_t launch_prefill_segments(const mes_linear* lin, int n_linears, const i
                                    const int32_t* seg, const void* x, void* scratch, hipEvent_t ev_start,
                                    hipEvent_t ev_stop, bool* first_kernel, hipStream_t s) {
   char* ws = reinterpret_cast<char*>(scratch);
+  const mes_delta& d = lin[0].experts[seg_experts[0]];   // d_in, bits, grid and k are the same for all experts and layers
+  const int n_chunks = ceil_to(d.d_in, kColPad) / 128, n_ssteps = (ceil_to(d.k, kSalPad) / 32 + 3) / 4, steps = n_chunks + n_ssteps;
+  const bool together = n_linears * n_ssteps <= ceil_to(ceil_to(d.d_in, kSalPad), 128) / 128;
+  const int per_launch = together ? n_linears : 1;
   for (int first = 0; first < n_seg; first += kMaxSegs) {
     const int ns = n_seg - first < kMaxSegs ? n_seg - first : kMaxSegs;
-    for (int l = 0; l < n_linears; ++l) {
-      const mes_delta* experts = lin[l].experts;
-      const mes_delta& d = experts[seg_experts[first]];   // shape, bits, grid and k are the same for all experts of a linear
-      PrefillParams p;
-      TileParams tp;
-      int n_tb = 0, n_tails = 0, tails[kMaxSegs];
-      p.n_full = 0;
-      for (int i = 0; i < kMaxSegs; ++i) {
-        const mes_delta& de = experts[seg_experts[first + (i < ns ? i : 0)]];
-        const int e = seg_experts[first + (i < ns ? i : 0)];
-        p.codes[i] = reinterpret_cast<const uint32_t*>(de.codes);
-        p.step[i] = de.step;
-        p.sal[i] = reinterpret_cast<const u32x4*>(de.salient);
-        tp.sidx[i] = de.salient_idx;
-        p.t_begin[i] = tp.t_begin[i] = seg[e];
-        p.t_end[i] = tp.t_end[i] = seg[e + 1];
-        p.tb0[i] = tp.tb0[i] = n_tb;
-        p.fb0[i] = p.n_full;
-        if (i < ns) {
-          const int len = seg[e + 1] - seg[e], full = len / 256, left = len - 256 * full;
-          n_tb += full;
-          p.n_full += full;
-          if (left > 0) {
-            p.tail_seg[n_tails] = i;
-            tails[n_tails++] = (left + 63) / 64;
-            ++n_tb;
-          }
+    PrefillParams p;
+    TileParams tp;
+    int seg_tiles[kMaxSegs], n_tq = 0;
+    for (int i = 0; i < kMaxSegs; ++i) {
+      const int e = seg_experts[first + (i < ns ? i : 0)];
+      p.t_begin[i] = tp.t_begin[i] = seg[e];
+      p.t_end[i] = tp.t_end[i] = seg[e + 1];
+      p.tile0[i] = tp.tile0[i] = n_tq;
+      if (i < ns) n_tq += seg_tiles[i] = (seg[e + 1] - seg[e] + 15) / 16;
+    }
+    p.xt = reinterpret_cast<const u32x4*>(ws);
+    p.n_chunks = n_chunks;
+    p.n_sb = ceil_to(d.k, kSalPad) / 32;
+    p.n_ssteps = n_ssteps;
+    p.n_tq = n_tq;
+    p.z = d.grid == MES_GRID_SYM ? (float)(1 << (d.bits - 1)) - 0.5f : (float)(1 << (d.bits - 1));
+    const size_t xt_bytes = (size_t)4 * (n_chunks + per_launch * n_ssteps) * n_tq * 1024;
+    p.tiles = reinterpret_cast<f32x4*>(ws + (xt_bytes + 255) / 256 * 256);
+    p.n_linears = per_launch;
+    tp.x = reinterpret_cast<const uint16_t*>(x);
+    tp.n_seg = ns;
+    tp.k = d.k;
+    tp.d_in = d.d_in;
+    tp.n_chunks = n_chunks;
+    tp.n_ssteps = n_ssteps;
+    tp.n_tq = n_tq;
+    tp.xt = reinterpret_cast<u32x4*>(ws);
+    for (int l0 = 0; l0 < n_linears; l0 += per_launch) {
+      int d_outs[MES_MAX_FUSED];
+      for (int l = 0; l < MES_MAX_FUSED; ++l) {
+        const mes_linear& src = lin[l0 + (l < per_launch ? l : 0)];   // unused entries repeat the first (never selected)
+        PrefillLinear& L = p.lin[l];
+        L.base = reinterpret_cast<const u32x4*>(src.w_base_tiled);
+        L.y = reinterpret_cast<uint16_t*>(src.y);
+        for (int i = 0; i < kMaxSegs; ++i) {
+          const mes_delta& de = src.experts[seg_experts[first + (i < ns ? i : 0)]];
+          L.codes[i] = reinterpret_cast<const uint32_t*>(de.codes);
+          L.step[i] = de.step;
+          L.sal[i] = reinterpret_cast<const u32x4*>(de.salient);
+          tp.sidx[l][i] = de.salient_idx;
         }
+        L.d_out = d_outs[l] = src.experts[seg_experts[first]].d_out;
+        L.n_jt = ceil_to(L.d_out, kRowPad) / 16;
       }
-      p.fb0[kMaxSegs] = p.n_full;
-      p.tb0[kMaxSegs] = tp.tb0[kMaxSegs] = n_tb;
-      for (int i = ns; i <= kMaxSegs; ++i) p.tb0[i] = tp.tb0[i] = n_tb;
-      for (int i = n_tails; i < kMaxSegs; ++i) p.tail_seg[i] = 0;
-      p.n_seg = tp.n_seg = ns;
-      const PrefillPlan pl = prefill_plan(d.d_in, d.d_out, d.k, n_tb, p.n_full, tails);
-      p.base = reinterpret_cast<const u32x4*>(lin[l].w_base_tiled);
-      p.xt = reinterpret_cast<const u32x4*>(ws);
-      p.y = reinterpret_cast<uint16_t*>(lin[l].y);
-      p.tiles = reinterpret_cast<f32x4*>(ws + pl.tiles_at);
-      p.d_out = d.d_out;
-      p.n_jt = ceil_to(d.d_out, kRowPad) / 16;
-      p.n_chunks = pl.n_chunks;
-      p.n_sb = ceil_to(d.k, kSalPad) / 32;
-      p.n_ssteps = pl.n_ssteps;
-      p.n_tq = pl.n_tq;
-      p.steps_per_split = pl.steps_per_split;
-      p.n_split = pl.n_split;
-      p.z = d.grid == MES_GRID_SYM ? (float)(1 << (d.bits - 1)) - 0.5f : (float)(1 << (d.bits - 1));
-      tp.x = reinterpret_cast<const uint16_t*>(x);
-      tp.k = d.k;
-      tp.d_in = d.d_in;
-      tp.n_kb_main = 4 * pl.n_chunks;
-      tp.n_tq = pl.n_tq;
-      tp.xt = reinterpret_cast<u32x4*>(ws);
       hipError_t e = hipSuccess;
-      // the input channels, the same for every layer of the call, go with the first one; every layer has its own
-      // gathered salient channels, behind them (one launch for both: a second one took 5 us)
-      tp.kb_begin = l == 0 ? 0 : tp.n_kb_main;
-      tp.n_blk = (size_t)(tp.n_kb_main + 4 * pl.n_ssteps - tp.kb_begin) * pl.n_tq;
-      if (tp.n_blk > 0) {
-        k_prefill_tile_x<<<(unsigned)((tp.n_blk + 3) / 4), 256, 0, s>>>(tp);
+      // the input channels, the same for every layer of the call, go with the first launch
+      tp.u_begin = l0 == 0 ? 0 : n_chunks;
+      tp.n_units = n_chunks + per_launch * n_ssteps - tp.u_begin;
+      if (tp.n_units > 0) {
+        const long waves = (long)tp.n_units * n_tq;
+        k_prefill_tile_x<<<(unsigned)((waves + 3) / 4), 256, 0, s>>>(tp);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
-      const dim3 grid(pl.n_rg, pl.n_tb, pl.n_split);
-      if (ev_start && *first_kernel && (e = hipEventRecord(ev_start, s)) != hipSuccess) return e;
-      *first_kernel = false;
-      switch (d.bits) {
-        case 1: e = launch_fused<1>(p, pl, grid, s); break;
-        case 2: e = launch_fused<2>(p, pl, grid, s); break;
-        case 3: e = launch_fused<3>(p, pl, grid, s); break;
-        default: e = launch_fused<4>(p, pl, grid, s); break;
+      PrefillPlan pl;
+      const bool planned = prefill_plan(pl, seg_tiles, ns, d_outs, per_launch, steps);
+      if (!planned) { pl.rt = 8; pl.n_split = 1; pl.steps_per_split = steps; }   // more blocks than one launch holds: full ones
+      p.n_split = pl.n_split;
+      p.steps_per_split = pl.steps_per_split;
+      p.n_rg = 0;
+      for (int l = 0; l < MES_MAX_FUSED; ++l) {
+        p.lin[l].rg_begin = p.n_rg;
+        if (l < per_launch) p.n_rg += (p.lin[l].n_jt + pl.rt - 1) / pl.rt;
+        p.lin[l].rg_end = p.n_rg;
       }
-      if (e != hipSuccess) return e;
-      if (pl.n_split > 1) {
-        k_prefill_reduce<8, 4><<<dim3(grid.x, grid.y, 32), 256, 0, s>>>(p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+      int sg = 0, tile = 0;                                     // (not planned: where the next launch's blocks begin)
+      for (bool more = true; more;) {
+        more = false;
+        if (planned) {
+          p.n_blk = pl.blocks.n;
+          for (int b = 0; b < p.n_blk; ++b) p.blocks[b] = pack_block(pl.blocks.b[b].sg, pl.blocks.b[b].tile0, pl.blocks.b[b].tiles);
+        } else {
+          p.n_blk = 0;
+          while (sg < ns && p.n_blk < kMaxBlocks) {
+            const int left = seg_tiles[sg] - tile, take = left < kBlockTiles ? left : kBlockTiles;
+            p.blocks[p.n_blk++] = pack_block(sg, p.tile0[sg] + tile, take);
+            tile += take;
+            if (tile == seg_tiles[sg]) { ++sg; tile = 0; }
+          }
+          more = sg < ns;
+        }
+        for (int b = p.n_blk; b < kMaxBlocks; ++b) p.blocks[b] = p.blocks[0];   // never selected
+        const dim3 grid(p.n_rg, p.n_blk, pl.n_split);
+        if (ev_start && *first_kernel && (e = hipEventRecord(ev_start, s)) != hipSuccess) return e;
+        *first_kernel = false;
+        switch (d.bits) {
+          case 1: e = launch_fused<1>(p, pl.rt, grid, s); break;
+          case 2: e = launch_fused<2>(p, pl.rt, grid, s); break;
+          case 3: e = launch_fused<3>(p, pl.rt, grid, s); break;
+          default: e = launch_fused<4>(p, pl.rt, grid, s); break;
+        }
+        if (e != hipSuccess) return e;
+        if (pl.n_split > 1) {
+          if (pl.rt == 7) k_prefill_reduce<7><<<dim3(p.n_rg, p.n_blk, 28), 64 * kWaves, 0, s>>>(p);
+          else k_prefill_reduce<8><<<dim3(p.n_rg, p.n_blk, 32), 64 * kWaves, 0, s>>>(p);
+          if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        if (ev_stop && (e = hipEventRecord(ev_stop, s)) != hipSuccess) return e;
       }
-      if (ev_stop && (e = hipEventRecord(ev_stop, s)) != hipSuccess) return e;
     }
   }
   return hipSuccess;
