@@ -103,16 +103,18 @@ struct TileParams {
   const int32_t* sidx[MES_MAX_FUSED][kMaxSegs];
   int t_begin[kMaxSegs], t_end[kMaxSegs], tile0[kMaxSegs];
   int n_seg, k, d_in, n_chunks, n_ssteps, n_tq;
-  int u_begin, n_units;     // this launch writes the units u_begin .. u_begin + n_units - 1 (a unit: four k blocks, see below)
+  int u_begin, n_units;     // this launch writes the units u_begin .. u_begin + n_units - 1 (see below)
   u32x4* xt;
 };
 
-// The segments' rows of x -> fragment order.  A wavefront writes one unit of one token tile tq: unit u < n_chunks are the k
-// blocks of input channels 128 u .. 128 u + 127, the units behind them, n_ssteps per layer, those of 128 of the layer's
-// salient channels.  Block (kb, tq), lane l: token 16 tq' + (l & 15) of the segment that tq belongs to (tq' counted from
-// the segment's first tile); the 8 input channels 32 kb + 8 (l >> 4) .., or the 8 salient channels of that segment's expert
-// with ranks 32 kb + 8 (l >> 4) ..; zero beyond the segment's last token, the last channel or rank.
-// Bound by memory latency: every lane has four loads in flight, 256 bytes of each of 16 rows per wavefront.
+// The segments' rows of x -> fragment order.  A wavefront writes one unit of one token tile tq: unit u < n_chunks are the four
+// k blocks of input channels 128 u .. 128 u + 127, the units behind them, 4 n_ssteps per layer, one k block of 32 of the
+// layer's salient channels each.  Block (kb, tq), lane l: token 16 tq' + (l & 15) of the segment that tq belongs to (tq'
+// counted from the segment's first tile); the 8 input channels 32 kb + 8 (l >> 4) .., or the 8 salient channels of that
+// segment's expert with ranks 32 kb + 8 (l >> 4) ..; zero beyond the segment's last token, the last channel or rank.
+// Bound by memory latency: a lane has four loads in flight, the wavefront 256 bytes of each of 16 rows.  (Gathers take a
+// cycle per lane and a second trip: four k blocks of them in one wavefront were the launch's last to end, 1536 tokens x 4096
+// channels, 128 salient ones, 19.5 us against TILE_NOW.)
 __global__ __launch_bounds__(256) void k_prefill_tile_x(const TileParams p) {
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const long w = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -124,34 +126,32 @@ __global__ __launch_bounds__(256) void k_prefill_tile_x(const TileParams p) {
   const int t = p.t_begin[sg] + 16 * (tq - p.tile0[sg]) + (lane & 15);
   const bool live = t < p.t_end[sg];
   const uint16_t* row = p.x + (size_t)(live ? t : p.t_begin[sg]) * p.d_in;
-  u32x4 v[4];
   if (u < p.n_chunks) {
+    u32x4 v[4];
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
-      const int c = 128 * u + 32 * kb + 8 * g;
-      v[kb] = u32x4{0, 0, 0, 0};
-      if (live && c < p.d_in) v[kb] = *reinterpret_cast<const u32x4*>(row + c);
+      const int c = 128 * u + 32 * kb + 8 * g;     // d_in % 8 == 0
+      v[kb] = *reinterpret_cast<const u32x4*>(row + (c < p.d_in ? c : p.d_in - 8));
+      if (!live || c >= p.d_in) v[kb] = u32x4{0, 0, 0, 0};
     }
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) p.xt[((size_t)(4 * u + kb) * p.n_tq + tq) * 64 + lane] = v[kb];
   } else {
-    const int l = (u - p.n_chunks) / p.n_ssteps, r_begin = 128 * (u - p.n_chunks - l * p.n_ssteps) + 8 * g;
+    const int l = (u - p.n_chunks) / (4 * p.n_ssteps), r0 = 32 * (u - p.n_chunks - 4 * l * p.n_ssteps) + 8 * g;
     const int32_t* sidx = p.sidx[l][sg];
+    int c[8];
+    uint32_t h[8];
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-      const int r0 = r_begin + 32 * kb;
-      uint32_t h[8];
+    for (int q = 0; q < 8; ++q) c[q] = sidx[r0 + q < p.k ? r0 + q : p.k - 1];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        h[q] = 0;
-        if (live && r0 + q < p.k) {
-          const int c = sidx[r0 + q];
-          if (c >= 0 && c < p.d_in) h[q] = row[c];   // a corrupt list can never address outside the row
-        }
-      }
-      v[kb] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+    for (int q = 0; q < 8; ++q) {
+      const bool valid = live && r0 + q < p.k && (uint32_t)c[q] < (uint32_t)p.d_in;   // a corrupt list can never address outside the row
+      h[q] = row[valid ? c[q] : 0];
+      if (!valid) h[q] = 0;
     }
+    p.xt[((size_t)(3 * p.n_chunks + u) * p.n_tq + tq) * 64 + lane] =
+        u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
   }
-#pragma unroll
-  for (int kb = 0; kb < 4; ++kb) p.xt[((size_t)(4 * u + kb) * p.n_tq + tq) * 64 + lane] = v[kb];
 }
 
 // What a wavefront keeps in flight of a later step's weights: its NOP of the step's 4 RT operands.
@@ -722,7 +722,7 @@ hipError_t launch_prefill_segments(const mes_linear* lin, int n_linears, const i
       hipError_t e = hipSuccess;
       // the input channels, the same for every layer of the call, go with the first launch
       tp.u_begin = l0 == 0 ? 0 : n_chunks;
-      tp.n_units = n_chunks + per_launch * n_ssteps - tp.u_begin;
+      tp.n_units = n_chunks + 4 * per_launch * n_ssteps - tp.u_begin;
       if (tp.n_units > 0) {
         const long waves = (long)tp.n_units * n_tq;
         k_prefill_tile_x<<<(unsigned)((waves + 3) / 4), 256, 0, s>>>(tp);
