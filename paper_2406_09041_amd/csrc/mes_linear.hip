@@ -425,14 +425,15 @@ struct Stream {
   }
 
   // Loads of one chunk() call that are younger than its stage copy: all of its weight and scale requests.
-  template <bool NOBASE> static constexpr int younger() { return NL + (NOBASE ? 0 : 4) + 2 * kSalPerChunk; }
+  template <bool NOBASE, bool SAL> static constexpr int younger() { return NL + (NOBASE ? 0 : 4) + (SAL ? 2 * kSalPerChunk : 0); }
 
   // One chunk out of base buffer BUF and stage `cur` (its per-token numbers: cur_x); the next chunks' data are
   // requested first.  NOBASE: a sweep after the first -- the base product is done, only the slots of this sweep are multiplied.
-  template <int BUF, bool NOBASE>
+  // SAL: a salient pair is multiplied and the next one requested.
+  template <int BUF, bool NOBASE, bool SAL>
   __device__ __forceinline__ void chunk(int cn, int c2, const char* cur, const char* cur_x, char* nxt, char* nxt_x, int wave) {
     stage_copy<NW>(xt + (size_t)cn * kStageBytes, nxt, nxt_x, wave, lane);
-    sal_lookup();
+    if constexpr (SAL) sal_lookup();
     if constexpr (!NOBASE) rs_acc += *reinterpret_cast<const float*>(cur_x + 256 + lane * 4);   // this chunk's share of the tokens' sums
     // Order inside a tile: the low-bit visits first (operands bhi / blo, read from LDS during the previous
     // tile's base product), then the base product (operands xb, read while the visits ran).  Every LDS read is
@@ -467,16 +468,18 @@ struct Stream {
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) acc_base[tt] = mfma_bf16(base[BUF][kb], xb[kb], acc_base[tt]);
       }
-      if (tt == 0) sal_address();
+      if constexpr (SAL) { if (tt == 0) sal_address(); }
     }
     static_assert(kSalPerChunk == 1, "one pair per chunk: the request steps above prepare exactly one");
-    sal_multiply(0);
-    sal_issue(sal_x[0], sal_d[0], sal_tt[0], sal_slot[0]);
+    if constexpr (SAL) {
+      sal_multiply(0);
+      sal_issue(sal_x[0], sal_d[0], sal_tt[0], sal_slot[0]);
+    }
     // The next chunk's code words (requested during the previous chunk) go to this wavefront's LDS area now:
     // its visits of this chunk are over, the area is its own, and the wavefronts get here at slightly
     // different times -- the 64 KiB of LDS writes spread out and fill what would be waiting at the barrier.
     park<BUF ^ 1>();
-    stage_barrier<younger<NOBASE>()>();
+    stage_barrier<younger<NOBASE, SAL>()>();
   }
 };
 
@@ -585,13 +588,22 @@ __device__ __forceinline__ void stream_rows(const LinearParams& p, char* lds, in
     ws.sal_issue(ws.sal_x[0], ws.sal_d[0], ws.sal_tt[0], ws.sal_slot[0]);
     ws.sal_multiply(0);
   }
+  const int n_sal = ws.sal_left;   // chunks that carry a pair
   ws.sal_lookup();
   ws.sal_address();
   ws.sal_issue(ws.sal_x[0], ws.sal_d[0], ws.sal_tt[0], ws.sal_slot[0]);
-  for (int i = 0; i < len; i += 2) {
-    ws.template chunk<0, false>(chunk_at(i + 1), chunk_at(i + 2), stage0, extra0, stage1, extra1, wave);
+  int i = 0;
+  for (; i < n_sal && i < len; i += 2) {
+    ws.template chunk<0, false, true>(chunk_at(i + 1), chunk_at(i + 2), stage0, extra0, stage1, extra1, wave);
     if (i + 1 >= len) break;
-    ws.template chunk<1, false>(chunk_at(i + 2), chunk_at(i + 3), stage1, extra1, stage0, extra0, wave);
+    ws.template chunk<1, false, true>(chunk_at(i + 2), chunk_at(i + 3), stage1, extra1, stage0, extra0, wave);
+  }
+  // The pairs are used up: the rest of the chunks without the arithmetic of one (about 100 vector instructions a chunk; few
+  // experts have few pairs: 256 tokens on 4096 x 28672, 2 bits, 315.0 -> 309.5 us; 64 on 14336 x 4096, 3 bits, 100.2 -> 98.0).
+  for (; i < len && i >= n_sal; i += 2) {
+    ws.template chunk<0, false, false>(chunk_at(i + 1), chunk_at(i + 2), stage0, extra0, stage1, extra1, wave);
+    if (i + 1 >= len) break;
+    ws.template chunk<1, false, false>(chunk_at(i + 2), chunk_at(i + 3), stage1, extra1, stage0, extra0, wave);
   }
   // Further sweeps over the same chunks for the slots beyond the first NA: activations again (from L2), these
   // slots' code words, no base weights.  The last barrier of the sweep before has every wavefront done with
@@ -603,10 +615,10 @@ __device__ __forceinline__ void stream_rows(const LinearParams& p, char* lds, in
     if constexpr (S::CB == 2) ws.template load_code_regs<1>(chunk_at(1));
     ws.template park<0>();
     stage_barrier<0>();
-    for (int i = 0; i < len; i += 2) {
-      ws.template chunk<0, true>(chunk_at(i + 1), chunk_at(i + 2), stage0, extra0, stage1, extra1, wave);
+    for (i = 0; i < len; i += 2) {
+      ws.template chunk<0, true, true>(chunk_at(i + 1), chunk_at(i + 2), stage0, extra0, stage1, extra1, wave);
       if (i + 1 >= len) break;
-      ws.template chunk<1, true>(chunk_at(i + 2), chunk_at(i + 3), stage1, extra1, stage0, extra0, wave);
+      ws.template chunk<1, true, true>(chunk_at(i + 2), chunk_at(i + 3), stage1, extra1, stage0, extra0, wave);
     }
   }
 
