@@ -47,18 +47,21 @@ namespace {
 // workgroups take about half as long again as the others') come first in g[] and in the workgroup ids, so that the
 // long workgroups start first and the short ones fill the compute units behind them -- in the order of the token
 // groups the last workgroups to start would be long ones, with most of the chip idle while they finish.
-// Within a class the ids are laid out so that the workgroups of one row group -- one per token group -- are
+// Within a class the ids are laid out so that the workgroups of one (row group, split) -- one per token group -- are
 // neighbours on one XCD: they start together, stream the same base weights at about the same time, and all but the
 // first find them in that XCD's L2.  Memory sees the base weights once per class rather than once per token group.
+// The (row group, split) pairs are dealt to the 8 XCDs one by one, so that none gets more than one pair above another: with the
+// row groups dealt out instead, each with all its splits, 34 row groups x 7 splits put 35 workgroups on the 32 compute
+// units of two XCDs, and the launch waited for a second round of three workgroups each (5128 -> 3204, 4 bits, 37 tokens of 5
+// experts: the kernel 41 us, now 22).
 constexpr int kMaxGroups = 4;
 struct LaunchParams {
   LinearParams g[kMaxGroups];
   int n_groups;
   int n_first;  // groups of the first class (g[0 .. n_first)), at least 1
   int rgs;      // row groups of the launch (all linears)
-  int rg8;      // ... in eights, rounded up
-  int wg_per_group;   // rg8 * 8 * nsplit.  Flat workgroup id within a class of m groups:
-                      // ((split * rg8 + rg / 8) * m + group) * 8 + rg % 8
+  int wg_per_group;   // rgs * nsplit, rounded up to a multiple of 8.  Flat workgroup id within a class of m groups, with
+                      // u = split * rgs + rg:  ((u / 8) * m + group) * 8 + u % 8
 };
 
 // ---- preparation ------------------------------------------------------------------------------------
@@ -502,7 +505,7 @@ struct LdsPlan {
 
 // One workgroup's work: row group rg, column split sp of token group p, with NA expert slots per sweep.
 template <int BITS, int TT, int NA, int NW>
-__device__ __forceinline__ void stream_rows(const LinearParams& p, char* lds, int rg, int sp) {
+__device__ __forceinline__ void stream_rows(const LinearParams& p, char* lds, int rg, int sp, int xcd) {
   const int tid = threadIdx.x, lane = tid & 63;
   // The wavefront index is the same in all 64 lanes; saying so keeps every value derived from it in scalar
   // registers and every branch on them a scalar branch.  MFMA ignores the EXEC mask, so an MFMA must never
@@ -537,11 +540,11 @@ __device__ __forceinline__ void stream_rows(const LinearParams& p, char* lds, in
   const uint32_t (&slot_tok)[TT] = ws.slot_tok;
 
   // The chunks of the range are visited from a start that differs from XCD to XCD (the sum does not care
-  // about the order; workgroups go round-robin to the 8 XCDs, so rg & 7 names the XCD): the XCDs do not
+  // about the order; workgroups go round-robin to the 8 XCDs): the XCDs do not
   // march in lockstep through the same columns, while the workgroups that share one XCD's L2 read the same
   // activation stage at about the same time and fetch it from memory once.
   const int len = c_end - c_begin;
-  const int rot = ((rg & 7) * len) >> 3;
+  const int rot = (xcd * len) >> 3;
   auto chunk_at = [&](int i) { i = i < len ? i : len - 1; int r = i + rot; r = r >= len ? r - len : r; return c_begin + r; };
   ws.begin_sweep(0);
   // Address translation warm-up.  The first loads of a workgroup go to as many pages as there are experts; one
@@ -690,21 +693,21 @@ __global__ __launch_bounds__(64 * NW) void k_delta_linear(const LaunchParams mp)
   const int first_wgs = mp.n_first * mp.wg_per_group;
   const bool second = (int)blockIdx.x >= first_wgs;
   const int b = second ? blockIdx.x - first_wgs : blockIdx.x, m = second ? mp.n_groups - mp.n_first : mp.n_first;
-  const int bq = b >> 3, bq2 = bq / m;
-  const int rg = (bq2 % mp.rg8) * 8 + (b & 7), sp = bq2 / mp.rg8;
-  if (rg >= mp.rgs) return;   // padding of the row groups to a multiple of eight
+  const int bq = b >> 3, bq2 = bq / m, xcd = b & 7;
+  const int u = bq2 * 8 + xcd, sp = u / mp.rgs, rg = u - sp * mp.rgs;
+  if (sp >= mp.g[0].nsplit) return;   // padding to a multiple of eight
   const LinearParams& p = mp.g[(second ? mp.n_first : 0) + bq - bq2 * m];
   if constexpr (NA > kMixFull) {
-    stream_rows<BITS, TT, NA, NW>(p, lds, rg, sp);
+    stream_rows<BITS, TT, NA, NW>(p, lds, rg, sp, xcd);
   } else {
     const int na = pass_slots(BITS, p.n_act);
     if (na == 4) {
-      stream_rows<BITS, TT, 4, NW>(p, lds, rg, sp);
+      stream_rows<BITS, TT, 4, NW>(p, lds, rg, sp, xcd);
     } else if constexpr (NA == kMixShort) {
-      stream_rows<BITS, TT, 8, NW>(p, lds, rg, sp);
+      stream_rows<BITS, TT, 8, NW>(p, lds, rg, sp, xcd);
     } else {
-      if (BITS <= 2 || na == kFull) stream_rows<BITS, TT, kFull, NW>(p, lds, rg, sp);
-      else stream_rows<BITS, TT, 8, NW>(p, lds, rg, sp);
+      if (BITS <= 2 || na == kFull) stream_rows<BITS, TT, kFull, NW>(p, lds, rg, sp, xcd);
+      else stream_rows<BITS, TT, 8, NW>(p, lds, rg, sp, xcd);
     }
   }
 }
@@ -784,11 +787,10 @@ Plan plan_for(int d_in, const int* d_out, int n_linears, bool pair) {
 
 // Expected time of a token group of few tokens, or of two in one launch, on the streaming path, us (for the choice between
 // the two paths; see few_tokens_us for the calls the numbers come from; 8 % off on those not used for them, two groups 13 %,
-// 9 % of it too low).  Workgroup ids go round-robin to 8 XCDs of 32 compute units and a row group's id names its XCD, so the
-// fullest XCD counts the rounds (81 row groups x 3 splits are 243 workgroups, and 33 on the first XCD: two rounds).  Salient
+// 9 % of it too low).  Workgroups are dealt to 8 XCDs of 32 compute units; the fullest XCD counts the rounds.  Salient
 // pairs that the chunks cannot carry are multiplied one after the other.
 double streaming_us(const LinearParams& a, const LinearParams* b, const Plan& pl, int rgs) {
-  const int groups = b ? 2 : 1, rounds = (groups * ((rgs + 7) / 8) * pl.nsplit + 31) / 32;
+  const int groups = b ? 2 : 1, rounds = (groups * ((rgs * pl.nsplit + 7) / 8) + 31) / 32;
   const int chunks = (a.n_chunks + pl.nsplit - 1) / pl.nsplit;
   auto sweeps = [](const LinearParams& p) { return p.n_act > full_slots(p.bits) ? 2 : 1; };
   const int left = (a.n_vis * a.n_sb + pl.nsplit - 1) / pl.nsplit - chunks * sweeps(a);
@@ -931,7 +933,6 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
   for (int sp = 0; sp <= pl.nsplit; ++sp) p0.c_split[sp] = (int16_t)((long)sp * p0.n_chunks / pl.nsplit);
   LaunchParams mp;
   mp.rgs = rgs;
-  mp.rg8 = (rgs + 7) / 8;
   // Token groups: up to 64 consecutive tokens that belong to at most kMaxSlots experts (the kernel sweeps the
   // chunks once per pass_slots of them).
   const int max_slots = kMaxSlots;
@@ -961,13 +962,13 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
     for (int g = 1; g < ng; ++g) same = same && body(g) == body(0);
     const int na = same ? body(0) : full ? kMixFull : kMixShort;
     mp.n_first = n_first > 0 ? n_first : ng;
-    mp.wg_per_group = mp.rg8 * 8 * pl.nsplit;
+    mp.wg_per_group = (rgs * pl.nsplit + 7) / 8 * 8;
     hipError_t e;
     k_prepare<<<dim3(items_max, ng), 256, 0, s>>>(mp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (c.ev_start && first_kernel && (e = hipEventRecord(c.ev_start, s)) != hipSuccess) return e;
     first_kernel = false;
-    const int grid = mp.rg8 * 8 * pl.nsplit * ng;
+    const int grid = mp.wg_per_group * ng;
     switch (d0.bits) {
       case 1: e = launch_nw<1>(mp, tt_max, na, pl.nw, grid, s); break;
       case 2: e = launch_nw<2>(mp, tt_max, na, pl.nw, grid, s); break;

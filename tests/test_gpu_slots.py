@@ -56,3 +56,21 @@ def test_small_groups_with_different_bodies_in_one_launch(counts, bits):
     oe = oracle_experts(wl)
     w64 = wl.w_base.double().cpu().numpy()
     check_rows(wl, ys[1], O.delta_linear(wl.x.double().cpu().numpy(), w64, oe, wl.seg_offsets), oe, w64)
+
+
+@pytest.mark.parametrize("d_in,d_out", [(2184, 1096), (648, 72), (1032, 2184)])
+@pytest.mark.parametrize("counts", [[37], [5] * 13, [64, 64, 3], [64] + [16] * 4 + [4] * 16 + [21]])
+def test_every_row_group_and_split_is_computed_once(d_in, d_out, counts):
+    """Numbers of (row group, split) pairs that are no multiple of the 8 dies they are dealt to, with one to four token groups
+    in a launch: the oracle's bars, and bit for bit the result of one launch per group."""
+    wl = synth.small_case(d_in, d_out, offsets(counts), 24, 2, seed=7, device=DEV)
+    w_t = mes.mes_pack_base(wl.w_base)
+    ge = [mes.mes_pack_delta(ex.delta, ex.salient_idx, 2) for ex in wl.experts]
+    ys = []
+    for room in (64, 191):
+        y = torch.full((wl.x.shape[0], wl.d_out), float("nan"), dtype=torch.bfloat16, device=DEV)
+        ys.append(mes.DeltaLinear(w_t, ge, max_tokens=room)(wl.x, wl.seg_offsets, y))
+    assert torch.equal(ys[0], ys[1])
+    oe = oracle_experts(wl)
+    w64 = wl.w_base.double().cpu().numpy()
+    check_rows(wl, ys[1], O.delta_linear(wl.x.double().cpu().numpy(), w64, oe, wl.seg_offsets), oe, w64)
