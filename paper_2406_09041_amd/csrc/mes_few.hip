@@ -86,30 +86,37 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
   const bool live = jt < n_tiles;                           // teams past the last row tile keep the barriers company
   jt = live ? jt : n_tiles - 1;
   const PerLinear& L = p.lin[l];
+  // Steps, wanted at the end, when a load would be waited for: lane 4 a + q brings slot a's for rows 4 q .. 4 q + 3
+  // (unused slots alias slot 0); the lookup of the pointer goes first, so that it is not queued behind the weights.
+  // (4096 x 4096, 2 bits, 8 tokens of as many experts: 21.7 -> 21.2 us against steps loaded when they are needed; the
+  // 16-slot bodies have no registers for it: at 3 bits 3 of them spilled, 12 experts 35.3 -> 37.8 us.)
+  constexpr bool kStepsEarly = NA < kMaxSlots;
+  const float* const step_at = L.step[kStepsEarly ? lane >> 2 : 0];
 
   // Salient channels: every pair (visit, 32 ranks) has 1 KiB of activations, gathered once for the workgroup into LDS
   // (for each layer of a gated pair: they have salient sets of their own), and 1 KiB of weights per row tile.  The
   // wavefronts of a layer deal the gathers among themselves; the indices of the first few
-  // are requested before anything else, their activations after the first chunk's weights, and they go to LDS when the
-  // stream is over: nothing waits for them.
-  const int n_pairs = p.n_vis * p.n_sb;
+  // are requested behind the first chunk's weights, their activations once all the first weights are asked for (the gathers
+  // wait for their indices; 5600 -> 1000, 4 bits, 128 channels, 17.9 -> 16.8 us against indices first and the gathers before the
+  // second chunk), and they go to LDS when the stream is over.
+  const int n_pairs = p.n_vis * p.n_sb, n_sb = p.n_sb;
+  // visit of a pair = pair / n_sb, by a multiplication (the dozen divisions took about 1 % of a call): the reciprocal in 16 bits
+  // is too large by less than 2^-16, and pair times that less than 1 / n_sb, as pair and n_sb are at most kFewPairs
+  const int inv_sb = n_sb > 0 ? (65535 + n_sb) / n_sb : 0;
+  auto visit_of = [&](int pair) { return pair * inv_sb >> 16; };
   const int gw = p.pair ? (team >> 1) * team_waves + kw : wave, gathers = p.pair ? NW / 2 : NW;
   u32x4 (*const sal_at)[64] = p.pair && l ? sal_lds + kFewPairs / 2 : sal_lds;
   constexpr int kGather = 4, kEarly = 2;                   // pairs per wavefront gathered, and weights of pairs requested, up front
   int sal_idx[kGather][8];
   auto request_indices = [&](int pair, int (&idx)[8]) {
-    const int32_t* si = L.sidx[p.vis_info[pair / p.n_sb] & 0xff];
+    const int v = visit_of(pair);
+    const int32_t* si = L.sidx[p.vis_info[v] & 0xff];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int r = 32 * (pair % p.n_sb) + 8 * g + e;
+      const int r = 32 * (pair - v * n_sb) + 8 * g + e;
       idx[e] = si[r < p.k ? r : p.k - 1];
     }
   };
-  if (n_pairs > 0) {
-#pragma unroll
-    for (int q = 0; q < kGather; ++q)
-      if (gw + gathers * q < n_pairs) request_indices(gw + gathers * q, sal_idx[q]);
-  }
 
   const char* const x_at = keep(reinterpret_cast<const char*>(p.x + (size_t)p.t0 * p.d_in));
   uint32_t x_off[TT];       // lanes past the last token read the group's first: their columns of the products are never stored
@@ -208,10 +215,21 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
   const int mine = kw < n_chunks ? (n_chunks - kw + team_waves - 1) / team_waves : 0;
   auto chunk_at = [&](int i) { return kw + team_waves * i; };
   request(buf[0], chunk_at(0));
+  if (n_pairs > 0) {
+#pragma unroll
+    for (int q = 0; q < kGather; ++q)
+      if (gw + gathers * q < n_pairs) request_indices(gw + gathers * q, sal_idx[q]);
+  }
+#pragma unroll
+  for (int u = 1; u < AHEAD; ++u) request(buf[u], chunk_at(u));
+  const int st_j = 16 * jt + 4 * (lane & 3);
+  typedef __attribute__((address_space(1))) const f32x4 gf4;   // (a generic load would count as an LDS access as well)
+  f32x4 st_v = {0, 0, 0, 0};
+  if constexpr (kStepsEarly) st_v = *reinterpret_cast<gf4*>(gptr(step_at + (st_j < L.d_out ? st_j : 0)));
   uint32_t sal_h[kGather][8];
   typedef __attribute__((address_space(1))) const uint16_t g16;
   auto request_gather = [&](int pair, const int (&idx)[8], uint32_t (&h)[8]) {
-    const int info = p.vis_info[pair / p.n_sb], a = info & 0xff, tl = 16 * (info >> 8) + n;
+    const int info = p.vis_info[visit_of(pair)], a = info & 0xff, tl = 16 * (info >> 8) + n;
     if (tl < p.lo[a] || tl >= p.hi[a]) return;              // other experts' tokens: zero when they are stored
     const uint32_t row_off = (uint32_t)tl * (uint32_t)d_in * 2u;
 #pragma unroll
@@ -220,7 +238,7 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
   };
   // (the activations of other experts' tokens and of ranks past k count as zero)
   auto store_gather = [&](int pair, const uint32_t (&h)[8]) {
-    const int info = p.vis_info[pair / p.n_sb], a = info & 0xff, tl = 16 * (info >> 8) + n, r0 = 32 * (pair % p.n_sb) + 8 * g;
+    const int v = visit_of(pair), info = p.vis_info[v], a = info & 0xff, tl = 16 * (info >> 8) + n, r0 = 32 * (pair - v * n_sb) + 8 * g;
     const bool inm = tl >= p.lo[a] && tl < p.hi[a];
     u32x4 x;
 #pragma unroll
@@ -233,21 +251,19 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
     for (int q = 0; q < kGather; ++q)
       if (gw + gathers * q < n_pairs) request_gather(gw + gathers * q, sal_idx[q], sal_h[q]);
   }
-#pragma unroll
-  for (int u = 1; u < AHEAD; ++u) request(buf[u], chunk_at(u));
   // weights of one pair and the row's step of its expert, as loaded; pairs past the last one repeat it
   struct PairLoad { u32x4 d; float step; };
   PairLoad pl[kEarly];
   auto request_pair = [&](int pair, PairLoad& o) {
     pair = pair < n_pairs ? pair : n_pairs - 1;
-    const int v = pair / p.n_sb, a = p.vis_info[v] & 0xff;
-    o.d = ld128(L.sal[a] + ((size_t)jt * p.n_sb + (pair - v * p.n_sb)) * 1024, (uint32_t)lane * 16u);
+    const int v = visit_of(pair), a = p.vis_info[v] & 0xff;
+    o.d = ld128(L.sal[a] + ((size_t)jt * n_sb + (pair - v * n_sb)) * 1024, (uint32_t)lane * 16u);
     const int row_n = 16 * jt + n;
     o.step = L.step[a][row_n < L.d_out ? row_n : L.d_out - 1];   // (rows past the end are never stored)
   };
   // acc_base += (D + z step) x as two bf16 pieces, exactly as the streaming kernel has it
   auto multiply_pair = [&](int pair, const PairLoad& o) {
-    const int tile = p.vis_info[pair / p.n_sb] >> 8;
+    const int tile = p.vis_info[visit_of(pair)] >> 8;
     const u32x4 x = sal_at[pair][lane];
     const f16x8 dh = __builtin_bit_cast(f16x8, o.d);
     const float zs = p.z * o.step;
@@ -310,18 +326,30 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
   // Zero point and step, then the sum over the wavefronts.  The matrix instructions issued from assembly blocks get
   // the wait states a result needs before vector instructions may read it.
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-  __syncthreads();                                          // every wavefront is done with its fp8 pieces
+  f32x4 stepv[TT];                                          // (tokens past the last one have no slot and are never stored)
+  if constexpr (kStepsEarly) {
+    wave_lds_fence();                                       // this wavefront is done with its fp8 pieces
+    *reinterpret_cast<f32x4*>(my_fp8 + (lane >> 2) * 64 + (lane & 3) * 16) = st_v;
+    wave_lds_fence();
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) stepv[tt] = *reinterpret_cast<const f32x4*>(my_fp8 + (slot_tok[tt] & (kMaxSlots - 1)) * 64 + g * 16);
+  } else {
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      const int j = 16 * jt + 4 * g;
+      stepv[tt] = f32x4{0, 0, 0, 0};
+      if (slot_tok[tt] != 0xffu && j < L.d_out) stepv[tt] = *reinterpret_cast<const f32x4*>(L.step[slot_tok[tt]] + j);
+    }
+  }
+  __syncthreads();                                          // ... and every wavefront, and with its steps
   f32x4* const part = reinterpret_cast<f32x4*>(&fp8_lds[0][0]);   // [wavefront][tile][lane]
 #pragma unroll
   for (int tt = 0; tt < TT; ++tt) {
-    f32x4 stepv = {0, 0, 0, 0};
-    const int j = 16 * jt + 4 * g;
-    if (slot_tok[tt] != 0xffu && j < L.d_out) stepv = *reinterpret_cast<const f32x4*>(L.step[slot_tok[tt]] + j);
     float r = rs[tt] + __shfl_xor(rs[tt], 16);
     r += __shfl_xor(r, 32);
     f32x4 o;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) o[v] = acc_base[tt][v] + stepv[v] * (acc_raw[tt][v] - p.z * r);
+    for (int v = 0; v < 4; ++v) o[v] = acc_base[tt][v] + stepv[tt][v] * (acc_raw[tt][v] - p.z * r);
     part[(wave * TT + tt) * 64 + lane] = o;
   }
   __syncthreads();
