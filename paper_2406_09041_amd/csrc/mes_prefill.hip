@@ -114,7 +114,7 @@ struct TileParams {
 // segment's expert with ranks 32 kb + 8 (l >> 4) ..; zero beyond the segment's last token, the last channel or rank.
 // Bound by memory latency: a lane has four loads in flight, the wavefront 256 bytes of each of 16 rows.  (Gathers take a
 // cycle per lane and a second trip: four k blocks of them in one wavefront were the launch's last to end, 1536 tokens x 4096
-// channels, 128 salient ones, 19.5 us against TILE_NOW.)
+// channels, 128 salient ones, 19.5 us against 9.7.)
 __global__ __launch_bounds__(256) void k_prefill_tile_x(const TileParams p) {
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const long w = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
