@@ -632,6 +632,10 @@ bool prefill_plan(PrefillPlan& best, const int* seg_tiles, int n_seg, const int*
       consider(24, true, 0);
       consider(16, true, 0);
       if (tiles * (long)n_rg < 12 * kMaxWorkgroups) consider(12, true, 0);
+      // launches that blocks of 8 or 4 tiles do not make longer than about a round: the chip is idle otherwise, and a block of 4
+      // tiles takes 1 us a step where one of 12 takes 1.5 (1648 -> 1920, 702 tokens 27.9 us with at least 11 tiles, now 22.4)
+      if (tiles * (long)n_rg < 12 * kMaxWorkgroups) consider(8, true, 0);
+      if (tiles * (long)n_rg < 8 * kMaxWorkgroups) consider(4, true, 0);
     }
   }
   return best_time < 1e30;

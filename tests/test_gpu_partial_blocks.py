@@ -16,3 +16,13 @@ def test_partial_token_blocks(d_in, d_out, k, bits, lengths):
     for n in lengths:
         off.append(off[-1] + n)
     run_case(synth.small_case(d_in, d_out, off, k, bits, seed=len(lengths)))
+
+
+@pytest.mark.parametrize("d_in,d_out,k,bits", [(1480, 360, 64, 4), (520, 1928, 0, 2), (2056, 72, 33, 1), (896, 1032, 8, 3)])
+@pytest.mark.parametrize("lengths", [[193], [270, 345], [200, 331, 449]])
+def test_small_token_blocks(d_in, d_out, k, bits, lengths):
+    """Launches that leave most of the chip idle are cut into blocks of up to 4 or 8 token tiles, also with the contraction split."""
+    off = [0]
+    for n in lengths:
+        off.append(off[-1] + n)
+    run_case(synth.small_case(d_in, d_out, off, k, bits, seed=3 + len(lengths)))
