@@ -521,7 +521,10 @@ __global__ __launch_bounds__(64 * kWaves) void k_prefill_reduce(const PrefillPar
 // it do not depend on the steps.
 constexpr double kBlockTime[2][8] = {{44, 56, 62, 79, 92, 100, 115, 122}, {44, 59, 68, 82, 106, 109, 130, 136}};
 constexpr double kFixedTime = 11;
-inline double block_time(int rt, int tiles, int steps) {
+// A launch of no more workgroups than compute units is not slowed down so much by its bigger blocks (1 bit, 3016 -> 696, 114
+// tiles, 25 steps, 4 / 8 / 12 / 16 tiles: 31 / 35 / 39 / 43 us; 4 bits, 1480 -> 2996, 32 tiles, 13 steps: 20 / 22 / 25 / 28).
+inline double block_time(int rt, int tiles, int steps, bool alone) {
+  if (alone && tiles <= 16) return 7.4 + steps * (rt == 8 ? 0.94 + 0.16 * ((tiles - 1) / 4) : 0.91 + 0.14 * ((tiles - 1) / 4));
   return kFixedTime + (kBlockTime[rt - 7][(tiles - 1) / 4] - kFixedTime) * steps / 33.0;
 }
 
@@ -541,10 +544,11 @@ double launch_time(const Blocks& bl, int n_rg, int rt, int steps, int n_split) {
   int n = 1;
   pool[0] = {0.0, kMaxWorkgroups};
   double end = 0.0;
+  const bool alone = (long)bl.n * n_rg * n_split <= kMaxWorkgroups;
   for (int i = 0; i < bl.n;) {
     int same = i + 1;
     while (same < bl.n && (bl.b[same].tiles - 1) / 4 == (bl.b[i].tiles - 1) / 4) ++same;
-    const double t = block_time(rt, bl.b[i].tiles, steps);
+    const double t = block_time(rt, bl.b[i].tiles, steps, alone);
     for (long left = (long)(same - i) * n_rg * n_split; left > 0;) {
       int first = 0;
       for (int q = 1; q < n; ++q) first = pool[q].at < pool[first].at ? q : first;
@@ -612,8 +616,8 @@ bool prefill_plan(PrefillPlan& best, const int* seg_tiles, int n_seg, const int*
       const long wgs = (long)n_rg * bl.n;
       for (int want = 1; want <= 8 && want * wgs <= kMaxWorkgroups && (want == 1 || 4 * want <= steps); ++want) {
         const int per = (steps + want - 1) / want, n_split = (steps + per - 1) / per;
-        // (partial sums: written and read at about 4 TB/s, and another launch)
-        const double t = launch_time(bl, n_rg, rt, per, n_split) + (n_split > 1 ? 4.0 + n_split * elements * 8.0 / 4e6 : 0.0);
+        // (partial sums: written and read at about 9 TB/s, and another launch)
+        const double t = launch_time(bl, n_rg, rt, per, n_split) + (n_split > 1 ? 4.0 + n_split * elements * 8.0 / 9e6 : 0.0);
         if (t < 0.99 * best_time) { best_time = t; best.rt = rt; best.n_split = n_split; best.steps_per_split = per; best.blocks = bl; }
       }
       if (wgs > kMaxWorkgroups) {
