@@ -10,6 +10,7 @@
 #include <type_traits>
 
 #include "mes_internal.h"
+#include "mes_prefill_plan.h"
 
 namespace mes {
 namespace {
@@ -21,11 +22,6 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 
-constexpr int kMaxWorkgroups = 256;  // one workgroup per compute unit; launches of fewer split the contraction
-
-constexpr int kMaxSegs = 8;          // long segments (experts) served by one launch
-constexpr int kMaxBlocks = 128;      // token blocks of one launch
-constexpr int kBlockTiles = 32;      // token tiles (16 tokens) of a full block
 constexpr int kWaves = 8;
 
 // Per layer of a call; per segment (= per expert with a long segment): codes, step, sal.
@@ -43,7 +39,7 @@ struct PrefillParams {
   PrefillLinear lin[MES_MAX_FUSED];
   int t_begin[kMaxSegs], t_end[kMaxSegs];   // a segment's rows of x and y
   int tile0[kMaxSegs];                      // its first token tile in xt
-  uint32_t blocks[kMaxBlocks];              // token blocks, the longest first: see token_block()
+  BlockEntry blocks[kMaxBlocks];            // token blocks, the longest first
   const u32x4* xt;          // the segments' activations in fragment order: [k block][token tile][64 lanes] x 16 bytes,
                             // k blocks 0 .. 4 n_chunks - 1 the input channels, then 4 n_ssteps per layer of gathered salient ones
   f32x4* tiles;             // split contraction only: accumulator tiles, [split][row group][token block][4 RT][thread]
@@ -51,13 +47,6 @@ struct PrefillParams {
   float z;
 };
 
-// A token block: its segment, its first token tile (in xt) and how many it has.
-struct TokenBlock { int sg, tile0, tiles; };
-inline uint32_t pack_block(int sg, int tile0, int tiles) { return (uint32_t)sg | (uint32_t)tiles << 3 | (uint32_t)tile0 << 9; }
-__device__ __forceinline__ TokenBlock token_block(const PrefillParams& p, int b) {
-  const uint32_t v = p.blocks[b];
-  return TokenBlock{(int)(v & 7), (int)(v >> 9), (int)((v >> 3) & 63)};
-}
 // Token tiles a wavefront takes of a block: of up to 16 tiles four columns of wavefronts share the tokens, and the two of a
 // column the k blocks; of more, eight.
 __host__ __device__ constexpr int wave_tiles(int tiles) { return tiles > 24 ? 4 : tiles > 16 ? 3 : (tiles + 3) / 4; }
@@ -301,16 +290,17 @@ __device__ __forceinline__ void multiply_rows(const PrefillParams& p, const Pref
   };
 
   // ---- activations: this wavefront's k blocks one after the other, the last one repeated
-  const uint64_t x_stride = (uint64_t)p.n_tq * 1024;     // from a k block to the next
+  const uint64_t x_stride = tile_offset(p.n_tq);         // from a k block to the next
   const uint64_t x_jump = (uint64_t)(4 * p.n_ssteps * l) * x_stride;   // over the other layers' salient channels
   uint32_t toff[TA];
 #pragma unroll
   for (int tt = 0; tt < TT; ++tt) {                      // tiles past the block's last one repeat it, and are not stored
-    const int t = TT * col + tt;
-    toff[tt] = __builtin_amdgcn_readfirstlane((uint32_t)(tb.tile0 + (t < tb.tiles ? t : tb.tiles - 1)) * 1024u);
+    const int t = TT * col + tt;                         // (offsets within the block: a launch may have more than 2^22 tiles)
+    toff[tt] = __builtin_amdgcn_readfirstlane((uint32_t)(t < tb.tiles ? t : tb.tiles - 1) * (uint32_t)kTileBytes);
   }
   u32x4 xb[XD][TA];
-  uint64_t x_at = uniform64(reinterpret_cast<uint64_t>(p.xt) + (uint64_t)(4 * st0 + NBW * half) * x_stride + (st0 >= n_chunks ? x_jump : 0));
+  uint64_t x_at = uniform64(reinterpret_cast<uint64_t>(p.xt) + tile_offset(tb.tile0) + (uint64_t)(4 * st0 + NBW * half) * x_stride +
+                            (st0 >= n_chunks ? x_jump : 0));
   int x_left = (st1 - st0) * NBW - 1, x_cross = (n_chunks - st0) * NBW;   // blocks behind the next one; until the salient ones
   auto request_x = [&](int j, int set) {                 // j: the block's number among those of its step
 #pragma unroll
@@ -473,7 +463,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_prefill_fused(const PrefillPara
   const int st1 = st0 + p.steps_per_split < n_steps ? st0 + p.steps_per_split : n_steps;
   const int l = linear_of(p, rg);
   const PrefillLinear& L = p.lin[l];
-  const TokenBlock tb = token_block(p, blk);
+  const TokenBlock tb = token_block(p.blocks[blk]);
   if (tb.tiles > 16) {
     const int tt = wave_tiles(tb.tiles);
     if (tt * wave >= tb.tiles) multiply_rows<BITS, RT, 0, 1>(p, L, l, tb, lds, wave, rg, blk, st0, st1);   // builds only
@@ -498,7 +488,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_prefill_reduce(const PrefillPar
   constexpr int NT = 64 * kWaves;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
   const int rg = blockIdx.x, blk = blockIdx.y, rt = blockIdx.z >> 2, tt = blockIdx.z & 3;
-  const TokenBlock tb = token_block(p, blk);
+  const TokenBlock tb = token_block(p.blocks[blk]);
   const int TT = wave_tiles(tb.tiles), tile = TT * wave + tt;
   if (tt >= TT || tile >= tb.tiles) return;
   const PrefillLinear& L = p.lin[linear_of(p, rg)];
@@ -513,136 +503,6 @@ __global__ __launch_bounds__(64 * kWaves) void k_prefill_reduce(const PrefillPar
     pk.y = pack_bf16(o[2], o[3]);
     *reinterpret_cast<uint2*>(L.y + (size_t)t * L.d_out + j) = pk;
   }
-}
-
-// ---- plan -----------------------------------------------------------------------------------------------
-
-// Time of a workgroup with up to 4, 8, ... 32 token tiles, us, 33 steps at 2 bits on a full chip, by row tiles (7, 8); 11 of
-// it do not depend on the steps.
-constexpr double kBlockTime[2][8] = {{44, 56, 62, 79, 92, 100, 115, 122}, {44, 59, 68, 82, 106, 109, 130, 136}};
-constexpr double kFixedTime = 11;
-// A launch of no more workgroups than compute units is not slowed down so much by its bigger blocks (1 bit, 3016 -> 696, 114
-// tiles, 25 steps, 4 / 8 / 12 / 16 tiles: 31 / 35 / 39 / 43 us; 4 bits, 1480 -> 2996, 32 tiles, 13 steps: 20 / 22 / 25 / 28).
-inline double block_time(int rt, int tiles, int steps, bool alone) {
-  if (alone && tiles <= 16) return 7.4 + steps * (rt == 8 ? 0.94 + 0.16 * ((tiles - 1) / 4) : 0.91 + 0.14 * ((tiles - 1) / 4));
-  return kFixedTime + (kBlockTime[rt - 7][(tiles - 1) / 4] - kFixedTime) * steps / 33.0;
-}
-
-struct Blocks {
-  TokenBlock b[kMaxBlocks];
-  int n;
-};
-
-struct PrefillPlan {
-  int rt, n_split, steps_per_split;
-  Blocks blocks;
-};
-
-// When the compute units are done that take, from a list, every token block's n_rg workgroups, each as soon as one is free.
-double launch_time(const Blocks& bl, int n_rg, int rt, int steps, int n_split) {
-  struct { double at; int units; } pool[48];                   // compute units by the time they are free
-  int n = 1;
-  pool[0] = {0.0, kMaxWorkgroups};
-  double end = 0.0;
-  const bool alone = (long)bl.n * n_rg * n_split <= kMaxWorkgroups;
-  for (int i = 0; i < bl.n;) {
-    int same = i + 1;
-    while (same < bl.n && (bl.b[same].tiles - 1) / 4 == (bl.b[i].tiles - 1) / 4) ++same;
-    const double t = block_time(rt, bl.b[i].tiles, steps, alone);
-    for (long left = (long)(same - i) * n_rg * n_split; left > 0;) {
-      int first = 0;
-      for (int q = 1; q < n; ++q) first = pool[q].at < pool[first].at ? q : first;
-      const int take = left < pool[first].units ? (int)left : pool[first].units;
-      const double done = pool[first].at + t;
-      end = done > end ? done : end;
-      left -= take;
-      if (take == pool[first].units || n == (int)(sizeof(pool) / sizeof(pool[0]))) {
-        pool[first].at = done;                                 // (no room to tell them apart: all of them)
-      } else {
-        pool[first].units -= take;
-        pool[n++] = {done, take};
-      }
-    }
-    i = same;
-  }
-  return end;
-}
-
-// The segments' tokens as blocks of at most `most` tiles, the longest first.  even: a segment's blocks alike, else full ones
-// and what is left.  The last `halved` full blocks become two each.  False: too many for one launch.
-bool cut_blocks(Blocks& bl, const int* seg_tiles, int n_seg, int most, bool even, int halved) {
-  bl.n = 0;
-  int tile0 = 0, full = 0;
-  if (halved > 0)
-    for (int i = 0; i < n_seg; ++i) full += seg_tiles[i] / kBlockTiles;
-  for (int i = 0; i < n_seg; ++i) {
-    const int r = seg_tiles[i], nb = (r + most - 1) / most;
-    for (int b = 0; b < nb; ++b) {
-      const int lo = even ? (int)((long)r * b / nb) : b * most, end = even ? (int)((long)r * (b + 1) / nb) : lo + most, hi = end < r ? end : r;
-      const bool halve = halved > 0 && hi - lo == kBlockTiles && full-- <= halved;
-      if (bl.n + (halve ? 2 : 1) > kMaxBlocks) return false;
-      const int mid = halve ? (lo + hi) / 2 : hi;
-      bl.b[bl.n++] = {i, tile0 + lo, mid - lo};
-      if (halve) bl.b[bl.n++] = {i, tile0 + mid, hi - mid};
-    }
-    tile0 += r;
-  }
-  for (int i = 1; i < bl.n; ++i) {                             // insertion: stable, and nearly sorted already
-    const TokenBlock v = bl.b[i];
-    int j = i;
-    for (; j > 0 && (bl.b[j - 1].tiles - 1) / 4 < (v.tiles - 1) / 4; --j) bl.b[j] = bl.b[j - 1];
-    bl.b[j] = v;
-  }
-  return true;
-}
-
-// Row tiles per workgroup, token blocks and column splits of a launch: whichever of a few candidates is expected to be done
-// first.  A workgroup has a compute unit to itself, so what counts is how the workgroups' times fill the 256 of them.
-// seg_tiles: 16-token tiles of every segment; d_out: of every layer.
-bool prefill_plan(PrefillPlan& best, const int* seg_tiles, int n_seg, const int* d_out, int n_linears, int steps) {
-  double best_time = 1e30;
-  Blocks bl;
-  double elements = 0;
-  for (int l = 0; l < n_linears; ++l) elements += d_out[l];
-  int tiles = 0;
-  for (int i = 0; i < n_seg; ++i) tiles += seg_tiles[i];
-  elements *= 16.0 * tiles;
-  for (int rt = 8; rt >= 7; --rt) {
-    int n_rg = 0;
-    for (int l = 0; l < n_linears; ++l) n_rg += (ceil_to(d_out[l], kRowPad) / 16 + rt - 1) / rt;
-    auto consider = [&](int most, bool even, int halved) {
-      if (!cut_blocks(bl, seg_tiles, n_seg, most, even, halved)) return;
-      // fewer workgroups than compute units: share the steps out, at least four to each
-      const long wgs = (long)n_rg * bl.n;
-      for (int want = 1; want <= 8 && want * wgs <= kMaxWorkgroups && (want == 1 || 4 * want <= steps); ++want) {
-        const int per = (steps + want - 1) / want, n_split = (steps + per - 1) / per;
-        // (partial sums: written and read at about 9 TB/s, and another launch)
-        const double t = launch_time(bl, n_rg, rt, per, n_split) + (n_split > 1 ? 4.0 + n_split * elements * 8.0 / 9e6 : 0.0);
-        if (t < 0.99 * best_time) { best_time = t; best.rt = rt; best.n_split = n_split; best.steps_per_split = per; best.blocks = bl; }
-      }
-      if (wgs > kMaxWorkgroups) {
-        const double t = launch_time(bl, n_rg, rt, steps, 1);
-        if (t < 0.99 * best_time) { best_time = t; best.rt = rt; best.n_split = 1; best.steps_per_split = steps; best.blocks = bl; }
-      }
-    };
-    consider(32, false, 0);
-    int full = 0;
-    for (int i = 0; i < n_seg; ++i) full += seg_tiles[i] / kBlockTiles;
-    const int over = (int)((long)full * n_rg % kMaxWorkgroups), h = over / n_rg;   // full workgroups of the last round
-    if (over > 0 && h > 0) consider(32, false, h);
-    if (over > 0 && h < full) consider(32, false, h + 1);
-    if (full * (long)n_rg < 4 * kMaxWorkgroups) {
-      consider(32, true, 0);
-      consider(24, true, 0);
-      consider(16, true, 0);
-      if (tiles * (long)n_rg < 12 * kMaxWorkgroups) consider(12, true, 0);
-      // launches that blocks of 8 or 4 tiles do not make longer than about a round: the chip is idle otherwise, and a block of 4
-      // tiles takes 1 us a step where one of 12 takes 1.5 (1648 -> 1920, 702 tokens 27.9 us with at least 11 tiles, now 22.4)
-      if (tiles * (long)n_rg < 12 * kMaxWorkgroups) consider(8, true, 0);
-      if (tiles * (long)n_rg < 8 * kMaxWorkgroups) consider(4, true, 0);
-    }
-  }
-  return best_time < 1e30;
 }
 
 template <int BITS>
@@ -752,12 +612,12 @@ hipError_t launch_prefill_segments(const mes_linear* lin, int n_linears, const i
         more = false;
         if (planned) {
           p.n_blk = pl.blocks.n;
-          for (int b = 0; b < p.n_blk; ++b) p.blocks[b] = pack_block(pl.blocks.b[b].sg, pl.blocks.b[b].tile0, pl.blocks.b[b].tiles);
+          for (int b = 0; b < p.n_blk; ++b) p.blocks[b] = block_entry(pl.blocks.b[b]);
         } else {
           p.n_blk = 0;
           while (sg < ns && p.n_blk < kMaxBlocks) {
             const int left = seg_tiles[sg] - tile, take = left < kBlockTiles ? left : kBlockTiles;
-            p.blocks[p.n_blk++] = pack_block(sg, p.tile0[sg] + tile, take);
+            p.blocks[p.n_blk++] = block_entry(TokenBlock{sg, p.tile0[sg] + tile, take});
             tile += take;
             if (tile == seg_tiles[sg]) { ++sg; tile = 0; }
           }
