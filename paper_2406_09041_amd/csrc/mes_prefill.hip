@@ -23,6 +23,8 @@ typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 
 constexpr int kWaves = 8;
+constexpr int kMaxGridY = 65535;     // token blocks of one launch
+static_assert(kRowPad == 64, "row_tiles() of the plan");
 
 // Per layer of a call; per segment (= per expert with a long segment): codes, step, sal.
 struct PrefillLinear {
@@ -39,11 +41,11 @@ struct PrefillParams {
   PrefillLinear lin[MES_MAX_FUSED];
   int t_begin[kMaxSegs], t_end[kMaxSegs];   // a segment's rows of x and y
   int tile0[kMaxSegs];                      // its first token tile in xt
-  BlockEntry blocks[kMaxBlocks];            // token blocks, the longest first
+  Blocks blocks;            // the token blocks
   const u32x4* xt;          // the segments' activations in fragment order: [k block][token tile][64 lanes] x 16 bytes,
                             // k blocks 0 .. 4 n_chunks - 1 the input channels, then 4 n_ssteps per layer of gathered salient ones
   f32x4* tiles;             // split contraction only: accumulator tiles, [split][row group][token block][4 RT][thread]
-  int n_linears, n_rg, n_blk, n_chunks, n_sb, n_ssteps, n_tq, steps_per_split, n_split;
+  int n_rg, n_blk, n_chunks, n_sb, n_ssteps, n_tq, steps_per_split, n_split;
   float z;
 };
 
@@ -51,11 +53,27 @@ struct PrefillParams {
 // column the k blocks; of more, eight.
 __host__ __device__ constexpr int wave_tiles(int tiles) { return tiles > 24 ? 4 : tiles > 16 ? 3 : (tiles + 3) / 4; }
 
-__device__ __forceinline__ int linear_of(const PrefillParams& p, int rg) {
-  int l = 0;
+// What a workgroup's start depends on, from the arguments in one trip: one after the other, as the compiler has it, each is
+// another 0.3 us of a call.
+struct Place {
+  TokenBlock tb;
+  int l, n_chunks, n_ssteps, steps_per_split;
+};
+__device__ __forceinline__ Place place_of(const PrefillParams& p, int rg, int blk) {
+  auto now = [](int& v) { asm volatile("" : "+s"(v)); };
+  BlockEntry e = p.blocks.list[blk < kMaxBlocks ? blk : 0];
+  int n_list = p.blocks.n_list, rg_end[MES_MAX_FUSED - 1];
+  Place at{{}, 0, p.n_chunks, p.n_ssteps, p.steps_per_split};
 #pragma unroll
-  for (int i = 0; i + 1 < MES_MAX_FUSED; ++i) l += (i + 1 < p.n_linears && rg >= p.lin[i].rg_end) ? 1 : 0;
-  return l;
+  for (int i = 0; i + 1 < MES_MAX_FUSED; ++i) rg_end[i] = p.lin[i].rg_end;
+  now(e.tile0); now(e.shape); now(n_list); now(at.n_chunks); now(at.n_ssteps); now(at.steps_per_split);
+#pragma unroll
+  for (int i = 0; i + 1 < MES_MAX_FUSED; ++i) {            // (of layers that are not there: all the launch's row groups)
+    now(rg_end[i]);
+    at.l += rg >= rg_end[i] ? 1 : 0;
+  }
+  at.tb = blk < n_list ? token_block(e) : unlisted_block(p.blocks, blk - n_list);
+  return at;
 }
 
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
@@ -458,12 +476,13 @@ __global__ __launch_bounds__(64 * kWaves) void k_prefill_fused(const PrefillPara
   __shared__ __attribute__((aligned(16))) u32x4 lds[RT * 4 * 4 * 64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rg = blockIdx.x, blk = blockIdx.y;
-  const int n_steps = p.n_chunks + p.n_ssteps;
-  const int st0 = blockIdx.z * p.steps_per_split;
-  const int st1 = st0 + p.steps_per_split < n_steps ? st0 + p.steps_per_split : n_steps;
-  const int l = linear_of(p, rg);
+  const Place at = place_of(p, rg, blk);
+  const int n_steps = at.n_chunks + at.n_ssteps;
+  const int st0 = blockIdx.z * at.steps_per_split;
+  const int st1 = st0 + at.steps_per_split < n_steps ? st0 + at.steps_per_split : n_steps;
+  const int l = at.l;
   const PrefillLinear& L = p.lin[l];
-  const TokenBlock tb = token_block(p.blocks[blk]);
+  const TokenBlock tb = at.tb;
   if (tb.tiles > 16) {
     const int tt = wave_tiles(tb.tiles);
     if (tt * wave >= tb.tiles) multiply_rows<BITS, RT, 0, 1>(p, L, l, tb, lds, wave, rg, blk, st0, st1);   // builds only
@@ -488,10 +507,11 @@ __global__ __launch_bounds__(64 * kWaves) void k_prefill_reduce(const PrefillPar
   constexpr int NT = 64 * kWaves;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
   const int rg = blockIdx.x, blk = blockIdx.y, rt = blockIdx.z >> 2, tt = blockIdx.z & 3;
-  const TokenBlock tb = token_block(p.blocks[blk]);
+  const Place at = place_of(p, rg, blk);
+  const TokenBlock tb = at.tb;
   const int TT = wave_tiles(tb.tiles), tile = TT * wave + tt;
   if (tt >= TT || tile >= tb.tiles) return;
-  const PrefillLinear& L = p.lin[linear_of(p, rg)];
+  const PrefillLinear& L = p.lin[at.l];
   f32x4 o = {0, 0, 0, 0};
   for (int sp = 0; sp < p.n_split; ++sp)
     o += p.tiles[((((size_t)sp * p.n_rg + rg) * p.n_blk + blk) * (RT * 4) + blockIdx.z) * NT + threadIdx.x];
@@ -561,7 +581,6 @@ hipError_t launch_prefill_segments(const mes_linear* lin, int n_linears, const i
     p.z = d.grid == MES_GRID_SYM ? (float)(1 << (d.bits - 1)) - 0.5f : (float)(1 << (d.bits - 1));
     const size_t xt_bytes = (size_t)4 * (n_chunks + per_launch * n_ssteps) * n_tq * 1024;
     p.tiles = reinterpret_cast<f32x4*>(ws + (xt_bytes + 255) / 256 * 256);
-    p.n_linears = per_launch;
     tp.x = reinterpret_cast<const uint16_t*>(x);
     tp.n_seg = ns;
     tp.k = d.k;
@@ -597,34 +616,20 @@ hipError_t launch_prefill_segments(const mes_linear* lin, int n_linears, const i
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
       PrefillPlan pl;
-      const bool planned = prefill_plan(pl, seg_tiles, ns, d_outs, per_launch, steps);
-      if (!planned) { pl.rt = 8; pl.n_split = 1; pl.steps_per_split = steps; }   // more blocks than one launch holds: full ones
+      prefill_plan(pl, seg_tiles, ns, d_outs, per_launch, steps);
       p.n_split = pl.n_split;
       p.steps_per_split = pl.steps_per_split;
+      p.blocks = pl.blocks;
+      p.n_blk = count(pl.blocks);
       p.n_rg = 0;
       for (int l = 0; l < MES_MAX_FUSED; ++l) {
         p.lin[l].rg_begin = p.n_rg;
         if (l < per_launch) p.n_rg += (p.lin[l].n_jt + pl.rt - 1) / pl.rt;
         p.lin[l].rg_end = p.n_rg;
       }
-      int sg = 0, tile = 0;                                     // (not planned: where the next launch's blocks begin)
-      for (bool more = true; more;) {
-        more = false;
-        if (planned) {
-          p.n_blk = pl.blocks.n;
-          for (int b = 0; b < p.n_blk; ++b) p.blocks[b] = block_entry(pl.blocks.b[b]);
-        } else {
-          p.n_blk = 0;
-          while (sg < ns && p.n_blk < kMaxBlocks) {
-            const int left = seg_tiles[sg] - tile, take = left < kBlockTiles ? left : kBlockTiles;
-            p.blocks[p.n_blk++] = block_entry(TokenBlock{sg, p.tile0[sg] + tile, take});
-            tile += take;
-            if (tile == seg_tiles[sg]) { ++sg; tile = 0; }
-          }
-          more = sg < ns;
-        }
-        for (int b = p.n_blk; b < kMaxBlocks; ++b) p.blocks[b] = p.blocks[0];   // never selected
-        const dim3 grid(p.n_rg, p.n_blk, pl.n_split);
+      for (int left = p.n_blk; left > 0;) {
+        const int blocks = left < kMaxGridY ? left : kMaxGridY;
+        const dim3 grid(p.n_rg, blocks, pl.n_split);
         if (ev_start && *first_kernel && (e = hipEventRecord(ev_start, s)) != hipSuccess) return e;
         *first_kernel = false;
         switch (d.bits) {
@@ -640,6 +645,8 @@ hipError_t launch_prefill_segments(const mes_linear* lin, int n_linears, const i
           if ((e = hipGetLastError()) != hipSuccess) return e;
         }
         if (ev_stop && (e = hipEventRecord(ev_stop, s)) != hipSuccess) return e;
+        left -= blocks;
+        p.blocks = behind(p.blocks, blocks);
       }
     }
   }

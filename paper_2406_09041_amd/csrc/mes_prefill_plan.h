@@ -9,7 +9,7 @@ namespace mes {
 
 constexpr int kMaxWorkgroups = 256;  // one workgroup per compute unit; launches of fewer split the contraction
 constexpr int kMaxSegs = 8;          // long segments (experts) served by one launch
-constexpr int kMaxBlocks = 128;      // token blocks of one launch
+constexpr int kMaxBlocks = 128;      // token blocks of a launch that are listed one by one
 constexpr int kBlockTiles = 32;      // token tiles (16 tokens) of a full block
 constexpr int kTileBytes = 1024;     // a token tile of one k block
 
@@ -22,6 +22,41 @@ struct TokenBlock { int sg, tile0, tiles; };
 struct BlockEntry { int tile0, shape; };
 constexpr BlockEntry block_entry(TokenBlock b) { return BlockEntry{b.tile0, b.sg | b.tiles << 3}; }
 constexpr TokenBlock token_block(BlockEntry e) { return TokenBlock{e.shape & (kMaxSegs - 1), e.tile0, e.shape >> 3}; }
+
+// The token blocks of a launch: the listed ones, the longest first -- or, of more blocks than the list holds, the listed ones (the
+// segments' last, partial blocks), then n_full blocks of full_tiles tiles, one segment's behind the other's, then n_half
+// halves of blocks that continue them.  One launch however many they are: launches of 128 blocks each leave part of the chip
+// idle at the end of each, all the time where the rows are one row group (80000 tokens of 4 experts on 512 -> 128:
+// 102 us, now 70.5).
+struct Blocks {
+  BlockEntry list[kMaxBlocks];
+  int n_list, n_full, n_half, full_tiles;
+  int first;                                   // of the blocks that are not listed, those before it are not this launch's
+  int full0[kMaxSegs], tile0[kMaxSegs];        // of a segment: its first full block, its first tile
+};
+constexpr int count(const Blocks& bl) { return bl.n_list + bl.n_full + bl.n_half; }
+constexpr TokenBlock unlisted_block(const Blocks& bl, int b) {   // b counts from the first one behind the list
+  b += bl.first;
+  int half = 0, tiles = bl.full_tiles;
+  if (b >= bl.n_full) {
+    half = (b - bl.n_full) & 1;
+    tiles /= 2;
+    b = bl.n_full + ((b - bl.n_full) >> 1);
+  }
+  int sg = 0;
+  for (int i = 1; i < kMaxSegs; ++i) sg += b >= bl.full0[i] ? 1 : 0;   // (segments without full blocks start where the next one does)
+  return TokenBlock{sg, bl.tile0[sg] + bl.full_tiles * (b - bl.full0[sg]) + half * tiles, tiles};
+}
+constexpr TokenBlock block_at(const Blocks& bl, int b) {
+  return b < bl.n_list ? token_block(bl.list[b]) : unlisted_block(bl, b - bl.n_list);
+}
+
+// The blocks behind the first n >= n_list ones (a grid has 65535 at most).
+constexpr Blocks behind(Blocks bl, int n) {
+  bl.first += n - bl.n_list;
+  bl.n_list = 0;
+  return bl;
+}
 
 // Bytes from the first tile of a k block to another.
 constexpr uint64_t tile_offset(int tile) { return (uint64_t)(uint32_t)tile * kTileBytes; }
@@ -37,10 +72,6 @@ inline double block_time(int rt, int tiles, int steps, bool alone) {
   return kFixedTime + (kBlockTime[rt - 7][(tiles - 1) / 4] - kFixedTime) * steps / 33.0;
 }
 
-struct Blocks {
-  TokenBlock b[kMaxBlocks];
-  int n;
-};
 
 struct PrefillPlan {
   int rt, n_split, steps_per_split;
@@ -53,12 +84,15 @@ inline double launch_time(const Blocks& bl, int n_rg, int rt, int steps, int n_s
   int n = 1;
   pool[0] = {0.0, kMaxWorkgroups};
   double end = 0.0;
-  const bool alone = (long)bl.n * n_rg * n_split <= kMaxWorkgroups;
-  for (int i = 0; i < bl.n;) {
-    int same = i + 1;
-    while (same < bl.n && (bl.b[same].tiles - 1) / 4 == (bl.b[i].tiles - 1) / 4) ++same;
-    const double t = block_time(rt, bl.b[i].tiles, steps, alone);
-    for (long left = (long)(same - i) * n_rg * n_split; left > 0;) {
+  const bool alone = (long)count(bl) * n_rg * n_split <= kMaxWorkgroups;
+  auto take_blocks = [&](int tiles, long blocks) {
+    const double t = block_time(rt, tiles, steps, alone);
+    for (long left = blocks * n_rg * n_split; left > 0;) {
+      if (n == 1 && left >= kMaxWorkgroups) {                  // whole rounds
+        end = pool[0].at += (double)(left / kMaxWorkgroups) * t;
+        left %= kMaxWorkgroups;
+        continue;
+      }
       int first = 0;
       for (int q = 1; q < n; ++q) first = pool[q].at < pool[first].at ? q : first;
       const int take = left < pool[first].units ? (int)left : pool[first].units;
@@ -72,43 +106,63 @@ inline double launch_time(const Blocks& bl, int n_rg, int rt, int steps, int n_s
         pool[n++] = {done, take};
       }
     }
+  };
+  auto listed = [&](int i) { return bl.list[i].shape >> 3; };
+  for (int i = 0; i < bl.n_list;) {
+    int same = i + 1;
+    while (same < bl.n_list && (listed(same) - 1) / 4 == (listed(i) - 1) / 4) ++same;
+    take_blocks(listed(i), same - i);
     i = same;
   }
+  if (bl.n_full > 0) take_blocks(bl.full_tiles, bl.n_full);
+  if (bl.n_half > 0) take_blocks(bl.full_tiles / 2, bl.n_half);
   return end;
 }
 
 // The segments' tokens as blocks of at most `most` tiles, the longest first.  even: a segment's blocks alike, else full ones
-// and what is left.  The last `halved` full blocks become two each.  False: too many for one launch.
-inline bool cut_blocks(Blocks& bl, const int* seg_tiles, int n_seg, int most, bool even, int halved) {
-  bl.n = 0;
-  int tile0 = 0, full = 0;
-  if (halved > 0)
-    for (int i = 0; i < n_seg; ++i) full += seg_tiles[i] / kBlockTiles;
+// and what is left.  The last `halved` full blocks (of kBlockTiles) become two each.
+inline void cut_blocks(Blocks& bl, const int* seg_tiles, int n_seg, int most, bool even, int halved) {
+  bl.n_full = bl.n_half = bl.n_list = bl.first = 0;
+  bl.full_tiles = most;
+  int tile0 = 0, full = 0, blocks = halved;
+  for (int i = 0; i < kMaxSegs; ++i) {
+    bl.full0[i] = full;
+    bl.tile0[i] = tile0;
+    if (i >= n_seg) continue;
+    full += seg_tiles[i] / most;
+    blocks += (seg_tiles[i] + most - 1) / most;
+    tile0 += seg_tiles[i];
+  }
+  const bool list_all = blocks <= kMaxBlocks;
+  if (!list_all) {
+    bl.n_full = full - halved;
+    bl.n_half = 2 * halved;
+  }
   for (int i = 0; i < n_seg; ++i) {
     const int r = seg_tiles[i], nb = (r + most - 1) / most;
-    for (int b = 0; b < nb; ++b) {
-      const int lo = even ? (int)((long)r * b / nb) : b * most, end = even ? (int)((long)r * (b + 1) / nb) : lo + most, hi = end < r ? end : r;
-      const bool halve = halved > 0 && hi - lo == kBlockTiles && full-- <= halved;
-      if (bl.n + (halve ? 2 : 1) > kMaxBlocks) return false;
+    for (int b = list_all ? 0 : r / most; b < nb; ++b) {
+      const bool alike = even && list_all;
+      const int lo = alike ? (int)((long)r * b / nb) : b * most, end = alike ? (int)((long)r * (b + 1) / nb) : lo + most, hi = end < r ? end : r;
+      const bool halve = list_all && halved > 0 && hi - lo == kBlockTiles && full-- <= halved;
       const int mid = halve ? (lo + hi) / 2 : hi;
-      bl.b[bl.n++] = {i, tile0 + lo, mid - lo};
-      if (halve) bl.b[bl.n++] = {i, tile0 + mid, hi - mid};
+      bl.list[bl.n_list++] = block_entry({i, bl.tile0[i] + lo, mid - lo});
+      if (halve) bl.list[bl.n_list++] = block_entry({i, bl.tile0[i] + mid, hi - mid});
     }
-    tile0 += r;
   }
-  for (int i = 1; i < bl.n; ++i) {                             // insertion: stable, and nearly sorted already
-    const TokenBlock v = bl.b[i];
+  auto size = [](const BlockEntry& e) { return ((e.shape >> 3) - 1) / 4; };
+  for (int i = 1; i < bl.n_list; ++i) {                        // insertion: stable, and nearly sorted already
+    const BlockEntry v = bl.list[i];
     int j = i;
-    for (; j > 0 && (bl.b[j - 1].tiles - 1) / 4 < (v.tiles - 1) / 4; --j) bl.b[j] = bl.b[j - 1];
-    bl.b[j] = v;
+    for (; j > 0 && size(bl.list[j - 1]) < size(v); --j) bl.list[j] = bl.list[j - 1];
+    bl.list[j] = v;
   }
-  return true;
+  for (int i = bl.n_list; i < kMaxBlocks; ++i) bl.list[i] = BlockEntry{0, 0};   // never selected
 }
 
 // Row tiles per workgroup, token blocks and column splits of a launch: whichever of a few candidates is expected to be done
 // first.  A workgroup has a compute unit to itself, so what counts is how the workgroups' times fill the 256 of them.
 // seg_tiles: 16-token tiles of every segment; d_out: of every layer.
-inline bool prefill_plan(PrefillPlan& best, const int* seg_tiles, int n_seg, const int* d_out, int n_linears, int steps) {
+inline void prefill_plan(PrefillPlan& best, const int* seg_tiles, int n_seg, const int* d_out, int n_linears, int steps) {
   double best_time = 1e30;
   Blocks bl;
   double elements = 0;
@@ -120,9 +174,9 @@ inline bool prefill_plan(PrefillPlan& best, const int* seg_tiles, int n_seg, con
     int n_rg = 0;
     for (int l = 0; l < n_linears; ++l) n_rg += (row_tiles(d_out[l]) + rt - 1) / rt;
     auto consider = [&](int most, bool even, int halved) {
-      if (!cut_blocks(bl, seg_tiles, n_seg, most, even, halved)) return;
+      cut_blocks(bl, seg_tiles, n_seg, most, even, halved);
       // fewer workgroups than compute units: share the steps out, at least four to each
-      const long wgs = (long)n_rg * bl.n;
+      const long wgs = (long)n_rg * count(bl);
       for (int want = 1; want <= 8 && want * wgs <= kMaxWorkgroups && (want == 1 || 4 * want <= steps); ++want) {
         const int per = (steps + want - 1) / want, n_split = (steps + per - 1) / per;
         // (partial sums: written and read at about 9 TB/s, and another launch)
@@ -151,7 +205,6 @@ inline bool prefill_plan(PrefillPlan& best, const int* seg_tiles, int n_seg, con
       if (tiles * (long)n_rg < 8 * kMaxWorkgroups) consider(4, true, 0);
     }
   }
-  return best_time < 1e30;
 }
 
 }  // namespace mes
