@@ -121,7 +121,8 @@ struct TileParams {
 // segment's expert with ranks 32 kb + 8 (l >> 4) ..; zero beyond the segment's last token, the last channel or rank.
 // Bound by memory latency: a lane has four loads in flight, the wavefront 256 bytes of each of 16 rows.  (Gathers take a
 // cycle per lane and a second trip: four k blocks of them in one wavefront were the launch's last to end, 1536 tokens x 4096
-// channels, 128 salient ones, 19.5 us against 9.7.)
+// channels, 128 salient ones, 19.5 us against 9.7.  The stored ranks are padded to 128: gathering the padding as well took
+// 64000 tokens x 512 channels, 8 salient ones, 2.5 to 4 us of a call of 54, small calls 0.5 us.)
 __global__ __launch_bounds__(256) void k_prefill_tile_x(const TileParams p) {
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const long w = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -146,15 +147,17 @@ __global__ __launch_bounds__(256) void k_prefill_tile_x(const TileParams p) {
   } else {
     const int l = (u - p.n_chunks) / (4 * p.n_ssteps), r0 = 32 * (u - p.n_chunks - 4 * l * p.n_ssteps) + 8 * g;
     const int32_t* sidx = p.sidx[l][sg];
-    int c[8];
-    uint32_t h[8];
+    uint32_t h[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (live && r0 < p.k) {                              // (lanes of ranks past the last one have nothing to gather)
+      int c[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) c[q] = sidx[r0 + q < p.k ? r0 + q : p.k - 1];
+      for (int q = 0; q < 8; ++q) c[q] = sidx[r0 + q < p.k ? r0 + q : p.k - 1];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const bool valid = live && r0 + q < p.k && (uint32_t)c[q] < (uint32_t)p.d_in;   // a corrupt list can never address outside the row
-      h[q] = row[valid ? c[q] : 0];
-      if (!valid) h[q] = 0;
+      for (int q = 0; q < 8; ++q) {
+        const bool valid = r0 + q < p.k && (uint32_t)c[q] < (uint32_t)p.d_in;   // a corrupt list can never address outside the row
+        h[q] = row[valid ? c[q] : 0];
+        if (!valid) h[q] = 0;
+      }
     }
     p.xt[((size_t)(3 * p.n_chunks + u) * p.n_tq + tq) * 64 + lane] =
         u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
