@@ -176,7 +176,7 @@ struct StepData {
 // halves of the work:
 //   multiply: every wavefront has token tiles of its own (TT of them) and takes all RT operands of its k blocks from LDS;
 //     activations come straight from memory, already in fragment order, XD - 1 k blocks ahead.  KS = 1: all 4 k blocks of a
-//     step, 8 x TT token tiles per workgroup.  KS = 2 (blocks of up to 16 tiles): wavefronts w and w + 4 share the token tiles
+//     step, 8 x TT token tiles per workgroup.  KS = 2 (blocks of up to 16 tiles, but see SHORT): wavefronts w and w + 4 share the token tiles
 //     and take two k blocks each; the sums meet in LDS at the end.  So both wavefronts of a SIMD multiply, whatever the block.
 //   build: wavefront w forms the operands (row tiles w / 4 + 2 i, k block w % 4) of the next step in the idle LDS buffer,
 //     bf16(W + (u - z) s) from a base fragment and a code word that were asked for a step before.  The vector instructions
@@ -191,7 +191,7 @@ __device__ __forceinline__ void multiply_rows(const PrefillParams& p, const Pref
   constexpr int NBW = 4 / KS;                            // k blocks of a step this wavefront multiplies
   constexpr int OPB = NOP / NBW;                         // operands built under one of them
   // sets of activation fragments: what the registers hold (512 of them per lane and SIMD, two wavefronts)
-  constexpr int XD = TT == 0 ? 1 : KS == 2 ? (TT <= 2 ? 4 : 2) : (RT == 7 && BITS <= 2 ? 4 : 3);
+  constexpr int XD = TT == 0 ? 1 : TT <= 2 ? 4 : KS == 2 ? 2 : (RT == 7 && BITS <= 2 ? 4 : 3);
   constexpr int U = NBW % XD == 0 ? 1 : (2 * NBW) % XD == 0 ? 2 : 3;   // steps until the sets come round
   static_assert((U * NBW) % XD == 0, "the sets are named at compile time");
   static_assert(NOP % NBW == 0, "every k block has the same number of operands to build");
@@ -473,7 +473,15 @@ __device__ __forceinline__ void multiply_rows(const PrefillParams& p, const Pref
 
 // Grid: (row groups of 16 RT output channels of all layers of the call, token blocks of up to 512 tokens, n_split); 512
 // threads, one workgroup per compute unit.
-template <int BITS, int RT>
+// SHORT: launches of short contractions, no block of more than 16 tiles, n_split = 1.  Blocks of 13 to 16 tiles take eight
+// columns of two tiles there: the operands are read from LDS twice as often, but there are no sums to exchange at the end, about 1 us.
+// (784 tokens x 7448, 3 / 13 / 25 / 33 / 49 steps, four columns 20.3 / 36.6 / 59.0 / 76.7 / 104.6 us, eight 19.4 / 34.7 / 58.5 /
+// 77.2 / 105.2; 490 x 12992, 1 bit, 3 / 17 / 33 / 49 steps 20.5 / 45.5 / 77.5 / 105.3 against 19.6 / 45.2 / 77.6 / 111.4.  Of 9 to
+// 12 tiles eight columns would leave two without tokens: slower from 5 steps on, 1470 x 4096, 3 bits, 22.0 against 22.3; in
+// split contractions the exchange is not what counts, 1024 x 1024 on 1024 channels 18.9 against 19.9.  Kernels of their
+// own: one more body in the others moves their spilled registers about, up to 20 % at 3 bits.)
+constexpr int kShortSteps = 20;
+template <int BITS, int RT, bool SHORT>
 __global__ __launch_bounds__(64 * kWaves) void k_prefill_fused(const PrefillParams p) {
   // two operand buffers of 4 RT KiB and, behind them, the operand too many; at the end 16 RT KiB of sums (KS = 2)
   __shared__ __attribute__((aligned(16))) u32x4 lds[RT * 4 * 4 * 64];
@@ -486,7 +494,18 @@ __global__ __launch_bounds__(64 * kWaves) void k_prefill_fused(const PrefillPara
   const int l = at.l;
   const PrefillLinear& L = p.lin[l];
   const TokenBlock tb = at.tb;
-  if (tb.tiles > 16) {
+  if constexpr (SHORT) {
+    if (tb.tiles > 12) {
+      if (2 * wave >= tb.tiles) multiply_rows<BITS, RT, 0, 1>(p, L, l, tb, lds, wave, rg, blk, st0, st1);   // builds only
+      else multiply_rows<BITS, RT, 2, 1>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
+    } else if (tb.tiles > 8) {
+      multiply_rows<BITS, RT, 3, 2>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
+    } else if (tb.tiles > 4) {
+      multiply_rows<BITS, RT, 2, 2>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
+    } else {
+      multiply_rows<BITS, RT, 1, 2>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
+    }
+  } else if (tb.tiles > 16) {
     const int tt = wave_tiles(tb.tiles);
     if (tt * wave >= tb.tiles) multiply_rows<BITS, RT, 0, 1>(p, L, l, tb, lds, wave, rg, blk, st0, st1);   // builds only
     else if (tt == 4) multiply_rows<BITS, RT, 4, 1>(p, L, l, tb, lds, wave, rg, blk, st0, st1);
@@ -530,8 +549,15 @@ __global__ __launch_bounds__(64 * kWaves) void k_prefill_reduce(const PrefillPar
 
 template <int BITS>
 hipError_t launch_fused(const PrefillParams& p, int rt, dim3 grid, hipStream_t s) {
-  if (rt == 7) k_prefill_fused<BITS, 7><<<grid, 64 * kWaves, 0, s>>>(p);
-  else k_prefill_fused<BITS, 8><<<grid, 64 * kWaves, 0, s>>>(p);
+  const int most = longest(p.blocks);
+  const bool brief = p.n_split == 1 && p.steps_per_split <= kShortSteps && most > 12 && most <= 16;
+  if (rt == 7) {
+    if (brief) k_prefill_fused<BITS, 7, true><<<grid, 64 * kWaves, 0, s>>>(p);
+    else k_prefill_fused<BITS, 7, false><<<grid, 64 * kWaves, 0, s>>>(p);
+  } else {
+    if (brief) k_prefill_fused<BITS, 8, true><<<grid, 64 * kWaves, 0, s>>>(p);
+    else k_prefill_fused<BITS, 8, false><<<grid, 64 * kWaves, 0, s>>>(p);
+  }
   return hipGetLastError();
 }
 

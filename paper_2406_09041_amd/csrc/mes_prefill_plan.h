@@ -35,6 +35,10 @@ struct Blocks {
   int full0[kMaxSegs], tile0[kMaxSegs];        // of a segment: its first full block, its first tile
 };
 constexpr int count(const Blocks& bl) { return bl.n_list + bl.n_full + bl.n_half; }
+constexpr int longest(const Blocks& bl) {                       // ... block's tiles
+  const int listed = bl.n_list > 0 ? bl.list[0].shape >> 3 : 0;
+  return bl.n_full > 0 && bl.full_tiles > listed ? bl.full_tiles : listed;
+}
 constexpr TokenBlock unlisted_block(const Blocks& bl, int b) {   // b counts from the first one behind the list
   b += bl.first;
   int half = 0, tiles = bl.full_tiles;

@@ -1,10 +1,13 @@
-"""Long segments on the one-product path: calls of more token blocks than a launch lists one by one."""
+"""Long segments on the one-product path: calls of more token blocks than a launch lists one by one, short contractions."""
 import pytest
+import torch
 
 from inputs import synth
-from test_gpu_parity import run_case
+from test_gpu_parity import TOL, run_case, sampled_rows_check
 
 pytestmark = pytest.mark.gpu
+mes = pytest.importorskip("paper_2406_09041_amd")
+DEV = "cuda:0"
 
 
 def offsets(lengths):
@@ -21,3 +24,36 @@ def offsets(lengths):
 ])
 def test_more_blocks_than_the_list_holds(d_in, d_out, k, bits, lengths):
     run_case(synth.small_case(d_in, d_out, offsets(lengths), k, bits, seed=len(lengths)))
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("d_in,d_out,k,lengths", [
+    (264, 7448, 8, [784]),                   # 8 row tiles; blocks of 13 tiles (the last column of wavefronts has one) and of 12
+    (648, 9000, 0, [220, 205]),              # 7 row tiles; 14 tiles (the last column has none) and 13
+    (264, 9000, 33, [256, 272, 200]),        # 16 tiles, and halves of 17
+])
+def test_short_contractions(d_in, d_out, k, lengths, bits):
+    """Blocks of 13 to 16 token tiles in launches of few steps: eight columns of wavefronts instead of four.  Every tile of
+    16 x 16 results within the path's Frobenius tolerance (256 errors of about 1.4 sigma = 2.3e-3 each; 16 rows' share of the norm
+    varies by a few times 1 / 16, hence twice the tolerance), and the element-wise bars on 512 channels (6 sigma of a sum of
+    d_in rounding errors, whose tails are a little heavier than normal, is exceeded about once in 4 million elements)."""
+    wl = synth.small_case(d_in, d_out, offsets(lengths), k, bits, seed=len(lengths), device=DEV)
+    w_t = mes.mes_pack_base(wl.w_base)
+    ge = [mes.mes_pack_delta(ex.delta, ex.salient_idx.to(DEV), bits) for ex in wl.experts]
+    y = torch.full((wl.x.shape[0], d_out), float("nan"), dtype=torch.bfloat16, device=DEV)
+    mes.DeltaLinear(w_t, ge, max_tokens=wl.x.shape[0])(wl.x, wl.seg_offsets, y)
+    torch.cuda.synchronize()
+    for p, lo, hi in zip(ge, wl.seg_offsets, wl.seg_offsets[1:]):
+        w = wl.w_base.double() + mes.mes_unpack_delta(p, want_codes=False)[0].double()
+        ref = wl.x[lo:hi].double() @ w.t()
+
+        def tiles(v):                        # sums of squares of the 16 x 16 tiles
+            v = torch.nn.functional.pad(v * v, (0, -d_out % 16, 0, -(hi - lo) % 16))
+            return v.reshape(-(-(hi - lo) // 16), 16, -(-d_out // 16), 16).sum((1, 3))
+        assert (tiles(y[lo:hi].double() - ref) <= (2 * TOL) ** 2 * tiles(ref)).all(), (lo, hi)
+    assert sampled_rows_check(wl, y, 512, 3 + bits) <= TOL
+
+
+def test_short_contractions_of_more_blocks_than_the_list_holds():
+    """16-tile blocks and partial ones of 4 tiles in one launch."""
+    run_case(synth.small_case(136, 64, offsets([8000] * 8), 8, 2, seed=4))
