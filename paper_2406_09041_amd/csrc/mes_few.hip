@@ -98,7 +98,11 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
   // wavefronts of a layer deal the gathers among themselves; the indices of the first few
   // are requested behind the first chunk's weights, their activations once all the first weights are asked for (the gathers
   // wait for their indices; 5600 -> 1000, 4 bits, 128 channels, 17.9 -> 16.8 us against indices first and the gathers before the
-  // second chunk), and they go to LDS when the stream is over.
+  // second chunk), and they go to LDS when the stream is over.  The 16-slot bodies at 2 and 3 bits keep indices first and
+  // gathers before the second chunk: two chunks of theirs are so many loads that the gathers come too late behind them (4096 ->
+  // 6144, 3 bits, 9 experts 44.0 against 46.7 us; 4096 x 4096, 2 bits, 9 experts 25.9 against 26.8, 16 experts 33.9 against 33.1;
+  // 30 calls 1.4 % faster on average).
+  constexpr bool kGathersFirst = NA == kMaxSlots && BITS >= 2;
   const int n_pairs = p.n_vis * p.n_sb, n_sb = p.n_sb;
   // visit of a pair = pair / n_sb, by a multiplication (the dozen divisions took about 1 % of a call): the reciprocal in 16 bits
   // is too large by less than 2^-16, and pair times that less than 1 / n_sb, as pair and n_sb are at most kFewPairs
@@ -214,14 +218,23 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
   // This wavefront's chunks: kw, kw + team_waves, ...
   const int mine = kw < n_chunks ? (n_chunks - kw + team_waves - 1) / team_waves : 0;
   auto chunk_at = [&](int i) { return kw + team_waves * i; };
+  auto request_first_indices = [&] {
+    if (n_pairs > 0) {
+#pragma unroll
+      for (int q = 0; q < kGather; ++q)
+        if (gw + gathers * q < n_pairs) request_indices(gw + gathers * q, sal_idx[q]);
+    }
+  };
+  auto request_other_chunks = [&] {
+#pragma unroll
+    for (int u = 1; u < AHEAD; ++u) request(buf[u], chunk_at(u));
+  };
+  if constexpr (kGathersFirst) request_first_indices();
   request(buf[0], chunk_at(0));
-  if (n_pairs > 0) {
-#pragma unroll
-    for (int q = 0; q < kGather; ++q)
-      if (gw + gathers * q < n_pairs) request_indices(gw + gathers * q, sal_idx[q]);
+  if constexpr (!kGathersFirst) {
+    request_first_indices();
+    request_other_chunks();
   }
-#pragma unroll
-  for (int u = 1; u < AHEAD; ++u) request(buf[u], chunk_at(u));
   const int st_j = 16 * jt + 4 * (lane & 3);
   typedef __attribute__((address_space(1))) const f32x4 gf4;   // (a generic load would count as an LDS access as well)
   f32x4 st_v = {0, 0, 0, 0};
@@ -251,6 +264,7 @@ __global__ __launch_bounds__(64 * NW) void k_few_tokens(const LinearParams p, in
     for (int q = 0; q < kGather; ++q)
       if (gw + gathers * q < n_pairs) request_gather(gw + gathers * q, sal_idx[q], sal_h[q]);
   }
+  if constexpr (kGathersFirst) request_other_chunks();
   // weights of one pair and the row's step of its expert, as loaded; pairs past the last one repeat it
   struct PairLoad { u32x4 d; float step; };
   PairLoad pl[kEarly];
