@@ -1,9 +1,11 @@
-"""Long segments on the one-product path: calls of more token blocks than a launch lists one by one, short contractions."""
+"""Long segments on the one-product path: calls of more token blocks than a launch lists one by one, short
+contractions, layers that share their activations."""
 import pytest
 import torch
 
 from inputs import synth
-from test_gpu_parity import TOL, run_case, sampled_rows_check
+from oracle import mes_oracle as O
+from test_gpu_parity import TOL, check_rows, gpu_experts, oracle_experts, run_case, sampled_rows_check
 
 pytestmark = pytest.mark.gpu
 mes = pytest.importorskip("paper_2406_09041_amd")
@@ -57,3 +59,27 @@ def test_short_contractions(d_in, d_out, k, lengths, bits):
 def test_short_contractions_of_more_blocks_than_the_list_holds():
     """16-tile blocks and partial ones of 4 tiles in one launch."""
     run_case(synth.small_case(136, 64, offsets([8000] * 8), 8, 2, seed=4))
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("d_in,d_outs,k,lengths", [
+    (248, [136, 72, 200], 40, [300, 5, 210]),     # one launch per layer: the scratch has no room for three layers' gathered channels
+    (120, [72, 328], 8, [193, 450]),              # ... nor for two beside one chunk
+    (1024, [72, 136], 512, [200]),                # one launch, three splits: the last one has nothing but salient steps
+    (2048, [72, 136, 64], 600, [200, 3]),         # five: one goes over to the salient steps of its layer, one begins in them
+    (520, [72, 264, 136], 33, [449]),             # one salient step per layer
+])
+def test_long_segments_of_layers_that_share_their_activations(d_in, d_outs, k, lengths, bits):
+    """Each layer has salient channels of its own, gathered behind the shared input channels or, where they do not fit, in the
+    same place one layer after the other."""
+    off = offsets(lengths)
+    wls = [synth.small_case(d_in, d, off, k, bits, seed=70 + i) for i, d in enumerate(d_outs)]
+    x = wls[0].x
+    layers = [(mes.mes_pack_base(w.w_base.to(DEV)), gpu_experts(w)) for w in wls]
+    ys = [torch.full((off[-1], d), float("nan"), dtype=torch.bfloat16, device=DEV) for d in d_outs]
+    mes.DeltaLinearMulti(layers, off[-1])(x.to(DEV), off, ys)
+    torch.cuda.synchronize()
+    for w, y in zip(wls, ys):
+        w.x = x
+        oe, w64 = oracle_experts(w), w.w_base.double().numpy()
+        check_rows(w, y, O.delta_linear(x.double().numpy(), w64, oe, off), oe, w64, what=w.d_out)

@@ -1,6 +1,7 @@
-"""One-product path: segments whose last block of 256 tokens is partial take fewer token tiles per multiplier (one for up to
-64 tokens, two for 128, three for 192) and run behind the full ones.  Every number of tiles, with the contraction split
-over workgroups (few rows) and not, 7 and 8 row tiles per workgroup, one launch and two."""
+"""One-product path: a segment's tokens are cut into blocks of up to 32 token tiles, its last one or all of them partial; a block
+of up to 4, 8, 12 or 16 tiles has its k blocks shared by two wavefronts per column, one of more has eight columns of three or
+four.  Every number of tiles, with the contraction split over workgroups (few rows) and not, 7 and 8 row tiles per workgroup,
+one launch and two."""
 import pytest
 
 from inputs import synth
