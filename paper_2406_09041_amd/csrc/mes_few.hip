@@ -441,7 +441,8 @@ bool few_tokens_fits(const LinearParams& p) {
 // preparation of the activations (which every row tile's wavefronts do again, per tile of tokens), and the
 // wavefronts' shares of the salient pairs; plus a share of the weights' way from memory.  The terms are those of the
 // kernel, the numbers least squares over 1800 calls (d_in and d_out from 256 to 14336, one layer, two or three, gated
-// pairs, 1 to 32 tokens, 1 to 16 experts, 1 to 4 bits, up to 128 salient channels); 9 % off on 1250 others.
+// pairs, 1 to 32 tokens, 1 to 16 experts, 1 to 4 bits, up to 128 salient channels); 11 % off on 1135 others, 4 % of it too
+// high: the kernel has become faster since.
 double few_tokens_us(const LinearParams& p) {
   const FewPlan f = few_plan(p);
   const int rounds = (f.grid + 255) / 256, more = p.tiles - 1;

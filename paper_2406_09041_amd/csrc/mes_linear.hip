@@ -786,8 +786,8 @@ Plan plan_for(int d_in, const int* d_out, int n_linears, bool pair) {
 }
 
 // Expected time of a token group of few tokens, or of two in one launch, on the streaming path, us (for the choice between
-// the two paths; see few_tokens_us for the calls the numbers come from; 8 % off on those not used for them, two groups 13 %,
-// 9 % of it too low).  Workgroups are dealt to 8 XCDs of 32 compute units; the fullest XCD counts the rounds.  Salient
+// the two paths; see few_tokens_us for the calls the numbers come from; with the present kernels 8.5 % off on 1135 calls not
+// used for them, two groups, 67 calls, 14 %, 12 % of it too low).  Workgroups are dealt to 8 XCDs of 32 compute units; the fullest XCD counts the rounds.  Salient
 // pairs that the chunks cannot carry are multiplied one after the other.
 double streaming_us(const LinearParams& a, const LinearParams* b, const Plan& pl, int rgs) {
   const int groups = b ? 2 : 1, rounds = (groups * ((rgs * pl.nsplit + 7) / 8) + 31) / 32;
@@ -877,7 +877,9 @@ hipError_t launch_reduce(const LaunchParams& mp, int tt, int nw, hipStream_t s) 
 
 // Expert segments at least this long take the one-product path of mes_prefill.hip (W + Delta~ formed in registers,
 // one dense contraction) when the workspace has room for it: from here on it is cheaper than streaming the weights
-// once per 64 tokens.
+// once per 64 tokens.  It has become cheaper below that too (4096 -> 14336, 2 bits, one expert with 64 / 128 / 192 tokens: streaming
+// 50 / 73 / 102 us, one product 41 / 48 / 53; 4 bits 53 / 82 / 118 against 44 / 52 / 56), but it rounds W + Delta~ to bf16 where
+// the streaming path's products are exact: shorter segments keep their precision.
 constexpr int kPrefillMin = 192;
 int long_segment_tokens() { return kPrefillMin; }
 
@@ -1060,12 +1062,13 @@ hipError_t launch_delta_linear(const LinearCall& c, hipStream_t s) {
         //   streaming: gated pairs that leave a round of its workgroups half empty (5120 -> 11008, 6 tokens of 3 experts 70.3
         //     against 83.0) or have many experts on many rows (4096 -> 14336, 1 bit, 9 experts 88.5 against 96.3), long columns
         //     (14336 -> 5120, 9 experts 77.3 against 91.5), most groups of two tiles on more than 4 chunks per wavefront.
-        // Over 3077 calls the choice costs 0.3 % against the better of the two.  (Equal expectations: the streaming path.)
+        // Over 1135 calls of the present kernels the choice costs 0.5 % against the better of the two; 14 of them take more than 3 %
+        // longer than on the streaming path, 11 % at worst.  (Equal expectations: the streaming path.)
         // A call of few tokens is two groups if more than kMaxSlots experts own them.  Where one launch can take the first, that
         // has a token of each of its experts, and the second is one tile too.  Both take the same path, one launch each or
         // one streaming launch with both, whatever the workspace has room for.  (1024 x 1024, 2 bits, 32 tokens of as many
-        // experts: 32.4 us streaming against 33.6; 4096 x 4096, 24 of 24: 63.0 against 55.9.  900 such calls: 0.88 of the
-        // streaming path's time, 14 of them more than 3 % slower, 19 % at worst.)
+        // experts: 32.4 us streaming against 33.6; 4096 x 4096, 24 of 24: 63.0 against 55.9.  67 such calls of the present kernels:
+        // 0.87 of the streaming path's time, 2 of them more than 3 % slower, 13 % at worst.)
         if (p.t0 == 0 && c.T <= 32 && few_tokens_fits(p)) {
           if (nt == c.T) {
             few = few_tokens_us(p) < 0.97 * streaming_us(p, nullptr, pl, rgs);
