@@ -678,7 +678,7 @@ hipError_t launch_prefill_segments(const mes_linear* lin, int n_linears, const i
         }
         if (ev_stop && (e = hipEventRecord(ev_stop, s)) != hipSuccess) return e;
         left -= blocks;
-        p.blocks = behind(p.blocks, blocks);
+        if (left > 0) p.blocks = behind(p.blocks, blocks);
       }
     }
   }

@@ -83,13 +83,55 @@ struct PrefillPlan {
   Blocks blocks;
 };
 
+// How a launch's tokens are cut: blocks of at most `most` tiles; even: a segment's blocks alike, else full ones and what is
+// left; the last `halved` full blocks (of kBlockTiles) become two each.
+struct Cut { int most; bool even; int halved; };
+
+constexpr int size_class(int tiles) { return (tiles - 1) / 4; }
+constexpr int kClasses = kBlockTiles / 4;
+
+// What the plan weighs of a cut: how many blocks are listed, by size, and how many are not.  Counted by segments, without
+// making the list: a plan weighs up to 16 cuts and takes one, and small calls are as long as the host takes to launch them (128
+// -> 368, 1091 + 372 tokens, with a list made per cut 11.7 us of host time, 11.8 a call; now 11.2 and 11.4).
+struct Sizes { int listed[kClasses], n_full, n_half, full_tiles, total; bool list_all; };
+inline Sizes sizes_of(const int* seg_tiles, int n_seg, Cut c) {
+  Sizes z = {};
+  z.full_tiles = c.most;
+  int full = 0;
+  z.total = c.halved;
+  for (int i = 0; i < n_seg; ++i) {
+    full += seg_tiles[i] / c.most;
+    z.total += (seg_tiles[i] + c.most - 1) / c.most;
+  }
+  z.list_all = z.total <= kMaxBlocks;
+  if (!z.list_all) {
+    z.n_full = full - c.halved;
+    z.n_half = 2 * c.halved;
+  }
+  for (int i = 0; i < n_seg; ++i) {
+    const int r = seg_tiles[i], nb = (r + c.most - 1) / c.most, left = r % c.most;
+    if (z.list_all && c.even) {                                // r % nb blocks have a tile more than the others
+      z.listed[size_class(r / nb)] += nb - r % nb;
+      if (r % nb > 0) z.listed[size_class(r / nb + 1)] += r % nb;
+    } else {
+      if (z.list_all) z.listed[size_class(c.most)] += r / c.most;
+      if (left > 0) ++z.listed[size_class(left)];
+    }
+  }
+  if (z.list_all && c.halved > 0) {
+    z.listed[size_class(kBlockTiles)] -= c.halved;
+    z.listed[size_class(kBlockTiles / 2)] += 2 * c.halved;
+  }
+  return z;
+}
+
 // When the compute units are done that take, from a list, every token block's n_rg workgroups, each as soon as one is free.
-inline double launch_time(const Blocks& bl, int n_rg, int rt, int steps, int n_split) {
+inline double launch_time(const Sizes& z, int n_rg, int rt, int steps, int n_split) {
   struct { double at; int units; } pool[48];                   // compute units by the time they are free
   int n = 1;
   pool[0] = {0.0, kMaxWorkgroups};
   double end = 0.0;
-  const bool alone = (long)count(bl) * n_rg * n_split <= kMaxWorkgroups;
+  const bool alone = (long)z.total * n_rg * n_split <= kMaxWorkgroups;
   auto take_blocks = [&](int tiles, long blocks) {
     const double t = block_time(rt, tiles, steps, alone);
     for (long left = blocks * n_rg * n_split; left > 0;) {
@@ -112,49 +154,40 @@ inline double launch_time(const Blocks& bl, int n_rg, int rt, int steps, int n_s
       }
     }
   };
-  auto listed = [&](int i) { return bl.list[i].shape >> 3; };
-  for (int i = 0; i < bl.n_list;) {
-    int same = i + 1;
-    while (same < bl.n_list && (listed(same) - 1) / 4 == (listed(i) - 1) / 4) ++same;
-    take_blocks(listed(i), same - i);
-    i = same;
-  }
-  if (bl.n_full > 0) take_blocks(bl.full_tiles, bl.n_full);
-  if (bl.n_half > 0) take_blocks(bl.full_tiles / 2, bl.n_half);
+  for (int c = kClasses - 1; c >= 0; --c)
+    if (z.listed[c] > 0) take_blocks(4 * c + 1, z.listed[c]);
+  if (z.n_full > 0) take_blocks(z.full_tiles, z.n_full);
+  if (z.n_half > 0) take_blocks(z.full_tiles / 2, z.n_half);
   return end;
 }
 
-// The segments' tokens as blocks of at most `most` tiles, the longest first.  even: a segment's blocks alike, else full ones
-// and what is left.  The last `halved` full blocks (of kBlockTiles) become two each.
-inline void cut_blocks(Blocks& bl, const int* seg_tiles, int n_seg, int most, bool even, int halved) {
-  bl.n_full = bl.n_half = bl.n_list = bl.first = 0;
-  bl.full_tiles = most;
-  int tile0 = 0, full = 0, blocks = halved;
+// The segments' tokens as blocks, the longest first.
+inline void cut_blocks(Blocks& bl, const int* seg_tiles, int n_seg, Cut c) {
+  const Sizes z = sizes_of(seg_tiles, n_seg, c);
+  bl.n_list = bl.first = 0;
+  bl.n_full = z.n_full;
+  bl.n_half = z.n_half;
+  bl.full_tiles = c.most;
+  int tile0 = 0, full = 0;
   for (int i = 0; i < kMaxSegs; ++i) {
     bl.full0[i] = full;
     bl.tile0[i] = tile0;
     if (i >= n_seg) continue;
-    full += seg_tiles[i] / most;
-    blocks += (seg_tiles[i] + most - 1) / most;
+    full += seg_tiles[i] / c.most;
     tile0 += seg_tiles[i];
   }
-  const bool list_all = blocks <= kMaxBlocks;
-  if (!list_all) {
-    bl.n_full = full - halved;
-    bl.n_half = 2 * halved;
-  }
   for (int i = 0; i < n_seg; ++i) {
-    const int r = seg_tiles[i], nb = (r + most - 1) / most;
-    for (int b = list_all ? 0 : r / most; b < nb; ++b) {
-      const bool alike = even && list_all;
-      const int lo = alike ? (int)((long)r * b / nb) : b * most, end = alike ? (int)((long)r * (b + 1) / nb) : lo + most, hi = end < r ? end : r;
-      const bool halve = list_all && halved > 0 && hi - lo == kBlockTiles && full-- <= halved;
+    const int r = seg_tiles[i], nb = (r + c.most - 1) / c.most;
+    for (int b = z.list_all ? 0 : r / c.most; b < nb; ++b) {
+      const bool alike = c.even && z.list_all;
+      const int lo = alike ? (int)((long)r * b / nb) : b * c.most, end = alike ? (int)((long)r * (b + 1) / nb) : lo + c.most, hi = end < r ? end : r;
+      const bool halve = z.list_all && c.halved > 0 && hi - lo == kBlockTiles && full-- <= c.halved;
       const int mid = halve ? (lo + hi) / 2 : hi;
       bl.list[bl.n_list++] = block_entry({i, bl.tile0[i] + lo, mid - lo});
       if (halve) bl.list[bl.n_list++] = block_entry({i, bl.tile0[i] + mid, hi - mid});
     }
   }
-  auto size = [](const BlockEntry& e) { return ((e.shape >> 3) - 1) / 4; };
+  auto size = [](const BlockEntry& e) { return size_class(e.shape >> 3); };
   for (int i = 1; i < bl.n_list; ++i) {                        // insertion: stable, and nearly sorted already
     const BlockEntry v = bl.list[i];
     int j = i;
@@ -169,47 +202,49 @@ inline void cut_blocks(Blocks& bl, const int* seg_tiles, int n_seg, int most, bo
 // seg_tiles: 16-token tiles of every segment; d_out: of every layer.
 inline void prefill_plan(PrefillPlan& best, const int* seg_tiles, int n_seg, const int* d_out, int n_linears, int steps) {
   double best_time = 1e30;
-  Blocks bl;
+  Cut best_cut = {kBlockTiles, false, 0};
   double elements = 0;
   for (int l = 0; l < n_linears; ++l) elements += d_out[l];
-  int tiles = 0;
-  for (int i = 0; i < n_seg; ++i) tiles += seg_tiles[i];
+  int tiles = 0, full = 0;
+  for (int i = 0; i < n_seg; ++i) {
+    tiles += seg_tiles[i];
+    full += seg_tiles[i] / kBlockTiles;
+  }
   elements *= 16.0 * tiles;
   for (int rt = 8; rt >= 7; --rt) {
     int n_rg = 0;
     for (int l = 0; l < n_linears; ++l) n_rg += (row_tiles(d_out[l]) + rt - 1) / rt;
-    auto consider = [&](int most, bool even, int halved) {
-      cut_blocks(bl, seg_tiles, n_seg, most, even, halved);
-      // fewer workgroups than compute units: share the steps out, at least four to each
-      const long wgs = (long)n_rg * count(bl);
-      for (int want = 1; want <= 8 && want * wgs <= kMaxWorkgroups && (want == 1 || 4 * want <= steps); ++want) {
-        const int per = (steps + want - 1) / want, n_split = (steps + per - 1) / per;
+    auto consider = [&](Cut c) {
+      const Sizes z = sizes_of(seg_tiles, n_seg, c);
+      auto weigh = [&](int n_split, int per) {
         // (partial sums: written and read at about 9 TB/s, and another launch)
-        const double t = launch_time(bl, n_rg, rt, per, n_split) + (n_split > 1 ? 4.0 + n_split * elements * 8.0 / 9e6 : 0.0);
-        if (t < 0.99 * best_time) { best_time = t; best.rt = rt; best.n_split = n_split; best.steps_per_split = per; best.blocks = bl; }
+        const double t = launch_time(z, n_rg, rt, per, n_split) + (n_split > 1 ? 4.0 + n_split * elements * 8.0 / 9e6 : 0.0);
+        if (t < 0.99 * best_time) { best_time = t; best.rt = rt; best.n_split = n_split; best.steps_per_split = per; best_cut = c; }
+      };
+      // fewer workgroups than compute units: share the steps out, at least four to each
+      const long wgs = (long)n_rg * z.total;
+      for (int want = 1; want <= 8 && want * wgs <= kMaxWorkgroups && (want == 1 || 4 * want <= steps); ++want) {
+        const int per = (steps + want - 1) / want;
+        weigh((steps + per - 1) / per, per);
       }
-      if (wgs > kMaxWorkgroups) {
-        const double t = launch_time(bl, n_rg, rt, steps, 1);
-        if (t < 0.99 * best_time) { best_time = t; best.rt = rt; best.n_split = 1; best.steps_per_split = steps; best.blocks = bl; }
-      }
+      if (wgs > kMaxWorkgroups) weigh(1, steps);
     };
-    consider(32, false, 0);
-    int full = 0;
-    for (int i = 0; i < n_seg; ++i) full += seg_tiles[i] / kBlockTiles;
+    consider({32, false, 0});
     const int over = (int)((long)full * n_rg % kMaxWorkgroups), h = over / n_rg;   // full workgroups of the last round
-    if (over > 0 && h > 0) consider(32, false, h);
-    if (over > 0 && h < full) consider(32, false, h + 1);
+    if (over > 0 && h > 0) consider({32, false, h});
+    if (over > 0 && h < full) consider({32, false, h + 1});
     if (full * (long)n_rg < 4 * kMaxWorkgroups) {
-      consider(32, true, 0);
-      consider(24, true, 0);
-      consider(16, true, 0);
-      if (tiles * (long)n_rg < 12 * kMaxWorkgroups) consider(12, true, 0);
+      consider({32, true, 0});
+      consider({24, true, 0});
+      consider({16, true, 0});
+      if (tiles * (long)n_rg < 12 * kMaxWorkgroups) consider({12, true, 0});
       // launches that blocks of 8 or 4 tiles do not make longer than about a round: the chip is idle otherwise, and a block of 4
       // tiles takes 1 us a step where one of 12 takes 1.5 (1648 -> 1920, 702 tokens 27.9 us with at least 11 tiles, now 22.4)
-      if (tiles * (long)n_rg < 12 * kMaxWorkgroups) consider(8, true, 0);
-      if (tiles * (long)n_rg < 8 * kMaxWorkgroups) consider(4, true, 0);
+      if (tiles * (long)n_rg < 12 * kMaxWorkgroups) consider({8, true, 0});
+      if (tiles * (long)n_rg < 8 * kMaxWorkgroups) consider({4, true, 0});
     }
   }
+  cut_blocks(best.blocks, seg_tiles, n_seg, best_cut);
 }
 
 }  // namespace mes

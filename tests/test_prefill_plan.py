@@ -34,6 +34,17 @@ int make_plan(const int* seg_tiles, int n_seg, const int* d_out, int n_linears, 
   }
   return 0;
 }
+// a cut as the plan weighs it, and as it is made: blocks by size, full and halved ones by arithmetic, all
+void weighed_and_made(const int* seg_tiles, int n_seg, int most, int even, int halved, int* weighed, int* made) {
+  const Cut c = {most, even != 0, halved};
+  const Sizes z = sizes_of(seg_tiles, n_seg, c);
+  Blocks bl;
+  cut_blocks(bl, seg_tiles, n_seg, c);
+  for (int i = 0; i < kClasses; ++i) { weighed[i] = z.listed[i]; made[i] = 0; }
+  for (int b = 0; b < bl.n_list; ++b) ++made[size_class(bl.list[b].shape >> 3)];
+  weighed[kClasses] = z.n_full; weighed[kClasses + 1] = z.n_half; weighed[kClasses + 2] = z.total;
+  made[kClasses] = bl.n_full; made[kClasses + 1] = bl.n_half; made[kClasses + 2] = count(bl);
+}
 }
 """
 
@@ -90,6 +101,20 @@ def test_every_token_is_planned_once(plan, seed):
         seg = [int(v) for v in np.exp(rng.uniform(np.log(lo), np.log(hi), rng.integers(1, 9)))]
         d_outs = [int(v) for v in np.exp(rng.uniform(np.log(1), np.log(4000), rng.integers(1, 4)))]
         checked_plan(plan, seg, [4 * d for d in d_outs], int(rng.integers(1, 200)))
+
+
+@pytest.mark.parametrize("seed", range(20))
+def test_cuts_are_weighed_as_they_are_made(plan, seed):
+    """The plan counts a cut's blocks by segments; the blocks themselves are made of the cut that is taken only."""
+    rng = np.random.default_rng(100 + seed)
+    for _ in range(50):
+        n, hi = int(rng.integers(1, 9)), (40, 300, 3000)[seed % 3]
+        seg = (ctypes.c_int * n)(*[int(v) for v in np.exp(rng.uniform(0, np.log(hi), n))])
+        full = sum(t // 32 for t in seg)
+        for most, even, halved in [(m, 1, 0) for m in (4, 8, 12, 16, 24, 32)] + [(32, 0, h) for h in {0, full // 2, full}]:
+            weighed, made = (ctypes.c_int * 11)(), (ctypes.c_int * 11)()
+            plan.weighed_and_made(seg, n, most, even, halved, weighed, made)
+            assert list(weighed) == list(made), (list(seg), most, even, halved)
 
 
 @pytest.mark.parametrize("tokens,d_out,halves", [
