@@ -91,7 +91,7 @@ constexpr int size_class(int tiles) { return (tiles - 1) / 4; }
 constexpr int kClasses = kBlockTiles / 4;
 
 // What the plan weighs of a cut: how many blocks are listed, by size, and how many are not.  Counted by segments, without
-// making the list: a plan weighs up to 16 cuts and takes one, and small calls are as long as the host takes to launch them (128
+// making the list: a plan weighs up to 18 cuts and takes one, and small calls are as long as the host takes to launch them (128
 // -> 368, 1091 + 372 tokens, with a list made per cut 11.7 us of host time, 11.8 a call; now 11.2 and 11.4).
 struct Sizes { int listed[kClasses], n_full, n_half, full_tiles, total; bool list_all; };
 inline Sizes sizes_of(const int* seg_tiles, int n_seg, Cut c) {
