@@ -193,8 +193,9 @@ __device__ __forceinline__ void multiply_rows(const PrefillParams& p, const Pref
   // Sets of activation fragments: what the registers hold (512 of them per lane and SIMD, two wavefronts) with nothing put aside
   // in the main loop.  (The last steps of the bodies of 4 tiles and 8 rows do put 20 to 55 registers aside.  A third set at 3 and
   // 4 bits with 8 rows had scratch accesses in every main step: 4096 tokens of 4 experts on 14336 -> 4096, 3 / 4 bits 466 / 460
-  // us, with two sets 446 / 452; at 1 and 2 bits two sets instead of three are 4 % slower.)
-  constexpr int XD = TT == 0 ? 1 : TT <= 2 ? 4 : KS == 2 ? 2 : (RT == 7 ? (BITS <= 2 ? 4 : 3) : BITS <= 2 ? 3 : 2);
+  // us, with two sets 446 / 452; at 1 and 2 bits two sets instead of three are 4 % slower, and so are blocks of 17 to 24 tiles at 3
+  // and 4 bits, by 1 to 2 %: 13248 -> 8048, 491 + 567 tokens, 3 bits, 276 us with two, 271 with three.)
+  constexpr int XD = TT == 0 ? 1 : TT <= 2 ? 4 : KS == 2 ? 2 : (RT == 7 ? (BITS <= 2 ? 4 : 3) : BITS <= 2 || TT == 3 ? 3 : 2);
   constexpr int U = NBW % XD == 0 ? 1 : (2 * NBW) % XD == 0 ? 2 : 3;   // steps until the sets come round
   static_assert((U * NBW) % XD == 0, "the sets are named at compile time");
   static_assert(NOP % NBW == 0, "every k block has the same number of operands to build");

@@ -83,3 +83,10 @@ def test_long_segments_of_layers_that_share_their_activations(d_in, d_outs, k, l
         w.x = x
         oe, w64 = oracle_experts(w), w.w_base.double().numpy()
         check_rows(w, y, O.delta_linear(x.double().numpy(), w64, oe, off), oe, w64, what=w.d_out)
+
+
+@pytest.mark.parametrize("bits", [3, 4])
+@pytest.mark.parametrize("d_out,lengths", [(9488, [265, 405])])
+def test_blocks_of_17_to_24_tiles_with_8_row_tiles(d_out, lengths, bits):
+    """... keep three sets of activation fragments at 3 and 4 bits, where full blocks have two; 9 chunks and a salient step."""
+    run_case(synth.small_case(1032, d_out, offsets(lengths), 33, bits, seed=bits))
